@@ -6,13 +6,16 @@ a circle of radius 0.15 L at (L/2, 3L/4) in the time-reversing single vortex
 (max |u| = 0.05, T = 80000 steps), velocity from separable 1-D tables (seeded
 synthetic inputs shaped like the paper's deformation tests).
 
-A step is one launch of the fused kernel (pull, phi, mu, F1 + F2, collision,
-store) over the whole lattice.  Prints one JSON line:
+A step is one launch of the fused kernel (phi, mu, F1 + F2, collision, streaming) over
+the whole lattice.  A call of several steps passes the sum of the populations (one FP64
+value per node) from step to step: its first step reads the nine float32 populations, its
+last one writes them.  Prints one JSON line:
   value        MLUPS = nx*ny*steps / time of the timed steps (inputs resident in HBM)
-  roofline     algorithmic bytes (72 B per node update: 9 float32 populations read and
-               9 written) / average kernel duration from HIP events, against the
-               8 TB/s HBM peak; traffic = measured HBM bytes per launch from the committed
-               rocprofv3 counter summary (null when the kernel source changed since)
+  roofline     algorithmic bytes (16 B per node update, 44 in the first and the last step)
+               / average kernel duration from HIP events, against the 8 TB/s HBM peak;
+               single_step: the same for calls of one step (72 B per node update), traffic
+               = measured HBM bytes per launch from the committed rocprofv3 counter summary
+               (null when the kernel source changed since)
   cpu_baseline the FP64 oracle on the host cores on a bounded number of steps
   accuracy     relative L2 of phi after 1000 steps against stored FP64 oracle samples
 """
@@ -31,7 +34,15 @@ sys.path.insert(0, ROOT)
 METRIC = ("MLUPS and % HBM peak (FP32 fused step, 2048^2) vs FP64 oracle accuracy; "
           "adjoint ms")
 HBM_PEAK_GBS = 8000.0
-BYTES_PER_LU = 72.0
+BYTES_PER_LU = 72.0  # one step of its own: nine populations read, nine written
+
+
+def run_bytes_per_lu(steps, state=36.0):
+    """Bytes per node update of one call of `steps` steps: `state` bytes of populations in
+    and out, and 8 bytes of sum field written and read between steps."""
+    return (2.0 * state + 16.0 * (steps - 1)) / steps
+
+
 # sources of the fused step kernel: a counter summary is used only while they are unchanged
 KERNEL_SRC = (os.path.join(ROOT, "paper_1805_00007_amd", "csrc", "lbm_ch_step.hip"),
               os.path.join(ROOT, "paper_1805_00007_amd", "csrc", "lbm_ch_device.h"),
@@ -162,8 +173,7 @@ def roofline(bytes_per_lu, nodes, us, kernel, profile, traffic=None):
 
 
 def storage_variant(lbm, torch, storage, steps):
-    """Same workload with 16-bit population storage (20 B per node update instead of 36
-    read and 36 written): throughput over at least 500 steps, and phi at the stored
+    """Same workload with 16-bit population storage (20 B of state per node): throughput over at least 500 steps, and phi at the stored
     1000-step oracle samples."""
     import numpy as np
     import workloads
@@ -180,12 +190,12 @@ def storage_variant(lbm, torch, storage, steps):
     ms = e0.elapsed_time(e1) / steps
     tiles = s.tiles
     s.close()
-    kernel = ("k_phi_pass (16-bit storage, single-pass tiles of 64 x %d)" % tiles[1]
-              if tiles[0] == 0 else "k_phi_step (16-bit storage, %d x %d tiles)" % tiles)
+    kernel = "k_phi_march (16-bit storage rounding, sum field between steps)"
+    lu = run_bytes_per_lu(steps, 20.0)
     out = {"MLUPS": round(w.nx * w.ny / (ms * 1e-3) / 1e6, 1), "ms_per_step": round(ms, 5),
-           "timed_steps": steps, "bytes_per_lu": 40, "tiles": list(tiles),
-           "effective_GBps": round(w.nx * w.ny * 40 / (ms * 1e-3) / 1e9, 1),
-           "roofline": roofline(40, w.nx * w.ny, ms * 1e3, kernel,
+           "timed_steps": steps, "bytes_per_lu": round(lu, 2), "tiles": list(tiles),
+           "effective_GBps": round(w.nx * w.ny * lu / (ms * 1e-3) / 1e9, 1),
+           "roofline": roofline(lu, w.nx * w.ny, ms * 1e3, kernel,
                                 "profiles/phi_step_vortex2048_16bit_kernel_trace.md")}
     if os.path.exists(GOLDEN):
         g = np.load(GOLDEN)
@@ -486,7 +496,7 @@ def main():
     t_ms = ev0.elapsed_time(ev1)
 
     # average duration of one launch of the fused kernel over the timed region: every
-    # step of this workload is exactly one launch of k_phi_step on `stream`, so the
+    # step of this workload is exactly one launch of k_phi_march on `stream`, so the
     # events around the region give the average launch duration (gaps between the
     # back-to-back launches included)
     k_ms = t_ms / args.steps
@@ -506,8 +516,10 @@ def main():
 
     nodes = w.nx * w.ny
     mlups = nodes * args.steps / (t_ms * 1e-3) / 1e6
-    algo = BYTES_PER_LU * nodes
+    lu = run_bytes_per_lu(args.steps)
+    algo = lu * nodes
     achieved = algo / (k_ms * 1e-3) / 1e9
+    single = BYTES_PER_LU * nodes / (iso_ms * 1e-3) / 1e9
     traffic = measured_traffic()
     out = {
         "metric": METRIC,
@@ -525,15 +537,19 @@ def main():
         "config": {"workload": w.name, "nx": w.nx, "ny": w.ny, "model": "II", "tau_g": 1.0,
                    "velocity": "single vortex, separable tables", "boundary": "periodic",
                    "storage": "f32"},
-        "effective_GBps": round(mlups * BYTES_PER_LU / 1e3, 1),
-        "hbm_frac_effective": round(mlups * BYTES_PER_LU / 1e3 / HBM_PEAK_GBS, 4),
+        "effective_GBps": round(mlups * lu / 1e3, 1),
+        "hbm_frac_effective": round(mlups * lu / 1e3 / HBM_PEAK_GBS, 4),
         "wall_s_timed": round(wall, 4),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic, "kernel": "k_phi_step",
+                     "kernel": "k_phi_march (vector-ALU bound: sum field between steps)",
                      "kernel_avg_us": round(k_ms * 1e3, 2),
-                     "isolated_launch_us": round(iso_ms * 1e3, 2),
-                     "algorithmic_bytes_per_launch": algo},
+                     "algorithmic_bytes_per_launch": algo,
+                     "single_step": {"kernel": "k_phi_step", "traffic": traffic,
+                                     "isolated_launch_us": round(iso_ms * 1e3, 2),
+                                     "achieved": round(single, 1),
+                                     "frac": round(single / HBM_PEAK_GBS, 4),
+                                     "algorithmic_bytes_per_launch": BYTES_PER_LU * nodes}},
     }
     if not args.no_accuracy:
         out["accuracy"] = accuracy(lbm, workloads.metric2048(steps=1000), torch)

@@ -163,7 +163,11 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
  * NS step) on `stream`.  The step counter n advances by nsteps.  With NS and model 1 or
  * 2 a step is one launch that advances f and g together (velocity and pressure are
  * formed inside it and not stored; lbm_ch_moments recomputes them); model 3 runs the NS
- * step and then the phase-field step.  Non-finite values:
+ * step and then the phase-field step.  Periodic lattices with a prescribed velocity at
+ * tau_g = 1, models 1 and 2: a call of several steps passes only the sum of the pulled
+ * populations (one FP64 value per node, which at tau_g = 1 is the whole state) from step
+ * to step and writes the populations in its last step; the state it leaves is bitwise
+ * that of as many calls of one step.  Non-finite values:
  * every step kernel raises a flag of the context when a phi it sums from the
  * populations is NaN or Inf; the flag lives in 4 bytes of pinned host memory mapped
  * into the device (allocated by lbm_ch_init, freed by lbm_ch_destroy), so it lands on
@@ -210,7 +214,10 @@ int lbm_ch_load_state(lbm_ch_ctx* ctx, const void* src, size_t bytes, int64_t st
  * single-pass tiles of 64 columns x ty rows (ty 4, 8 or 16) that pull their rows and a
  * margin of 2 at once, for periodic float32 lattices with a prescribed velocity at
  * tau_g = 1, models 1 and 2 (LBM_CH_EINVAL elsewhere).  The default is chosen at init
- * from the lattice size and storage; it changes speed only, never results.
+ * from the lattice size and storage; it changes speed only, never results.  Calls that
+ * pass the sum field from step to step (lbm_ch_step) choose their own strips, and so do
+ * calls of one step on some of those lattices while the default is in force: setting a
+ * shape makes it govern calls of one step.
  *   Where single-pass tiles serve: with float32 storage below 2048^2 nodes, tx = 0 with
  *   ty = 4 up to 65536 nodes, else 16; with 16-bit storage at every size, ty = 4 up to
  *   65536 nodes, 8 below 2048^2, else 16.
@@ -246,9 +253,10 @@ int lbm_ch_default_tiles(const lbm_ch_params* params, int32_t* tx, int32_t* ty);
  * LBM_CH_EINVAL for other values of enable. */
 int lbm_ch_set_graphs(lbm_ch_ctx* ctx, int32_t enable);
 
-/* Autotuner: time trial_steps >= 1 steps (after one untimed step) for each tile shape
+/* Autotuner: time trial_steps >= 1 single steps (after one untimed step) for each tile shape
  * tx in {64, 128, 256, 512} (skipping widths with more than half the lanes idle) and ty in
- * {1, 2, 4, 8, 16, 32}, keep the fastest, and restore the state and step counter from
+ * {1, 2, 4, 8, 16, 32}, and the default (lbm_ch_set_tiles) where that has strips of its
+ * own, keep the fastest, and restore the state and step counter from
  * `backup`, a caller device buffer of exactly lbm_ch_state_bytes(ctx) bytes.
  * Synchronises `stream`.  *best_us (may be NULL) receives the chosen shape's time per
  * step in microseconds. */

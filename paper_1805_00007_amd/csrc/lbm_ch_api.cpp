@@ -104,12 +104,14 @@ struct lbm_ch_ctx {
   void* g[2];
   float *f[2], *u, *v, *pr, *phi, *ztab, *xh;
   double *part, *diag;
+  double* m[2];  // sum fields of steps in the order-parameter form (over u, v, pr, phi)
   int cur;  // index of the buffer holding the current state
   int64_t step;
   int vmode;  // internal VelMode of the prescribed velocity
   const float *ax, *ay, *bx, *by, *ux, *uy;
   std::vector<double> tf;
   int tx, ty, nstrips, nblocks, xcd_remap;
+  bool march1;  // single steps run as marches (march_call); a tile shape set by the caller clears it
   int graphs;                     // lbm_ch_set_graphs: replay captured launch sequences
   hipStream_t cap;                // capture stream, created at the first capture
   std::vector<struct CtxExec> execs;  // cached executable graphs, most recently used last
@@ -287,10 +289,55 @@ static void default_tiles(const lbm_ch_params& p, int& tx_out, int& ty_out) {
   ty_out = ty;
 }
 
+// Rows per wave of a march between population and order-parameter form (launch_phi_march:
+// strips of 58 columns, four waves to a workgroup, so one on each SIMD of a CU).  A wave
+// pays its rows and about 2.3 rows' worth of entering rows; b workgroups to a CU share
+// its SIMDs, and a lone wave runs at 1 / 1.36 of a SIMD's rate.  The height with the
+// least (rows + 2.3) b therefore fills whole rounds of the 256 CUs.  Against a sweep of
+// heights 3 .. 74 the choice is within 5 % at every size from 128^2 to 5000 x 3900
+// (2048^2: within 3 % of the best; 6, 12, 24 and 32 rows cost 12-20 % more).
+static int march_rows(int nx, int ny) {
+  const long strips = (nx + 57) / 58;
+  int best = 4;
+  double cost = 1e30;
+  for (int ty = 4; ty <= 64; ++ty) {
+    const long blocks = (strips * ((ny + ty - 1) / ty) + 3) / 4;
+    const long b = (blocks + 255) / 256;
+    const double t = (ty + 2.3) * (b == 1 ? 1.36 : (double)b);
+    if (t < cost) {
+      cost = t;
+      best = ty;
+    }
+  }
+  return best;
+}
+
+// Whether a single step runs as a march from populations to populations instead of with
+// the context's tiles: 16-bit storage on lattices of 2 million nodes and more (us for a
+// step and the read-out of phi, tile / march, half storage: 1280^2 26.6 / 26.9, 2048^2 71 /
+// 64, 3000^2 150 / 129, 4000^2 252 / 244).  With float32 storage the tiles, which store
+// whole lines, are ahead or level at most sizes (768^2 16.4 / 16.7, 1024^2 23.0 / 23.4,
+// 1792^2 76 / 75; the step alone at 4096^2 216 / 310).
+static bool march_single(const lbm_ch_params& p) {
+  const int64_t nodes = (int64_t)p.nx * p.ny;
+  return p.storage != LBM_CH_STORE_F32 && nodes >= 2000000 && nodes <= (16 << 20);
+}
+
+// Whether a call of nsteps steps runs as marches: several steps in the order-parameter
+// form (us a step in calls of 2 / 100 steps, tiles against marches: 384^2 7.2 / 6.0 against
+// 7.0 / 4.8, 2048^2 64 / 62 against 34 / 24; a lattice of 256^2 nodes or fewer would gain
+// 0.4 us in long calls and lose as much in short ones), single ones by march_single.
+static bool march_call(const lbm_ch_ctx* c, int64_t nsteps) {
+  if (c->p.velocity_mode == LBM_CH_VEL_NS || nsteps < 1) return false;
+  if (!march_ok(c->p.walls != 0, c->vmode, c->p.model, tau_one(c))) return false;
+  return nsteps == 1 ? c->march1 : (int64_t)c->p.nx * c->p.ny > 65536;
+}
+
 static void choose_tiles(lbm_ch_ctx* c) {
   int tx, ty;
   default_tiles(c->p, tx, ty);
   apply_tiles(c, tx, ty);
+  c->march1 = march_single(c->p);
 }
 
 extern "C" {
@@ -360,6 +407,8 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   c->v = (float*)(c->ws + L.off_v);
   c->pr = (float*)(c->ws + L.off_p);
   c->phi = (float*)(c->ws + L.off_phi);
+  c->m[0] = (double*)(c->ws + L.off_u);
+  c->m[1] = c->m[0] + (size_t)p->nx * p->ny;
   c->ztab = (float*)(c->ws + L.off_ztab);
   c->part = (double*)(c->ws + L.off_part);
   c->diag = (double*)(c->ws + L.off_diag);
@@ -441,6 +490,30 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   return LBM_CH_OK;
 }
 
+// nsteps >= 1 steps at tau_g = 1 in the order-parameter form: the first reads the
+// populations, the last writes them (into the buffer that nsteps single steps would).
+// Before the last step the first has read the current buffer, so it may be the target.
+static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi_out,
+                           hipStream_t stream) {
+  const int to = c->cur ^ (int)(nsteps & 1);
+  a.ty = march_rows(c->p.nx, c->p.ny);
+  for (int64_t s = 0; s < nsteps; ++s) {
+    const bool first = s == 0, last = s == nsteps - 1;
+    a.tf = time_factor(c, c->step);
+    a.src = c->g[c->cur];
+    a.dst = c->g[to];
+    a.msrc = c->m[(s + 1) & 1];
+    a.mdst = c->m[s & 1];
+    a.phi_rec = phi_out ? phi_out + (size_t)s * c->p.nx * c->p.ny : nullptr;
+    const hipError_t e =
+        launch_phi_march(c->vmode, c->p.model, c->p.storage, first, last, a, stream);
+    if (e != hipSuccess) return hip_fail(e);
+    c->step += 1;
+  }
+  c->cur = to;
+  return LBM_CH_OK;
+}
+
 // nsteps steps; with phi_out, phi^n of step n is also written to phi_out + (n - n0) nx ny.
 static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t stream) {
   const bool ns = c->p.velocity_mode == LBM_CH_VEL_NS;
@@ -472,6 +545,9 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
   // Coupled steps of models 1 and 2 run as one launch (f and g together) on output tiles
   // of 64 columns x rows; model 3 keeps the two launches (NS step, then phase field).
   const bool fused = ns && (c->p.model == 1 || c->p.model == 2);
+  // Several steps at tau_g = 1 pass the sum field m between them (two FP64 fields in the
+  // workspace, whose single-precision fields steps of this kind do not use).
+  if (march_call(c, nsteps)) return run_steps_march(c, a, nsteps, phi_out, stream);
   StepArgs r = a;
   int rt_rows = 0, rt_blocks = 0;
   if (fused) {
@@ -758,6 +834,7 @@ int lbm_ch_set_tiles(lbm_ch_ctx* c, int32_t tx, int32_t ty) {
     return LBM_CH_EINVAL;
   }
   apply_tiles(c, tx, ty);
+  c->march1 = false;
   return LBM_CH_OK;
 }
 
@@ -794,18 +871,28 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
   int btx = tx0, bty = ty0;
   const int nx = c->p.nx, ny = c->p.ny;
   const bool pass = pass_eligible(c->p);
-  for (int xx : {0, 64, 128, 256, 512}) {
+  const bool march0 = c->march1;
+  bool bmarch = false;
+  // xx = -1: the march between populations, where it serves (with the default tiles)
+  const bool march = c->p.velocity_mode != LBM_CH_VEL_NS &&
+                     march_ok(c->p.walls != 0, c->vmode, c->p.model, tau_one(c));
+  for (int xx : {-1, 0, 64, 128, 256, 512}) {
     if (e != hipSuccess) break;
     if (xx == 0 && !pass) continue;
+    if (xx < 0 && !march) continue;
+    c->march1 = xx < 0;
     if (xx > 64 && xx / 2 >= nx) continue;  // more than half the lanes idle
     for (int yy : {1, 2, 4, 8, 16, 32}) {
       if (xx == 0 && yy != 4 && yy != 8 && yy != 16) continue;
+      if (xx < 0 && yy != 1) continue;
       if (yy > ny && yy > 2) continue;
-      apply_tiles(c, xx, yy);
+      if (xx >= 0) apply_tiles(c, xx, yy);
       r = run_steps(c, 1, nullptr, stream);  // untimed: first launch of this kernel shape
       if (r == LBM_CH_OK) {
         e = hipEventRecord(e0, stream);
-        if (e == hipSuccess) r = run_steps(c, trial_steps, nullptr, stream);
+        // single steps: the launches that the tile shape governs
+        for (int k = 0; e == hipSuccess && r == LBM_CH_OK && k < trial_steps; ++k)
+          r = run_steps(c, 1, nullptr, stream);
         if (e == hipSuccess && r == LBM_CH_OK) e = hipEventRecord(e1, stream);
         if (e == hipSuccess && r == LBM_CH_OK) e = hipEventSynchronize(e1);
       }
@@ -814,6 +901,7 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
       if (e != hipSuccess || r != LBM_CH_OK) break;
       if (best < 0.0f || ms < best) {
         best = ms;
+        bmarch = xx < 0;
         btx = xx;
         bty = yy;
       }
@@ -823,8 +911,10 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   // restore the state and the step counter whatever happened above
-  apply_tiles(c, (e == hipSuccess && r == LBM_CH_OK) ? btx : tx0,
-              (e == hipSuccess && r == LBM_CH_OK) ? bty : ty0);
+  const bool ok = e == hipSuccess && r == LBM_CH_OK;
+  if (ok && bmarch) default_tiles(c->p, btx, bty);
+  apply_tiles(c, ok ? btx : tx0, ok ? bty : ty0);
+  c->march1 = ok ? bmarch : march0;
   const int r2 = lbm_ch_load_state(c, backup, backup_bytes, step0, stream);
   if (e != hipSuccess) return hip_fail(e);
   if (r != LBM_CH_OK) return r;

@@ -220,26 +220,38 @@ __device__ __forceinline__ void close_mass(double m, float g[9]) {
   g[0] = (float)e0;
   g[8] = (float)((double)g[8] + (e0 - (double)g[0]));
 }
-// Writes the nine post-collision populations of node (col, row) in storage ST such that
-// the exact sum of the stored values is m (float32: up to the rounding of g_8; 16-bit:
-// up to the float32 rounding of g_0, which takes m minus the decoded others).  Returns
-// the stored values in g.
+// The values that storage ST keeps of the nine post-collision populations g of a node, such
+// that their exact sum is m (float32: up to the rounding of g_8; 16-bit: up to the
+// float32 rounding of g_0, which takes m minus the decoded others); h receives the
+// 16-bit codes of g_1..g_8.
 template <int ST>
-__device__ __forceinline__ void finish_store(rsrc_t d, uint32_t pitch, uint32_t col,
-                                             uint32_t row, double m, float g[9]) {
+__device__ __forceinline__ void stored_values(double m, float g[9], uint32_t h[9]) {
   if (ST == ST_F32) {
     close_mass(m, g);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) stb_nt(d, g[i], col * 4u, pop_off<ST>(i, pitch, row));
     return;
   }
-  uint32_t h[9];
 #pragma unroll
   for (int i = 1; i < 9; ++i) {
     h[i] = enc16<ST>(g[i] * INV_W[i]);
     g[i] = WT[i] * dec16<ST>(h[i]);
   }
   g[0] = (float)(m - sum8_hi(g));
+}
+// Writes the nine post-collision populations of node (col, row) in storage ST
+// (stored_values) and returns the stored values in g.
+template <int ST, bool NT = true>
+__device__ __forceinline__ void finish_store(rsrc_t d, uint32_t pitch, uint32_t col,
+                                             uint32_t row, double m, float g[9]) {
+  uint32_t h[9];
+  stored_values<ST>(m, g, h);
+  if (ST == ST_F32) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      if (NT) stb_nt(d, g[i], col * 4u, pop_off<ST>(i, pitch, row));
+      else stb(d, g[i], col * 4u, pop_off<ST>(i, pitch, row));
+    }
+    return;
+  }
   stb(d, g[0], col * 4u, pop_off<ST>(0, pitch, row));
 #pragma unroll
   for (int i = 1; i < 9; ++i)
@@ -247,16 +259,23 @@ __device__ __forceinline__ void finish_store(rsrc_t d, uint32_t pitch, uint32_t 
                                           pop_off<ST>(i, pitch, row), 0);
 }
 
+// The sum of the nine populations pulled to a node, in FP64: the rest, west- and
+// east-moving groups are summed apart, each in the order in which a march down the rows
+// meets its terms (sources in row y, y - 1, y + 1), so that a kernel that keeps partial
+// sums of a row instead of the populations forms the very same number.
+__device__ __forceinline__ double sum9d(const float g[9]) {
+  const double c = ((double)g[0] + (double)g[2]) + (double)g[4];
+  const double w = ((double)g[1] + (double)g[5]) + (double)g[8];
+  const double e = ((double)g[3] + (double)g[6]) + (double)g[7];
+  return c + (w + e);
+}
 __device__ __forceinline__ float sum9(const float g[9], float& lo) {
-  const double s = sum8_hi(g) + (double)g[0];
+  const double s = sum9d(g);
   const float f = (float)s;
   lo = (float)(s - (double)f);
   return f;
 }
-__device__ __forceinline__ float sum9(const float g[9]) {
-  float lo;
-  return sum9(g, lo);
-}
+__device__ __forceinline__ float sum9(const float g[9]) { return (float)sum9d(g); }
 
 // Bulk part of Eq. mu for the double well of Eq. bulk.
 __device__ __forceinline__ float mu_bulk(const Coef& c, float phi) {

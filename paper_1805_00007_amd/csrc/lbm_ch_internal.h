@@ -46,6 +46,8 @@ struct StepArgs {
   float* xh;          // model 3: X of the previous step (2 planes of nx*ny), rewritten
   int xfirst;         // model 3: 1 on the first step (no earlier X: zero difference)
   float* phi_rec;     // launch_phi_record only: phi of the source state (nx*ny), written
+  const double* msrc; // order-parameter form (lbm_ch_march.hip): sums at t_n
+  double* mdst;       // and at t_{n+1} (nx*ny each)
   int* nonfinite;     // set to 1 when a phi summed in stage 1 is NaN or Inf (may be null)
 };
 
@@ -103,6 +105,14 @@ hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int stora
 bool phi_record_fused(bool walls, int vmode, int model, int storage);
 hipError_t launch_phi_record(int tx, int vmode, int model, bool t1, const StepArgs& a,
                              int nblocks, hipStream_t s);
+// Marching steps between the population and order-parameter forms of a tau_g = 1 state
+// (lbm_ch_march.hip): periodic lattices, prescribed velocity, models 1 and 2, any storage
+// (march_ok).  from_g: the source is a.src (populations), else a.msrc; to_g: the result
+// goes to a.dst, else to a.mdst.  a.phi_rec (may be null) receives phi of the source
+// state.  a.ty rows per wave; strips and grid are set by the launcher.
+bool march_ok(bool walls, int vmode, int model, bool t1);
+hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool to_g,
+                            const StepArgs& a, hipStream_t s);
 // grid: a multiple of 8 workgroups.  persistent: the grid strides over the tiles (size
 // it with phi_batch_blocks_per_cu); otherwise one tile per workgroup (grid >= tiles).
 int phi_batch_blocks_per_cu(int tx, int vmode, bool model2, bool t1);

@@ -1,0 +1,293 @@
+// gfx950 kernels of several consecutive tau_g = 1 steps of the lattice Boltzmann
+// Cahn-Hilliard solver (Zhang, Guo & Liang, arXiv:1805.00007), in the order-parameter
+// form of the state.
+//
+// At tau_g = 1 the collision of Eq. LB keeps nothing of the pulled populations (g* =
+// g^eq + S/2), so between two steps the state is the field m(x) = sum_i g_i alone: one
+// FP64 value per node instead of nine populations.  A call of several steps reads the
+// populations once, passes m from step to step (16 bytes per node update instead of 72)
+// and writes the populations once, in its last step.  Every step still forms the nine
+// populations of a node exactly as the population kernels store them (collide_t1,
+// stored_values: the float32 values with their mass closure, or the decoded 16-bit
+// codes) and sums the pulled ones in the same order (sum9d), so the result is bitwise
+// that of single steps.
+#include "lbm_ch_device.h"
+#include "lbm_ch_stencil.h"
+
+#include <type_traits>
+
+namespace lbmch {
+namespace {
+
+#pragma clang fp contract(off)
+
+// The value of the lane to the west (x - 1) and to the east (x + 1): whole-wave shifts by
+// one lane; the lane at the end gets 0.
+__device__ __forceinline__ int west_i(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int east_i(int v) { return __builtin_amdgcn_mov_dpp(v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ float west(float v) {
+  return __builtin_bit_cast(float, west_i(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ float east(float v) {
+  return __builtin_bit_cast(float, east_i(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double west(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)west_i((int)(uint32_t)u), hi = (uint32_t)west_i((int)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double east(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)east_i((int)(uint32_t)u), hi = (uint32_t)east_i((int)(u >> 32));
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double ldb64(rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+}
+__device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_t soff) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
+}
+// A table read at a wave-uniform index through the scalar cache (never written while a
+// step runs).
+__device__ __forceinline__ float ld_uniform(const float* p, int i) {
+  return ((const __attribute__((address_space(4))) float*)(uintptr_t)p)[i];
+}
+
+template <int N>
+using ic = std::integral_constant<int, N>;
+
+// One wave marches up TY rows of a strip of 64 lanes, one lane per column, with every
+// rolling row in registers and the x neighbours from the adjacent lanes (DPP shifts): no
+// LDS and no barrier, so waves never wait for each other.  Row r enters (pulled or
+// loaded three rows ahead), then
+//   row r    : phi, u, q = phi u, and the E - W, E + W of each                 (Eq. macroscopicg)
+//   row r - 1: mu, D = div q, and theirs                                        (Eqs. mu, mark3)
+//   row r - 2: F = F1 + F2, the nine populations as storage ST keeps them       (Eqs. t0-phiu, geq, liangFi, LB)
+//   row r - 3: the sum of the populations pulled from rows r - 4 .. r - 2       (streaming)
+// The outer lanes of a strip lose one column of validity per stage: a strip yields 64 - 2M
+// columns, M = 2 where the populations are stored, 3 where their sums are.  A chunk of TY
+// rows marches through 2M more.
+//
+// VALU-bound: about 180 instructions per wave and row, 260 ns of a SIMD (FP64 ones and
+// lane shifts take 4.3-5 cycles, float32 ones 2.9).  2048^2 float32: 26 us a step (67 MB,
+// 2.6 TB/s of cached traffic) against 61.5 us for the population step's 302 MB; 4096^2 80
+// us against 216; half storage 2048^2 30 us against 44.  The step that reads and the step
+// that writes populations take 35 and 41 us at 2048^2; the latter keeps the default cache
+// policy, because a strip's 240-byte rows are parts of lines that the neighbouring strip
+// completes in L2 (both steps together 67 us, non-temporal 96).
+template <int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
+__device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
+  constexpr bool VFIELD = VMODE == VEL_FIELD;
+  constexpr int M = TO_G ? 2 : 3;
+  constexpr int OUT = 64 - 2 * M;
+  const Coef& c = a.c;
+  const int nx = a.nx, ny = a.ny;
+  const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
+  const uint32_t rb = (uint32_t)nx * 4u;
+  rsrc_t rsrc, rdst, ru, rv, rrec;
+  if (FROM_G) rsrc = make_rsrc(a.src, pop_bytes(ST, pitch, ny));
+  else rsrc = make_rsrc(a.msrc, nodes * 8u);
+  if (TO_G) rdst = make_rsrc(a.dst, pop_bytes(ST, pitch, ny));
+  else rdst = make_rsrc(a.mdst, nodes * 8u);
+  if (VFIELD) {
+    ru = make_rsrc(a.ux, nodes * 4u);
+    rv = make_rsrc(a.uy, nodes * 4u);
+  }
+  if (REC) rrec = make_rsrc(a.phi_rec, nodes * 4u);
+
+  const int lane = threadIdx.x & 63;
+  const int x0 = (L % a.nstrips) * OUT;
+  const int y0 = (L / a.nstrips) * a.ty;
+  const int rows = min(a.ty, ny - y0);
+  const int xl = x0 - M + lane;
+  const int x = ((xl % nx) + nx) % nx;
+  const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+  // columns this strip stores; the other lanes store at an offset beyond any buffer for
+  // each element size (8, 4 and 2 bytes: 0xFFFFFE00, 0xFFFFFF00 and, against at most 1.2e9
+  // bytes of 16-bit state, 0x7FFFFF80), which drops the store
+  const bool own = lane >= M && lane < M + OUT && xl < nx;
+  const uint32_t cst = own ? (uint32_t)x : 0x3FFFFFC0u;
+
+  float axc = 0.f, bxc = 0.f;
+  if (!VFIELD) {
+    axc = a.ax[x];
+    bxc = a.bx[x];
+  }
+
+  struct In {
+    double m;
+    float g[9], a, b;
+  };
+  In in[3];
+  // rows enter in order from y0 - M; past the last needed row the load repeats it (in cache)
+  int lrow = ((y0 - M) % ny + ny) % ny;
+  int left = rows + 2 * M;
+  auto fetch = [&](In& I) {
+    if (FROM_G) pull9<false, ST>(rsrc, pitch, ny, lrow, (uint32_t)x, xm, xp, I.g);
+    else I.m = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)lrow * 2u * rb);
+    if (VFIELD) {
+      I.a = ldb(ru, (uint32_t)x * 4u, (uint32_t)lrow * rb);
+      I.b = ldb(rv, (uint32_t)x * 4u, (uint32_t)lrow * rb);
+    } else {
+      I.a = ld_uniform(a.ay, lrow);
+      I.b = ld_uniform(a.by, lrow);
+    }
+    if (--left > 0) lrow = lrow + 1 == ny ? 0 : lrow + 1;
+  };
+
+  double m[3];
+  float ph[3], hph[3], u[3], v[3], qx[3], xqx[3], qy[3], hqy[3];
+  float mu[3], xmu[3], hmu[3], dv[3], xd[3], hd[3];
+  double ac = 0.0, aw = 0.0, ae = 0.0, sc = 0.0, sw = 0.0, se = 0.0;
+
+  auto row_x = [](float q) { return east(q) - west(q); };
+  auto ddx = [&](float qm, float qp, float X0) { return row_dx(X0, row_x(qp + qm)); };
+
+  // Row K enters slot K % 3; stage: the last of the four above that this row runs.  yo:
+  // the row that is stored.
+  auto push = [&](auto K, auto STAGE, int yo) {
+    constexpr int j = decltype(K)::value % 3, j1 = (j + 2) % 3, j2 = (j + 1) % 3;
+    constexpr int stage = decltype(STAGE)::value;
+    In& I = in[j];
+    const float phi_out = TO_G ? ph[j2] : ph[j];  // phi of the stored row
+    // --- row r
+    if (FROM_G) m[j] = sum9d(I.g);
+    else m[j] = I.m;
+    ph[j] = (float)m[j];
+    if (__builtin_expect(!__builtin_isfinite(ph[j]), 0) && a.nonfinite) *a.nonfinite = 1;
+    if (VFIELD) {
+      u[j] = a.tf * I.a;
+      v[j] = a.tf * I.b;
+    } else {
+      u[j] = axc * (I.a * a.tf);
+      v[j] = bxc * (I.b * a.tf);
+    }
+    fetch(I);
+    hph[j] = east(ph[j]) + west(ph[j]);
+    if (MODEL2) {
+      qx[j] = ph[j] * u[j];
+      qy[j] = ph[j] * v[j];
+      xqx[j] = row_x(qx[j]);
+      hqy[j] = east(qy[j]) + west(qy[j]);
+    }
+    if (stage < 1) return;
+    // --- row r - 1
+    mu[j1] = t1_mu(c, ph[j1], row_lap(ph[j2], ph[j1], ph[j], hph[j2], hph[j1], hph[j]));
+    xmu[j1] = row_x(mu[j1]);
+    hmu[j1] = east(mu[j1]) + west(mu[j1]);
+    if (MODEL2) {
+      dv[j1] = ddx(qx[j2], qx[j], xqx[j1]) + row_dy(qy[j2], qy[j], hqy[j2], hqy[j]);
+      xd[j1] = row_x(dv[j1]);
+      hd[j1] = east(dv[j1]) + west(dv[j1]);
+    }
+    if (stage < 2) return;
+    // --- row r - 2: mu and D of rows r - 3, r - 2, r - 1 in slots j, j2, j1
+    float fx, fy, dx = 0.f, dy = 0.f, g[9];
+    if (MODEL2) {
+      dx = ddx(dv[j], dv[j1], xd[j2]);
+      dy = row_dy(dv[j], dv[j1], hd[j], hd[j1]);
+    }
+    t1_force<MODEL2>(c, ph[j2], ddx(mu[j], mu[j1], xmu[j2]), row_dy(mu[j], mu[j1], hmu[j], hmu[j1]), dx, dy, fx, fy);
+    collide_t1(c, ph[j2], mu[j2], u[j2], v[j2], fx, fy, g);
+    if (TO_G) {
+      if (stage < 3) return;
+      if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)yo * rb);
+      finish_store<ST, false>(rdst, pitch, cst, (uint32_t)yo, m[j2], g);
+      return;
+    }
+    uint32_t h[9];
+    stored_values<ST>(m[j2], g, h);
+    // --- row r - 3: the groups of sum9d, each summed at its source column
+    const double oc = ac + (double)g[4], ow = aw + (double)g[8], oe = ae + (double)g[7];
+    ac = (double)g[0] + sc;
+    aw = (double)g[1] + sw;
+    ae = (double)g[3] + se;
+    sc = (double)g[2];
+    sw = (double)g[5];
+    se = (double)g[6];
+    if (stage < 3) return;
+    if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)yo * rb);
+    stb64(rdst, oc + (west(ow) + east(oe)), cst * 8u, (uint32_t)yo * 2u * rb);
+  };
+
+  fetch(in[0]);
+  fetch(in[1]);
+  fetch(in[2]);
+  push(ic<0>{}, ic<0>{}, 0);
+  push(ic<1>{}, ic<0>{}, 0);
+  push(ic<2>{}, ic<1>{}, 0);
+  push(ic<3>{}, ic<1>{}, 0);
+  if (!TO_G) {
+    push(ic<4>{}, ic<2>{}, 0);
+    push(ic<5>{}, ic<2>{}, 0);
+  }
+  constexpr int K0 = 2 * M;
+#pragma unroll 1
+  for (int i = 0; i < rows; i += 3) {
+    push(ic<K0>{}, ic<3>{}, y0 + i);
+    if (i + 1 >= rows) break;
+    push(ic<K0 + 1>{}, ic<3>{}, y0 + i + 1);
+    if (i + 2 >= rows) break;
+    push(ic<K0 + 2>{}, ic<3>{}, y0 + i + 2);
+  }
+}
+
+constexpr int MARCH_WAVES = 4;  // waves per workgroup (independent of each other)
+
+template <int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
+__global__ void __launch_bounds__(64 * MARCH_WAVES) k_phi_march(const StepArgs a, const int total) {
+  // workgroup w runs on XCD w % 8: give each XCD a band of neighbouring strips and chunks
+  const int per = gridDim.x >> 3;
+  const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (L >= total) return;
+  march_tile<VMODE, MODEL2, ST, FROM_G, TO_G, REC>(a, L);
+}
+#pragma clang fp contract(fast)
+
+template <int ST, bool FROM_G, bool TO_G>
+hipError_t march_f(int vmode, bool model2, StepArgs a, hipStream_t s) {
+  constexpr int OUT = TO_G ? 60 : 58;
+  a.nstrips = (a.nx + OUT - 1) / OUT;
+  const int total = a.nstrips * ((a.ny + a.ty - 1) / a.ty);
+  const int grid = ((total + MARCH_WAVES - 1) / MARCH_WAVES + 7) / 8 * 8;
+  const bool rec = a.phi_rec != nullptr;
+#define LBM_MARCH(V, M2, R) \
+  hipLaunchKernelGGL((k_phi_march<V, M2, ST, FROM_G, TO_G, R>), dim3(grid), dim3(64 * MARCH_WAVES), 0, s, a, total)
+  if (vmode == VEL_SEP) {
+    if (model2) { if (rec) LBM_MARCH(VEL_SEP, true, true); else LBM_MARCH(VEL_SEP, true, false); }
+    else { if (rec) LBM_MARCH(VEL_SEP, false, true); else LBM_MARCH(VEL_SEP, false, false); }
+  } else {
+    if (model2) { if (rec) LBM_MARCH(VEL_FIELD, true, true); else LBM_MARCH(VEL_FIELD, true, false); }
+    else { if (rec) LBM_MARCH(VEL_FIELD, false, true); else LBM_MARCH(VEL_FIELD, false, false); }
+  }
+#undef LBM_MARCH
+  return hipGetLastError();
+}
+
+template <int ST>
+hipError_t march_t(int vmode, bool model2, bool from_g, bool to_g, const StepArgs& a, hipStream_t s) {
+  if (from_g) return to_g ? march_f<ST, true, true>(vmode, model2, a, s) : march_f<ST, true, false>(vmode, model2, a, s);
+  return to_g ? march_f<ST, false, true>(vmode, model2, a, s) : march_f<ST, false, false>(vmode, model2, a, s);
+}
+
+}  // namespace
+
+bool march_ok(bool walls, int vmode, int model, bool t1) {
+  return !walls && t1 && (vmode == VEL_SEP || vmode == VEL_FIELD) && (model == 1 || model == 2);
+}
+
+hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool to_g,
+                            const StepArgs& a, hipStream_t s) {
+  if (!march_ok(false, vmode, model, true) || a.ty < 1) return hipErrorInvalidValue;
+  switch (storage) {
+    case ST_F32: return march_t<ST_F32>(vmode, model == 2, from_g, to_g, a, s);
+    case ST_F16: return march_t<ST_F16>(vmode, model == 2, from_g, to_g, a, s);
+    case ST_BF16: return march_t<ST_BF16>(vmode, model == 2, from_g, to_g, a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace lbmch

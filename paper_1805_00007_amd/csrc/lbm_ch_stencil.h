@@ -18,18 +18,26 @@ namespace {
 // rp: y+1), as the weighted neighbour sums
 //   d_x = [4 (E - W) + (NE + SE) - (NW + SW)] / 12,  d_y = [4 (N - S) + (NE + NW) - (SE + SW)] / 12,
 //   lap = [4 (E + W + N + S) + (NE + NW + SE + SW) - 20 C] / 6.
+// First from the row values v, and the sums E + W (H) and differences E - W (X) of a row:
+// dx from X_0 and the X of the sum of the outer rows; then on LDS rows.
+__device__ __forceinline__ float row_dx(float X0, float Xpm) {
+  return fmaf(4.0f, X0, Xpm) * (1.0f / 12.0f);
+}
+__device__ __forceinline__ float row_dy(float vm, float vp, float Hm, float Hp) {
+  return fmaf(4.0f, vp - vm, Hp - Hm) * (1.0f / 12.0f);
+}
+__device__ __forceinline__ float row_lap(float vm, float v0, float vp, float Hm, float H0, float Hp) {
+  return fmaf(4.0f, H0 + (vp + vm), fmaf(-20.0f, v0, Hp + Hm)) * (1.0f / 6.0f);
+}
 __device__ __forceinline__ float t1_dx(const float* rm, const float* r0, const float* rp, int j) {
-  const float diag = (rp[j + 1] + rm[j + 1]) - (rp[j - 1] + rm[j - 1]);
-  return fmaf(4.0f, r0[j + 1] - r0[j - 1], diag) * (1.0f / 12.0f);
+  return row_dx(r0[j + 1] - r0[j - 1], (rp[j + 1] + rm[j + 1]) - (rp[j - 1] + rm[j - 1]));
 }
 __device__ __forceinline__ float t1_dy(const float* rm, const float* r0, const float* rp, int j) {
-  const float diag = (rp[j + 1] + rp[j - 1]) - (rm[j + 1] + rm[j - 1]);
-  return fmaf(4.0f, rp[j] - rm[j], diag) * (1.0f / 12.0f);
+  return row_dy(rm[j], rp[j], rm[j + 1] + rm[j - 1], rp[j + 1] + rp[j - 1]);
 }
 __device__ __forceinline__ float t1_lap(const float* rm, const float* r0, const float* rp, int j) {
-  const float axis = (r0[j + 1] + r0[j - 1]) + (rp[j] + rm[j]);
-  const float diag = (rp[j + 1] + rp[j - 1]) + (rm[j + 1] + rm[j - 1]);
-  return fmaf(4.0f, axis, fmaf(-20.0f, r0[j], diag)) * (1.0f / 6.0f);
+  return row_lap(rm[j], r0[j], rp[j], rm[j + 1] + rm[j - 1], r0[j + 1] + r0[j - 1],
+                 rp[j + 1] + rp[j - 1]);
 }
 // mu of Eq. mu with the double well of Eq. bulk: 2 beta (phi - phi_A)(phi - phi_B)
 // (2 phi - phi_A - phi_B) - kappa lap(phi).
@@ -58,6 +66,21 @@ __device__ __forceinline__ void collide_t1(const Coef& c, float phi, float mu, f
   pair(v, hy, WT[2], g[2], g[4]);
   pair(u + v, hx + hy, WT[5], g[5], g[7]);
   pair(v - u, hy - hx, WT[6], g[6], g[8]);
+}
+
+// F = F1 + F2 with F1 = (phi/rho) F_s, F_s = -phi grad mu (Eq. t0-phiu, grad p = 0), and
+// for Model-II F2 = K grad D (Eq. mark3).
+template <bool MODEL2>
+__device__ __forceinline__ void t1_force(const Coef& c, float phi, float mux, float muy, float dx,
+                                         float dy, float& fx, float& fy) {
+  const float rho = fmaf(c.a, phi, c.b);
+  const float s1 = -(phi * phi) * rcp(rho);
+  fx = s1 * mux;
+  fy = s1 * muy;
+  if (MODEL2) {
+    fx = fmaf(c.k2, dx, fx);
+    fy = fmaf(c.k2, dy, fy);
+  }
 }
 
 // Collision of Eq. LB at any tau_g (g^eq of Eq. geq, S_i = 3 w_i c_i.F of Eq. liangFi):

@@ -340,7 +340,7 @@ struct PullT1 {
   float a, b;             // separable: ay[y], by[y]; field: u, v of the node (as loaded)
 };
 struct RowT1 {
-  float phi, lo;          // phi and the FP64 remainder of the sum
+  double m;               // the FP64 sum of the pulled populations
   float a, b;             // separable: ay[y], by[y] times tf (and parity); field: u, v
 };
 
@@ -423,8 +423,9 @@ __device__ __forceinline__ void phi_tile_t1(const StepArgs& a, const int L) {
                     bool wr = true) {
     float sg;
     row_of<WALLS>(r, ny, sg);
-    R.phi = sum9(P.g, R.lo);
-    if (__builtin_expect(!__builtin_isfinite(R.phi), 0) && a.nonfinite) *a.nonfinite = 1;
+    R.m = sum9d(P.g);
+    const float phi = (float)R.m;
+    if (__builtin_expect(!__builtin_isfinite(phi), 0) && a.nonfinite) *a.nonfinite = 1;
     const float f = a.tf * sg;
     float u, v;
     if (VMODE == VEL_SEP) {
@@ -437,40 +438,36 @@ __device__ __forceinline__ void phi_tile_t1(const StepArgs& a, const int L) {
       v = R.b = f * P.b;
     }
     if (!wr) return;
-    s_phi[slot][jj] = R.phi;
+    s_phi[slot][jj] = phi;
     if (MODEL2) {
-      s_qx[slot][jj] = R.phi * u;
-      s_qy[slot][jj] = R.phi * v;
+      s_qx[slot][jj] = phi * u;
+      s_qy[slot][jj] = phi * v;
     }
   };
   // Stencils take their three rows in lattice order (slots of lattice rows y - 1, y,
   // y + 1), whichever way the chunk marches, so that every value is computed by the same
   // expression in every tile.
   auto stage2 = [&](int jj, int sm, int s0, int sp) {
-    const float* pm = s_phi[sm];
     const float* p0 = s_phi[s0];
-    const float* pp = s_phi[sp];
-    s_mu[s0][jj] = t1_mu(c, p0[jj], t1_lap(pm, p0, pp, jj));
+    s_mu[s0][jj] = t1_mu(c, p0[jj], t1_lap(s_phi[sm], p0, s_phi[sp], jj));
     if (MODEL2)
       s_d[s0][jj] = t1_dx(s_qx[sm], s_qx[s0], s_qx[sp], jj) + t1_dy(s_qy[sm], s_qy[s0], s_qy[sp], jj);
   };
   auto stage3 = [&](int y, const RowT1& R, int sm, int s0, int sp) {
-    const float mux = t1_dx(s_mu[sm], s_mu[s0], s_mu[sp], j);
-    const float muy = t1_dy(s_mu[sm], s_mu[s0], s_mu[sp], j);
-    // F1 = (phi/rho) F_s with F_s = -phi grad mu (Eq. t0-phiu, grad p = 0); F2 = K grad D
-    const float rho = fmaf(c.a, R.phi, c.b);
-    const float s1 = -(R.phi * R.phi) * rcp(rho);
-    float fx = s1 * mux, fy = s1 * muy;
+    const float phi = (float)R.m;
+    float dx = 0.0f, dy = 0.0f, fx, fy;
     if (MODEL2) {
-      fx = fmaf(c.k2, t1_dx(s_d[sm], s_d[s0], s_d[sp], j), fx);
-      fy = fmaf(c.k2, t1_dy(s_d[sm], s_d[s0], s_d[sp], j), fy);
+      dx = t1_dx(s_d[sm], s_d[s0], s_d[sp], j);
+      dy = t1_dy(s_d[sm], s_d[s0], s_d[sp], j);
     }
+    t1_force<MODEL2>(c, phi, t1_dx(s_mu[sm], s_mu[s0], s_mu[sp], j),
+                     t1_dy(s_mu[sm], s_mu[s0], s_mu[sp], j), dx, dy, fx, fy);
     const float u = VMODE == VEL_SEP ? axc * R.a : R.a;
     const float v = VMODE == VEL_SEP ? bxc * R.b : R.b;
-    if (REC) stb_nt(rrec, R.phi, vc * 4u, (uint32_t)y * rb);
+    if (REC) stb_nt(rrec, phi, vc * 4u, (uint32_t)y * rb);
     float g[9];
-    collide_t1(c, R.phi, s_mu[s0][j], u, v, fx, fy, g);
-    finish_store<ST>(rdst, pitch, vc, (uint32_t)y, (double)R.phi + (double)R.lo, g);
+    collide_t1(c, phi, s_mu[s0][j], u, v, fx, fy, g);
+    finish_store<ST>(rdst, pitch, vc, (uint32_t)y, R.m, g);
   };
 
   // Rows the march needs: m = -2 .. rows + 1; a pull past the last one is clamped to it
@@ -654,31 +651,44 @@ __global__ void __launch_bounds__(64 * R) k_phi_pass(const StepArgs a) {
     if (ny >= R + 4) return y < 0 ? y + ny : (y >= ny ? y - ny : y);
     return (y % ny + ny) % ny;
   };
-  // stage 1 at one region node: pull, phi (with its FP64 remainder), the velocity factors
-  // as phi_tile_t1 keeps them (separable: ay[y] tf and bx[x] ... as a, b) and q = phi u
-  struct Node {
-    float phi, lo, a, b, u, v;
+  // stage 1 at one region node: the pull of the populations with the velocity factors, then
+  // the sum m, phi, the velocity as phi_tile_t1 forms it, and q = phi u into the region
+  struct Pull {
+    float g[9], a, b, ax, bx;
   };
-  auto node = [&](auto lanes, int rr, int cc) {
+  struct Node {
+    double m;
+    float phi, u, v;
+  };
+  auto pull = [&](auto lanes, int rr, int cc, Pull& P) {
     const int x = col(cc), y = row(rr);
     const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
-    float g[9];
     if constexpr (decltype(lanes)::value)
-      pull9_lanes<false, ST>(rsrc, pitch, ny, y, (uint32_t)x, xm, xp, g);
+      pull9_lanes<false, ST>(rsrc, pitch, ny, y, (uint32_t)x, xm, xp, P.g);
     else
-      pull9<false, ST>(rsrc, pitch, ny, y, (uint32_t)x, xm, xp, g);
-    Node n;
-    n.phi = sum9(g, n.lo);
-    const float f = a.tf;  // periodic: the row parity factor is 1
+      pull9<false, ST>(rsrc, pitch, ny, y, (uint32_t)x, xm, xp, P.g);
     if (VMODE == VEL_SEP) {
-      n.a = a.ay[y] * f;
-      n.b = a.by[y] * f;
-      n.u = a.ax[x] * n.a;
-      n.v = a.bx[x] * n.b;
+      P.a = a.ay[y];
+      P.b = a.by[y];
+      P.ax = a.ax[x];
+      P.bx = a.bx[x];
     } else {
       const uint32_t k = (uint32_t)y * nx + x;
-      n.a = n.u = f * a.ux[k];
-      n.b = n.v = f * a.uy[k];
+      P.a = a.ux[k];
+      P.b = a.uy[k];
+    }
+  };
+  auto node = [&](const Pull& P, int k) {
+    Node n;
+    n.m = sum9d(P.g);
+    n.phi = (float)n.m;
+    const float f = a.tf;  // periodic: the row parity factor is 1
+    n.u = VMODE == VEL_SEP ? P.ax * (P.a * f) : f * P.a;
+    n.v = VMODE == VEL_SEP ? P.bx * (P.b * f) : f * P.b;
+    s_ph[k] = n.phi;
+    if (MODEL2) {
+      s_qx[k] = n.phi * n.u;
+      s_qy[k] = n.phi * n.v;
     }
     return n;
   };
@@ -692,16 +702,14 @@ __global__ void __launch_bounds__(64 * R) k_phi_pass(const StepArgs a) {
   const int xo = x0 + t % PS_C, yo = y0 + tw;
   const bool own = xo < nx && yo < ny;
 
-  const Node no = node(OWN{}, ro, co);
-  if (__builtin_expect(!__builtin_isfinite(no.phi), 0) && own && a.nonfinite) *a.nonfinite = 1;
-  s_ph[ko] = no.phi;
-  if (MODEL2) {
-    s_qx[ko] = no.phi * no.u;
-    s_qy[ko] = no.phi * no.v;
-  }
+  // every pull is issued before the first is used
+  Pull po, pm[EX];
+  pull(OWN{}, ro, co, po);
+  int km[EX];
 #pragma unroll
   for (int i = 0; i < EX; ++i) {
     const int e = t + i * NT;
+    km[i] = -1;
     if (e < NX) {
       int rr, cc;  // the band of width 2 around the tile, row by row
       if (e < 2 * PS_W) {
@@ -717,15 +725,16 @@ __global__ void __launch_bounds__(64 * R) k_phi_pass(const StepArgs a) {
         rr = 2 + R + q / PS_W;
         cc = q % PS_W;
       }
-      const Node m = node(MARGIN{}, rr, cc);
-      const int k = rr * PS_W + cc;
-      s_ph[k] = m.phi;
-      if (MODEL2) {
-        s_qx[k] = m.phi * m.u;
-        s_qy[k] = m.phi * m.v;
-      }
+      pull(MARGIN{}, rr, cc, pm[i]);
+      km[i] = rr * PS_W + cc;
     }
   }
+  __builtin_amdgcn_sched_barrier(0);
+  const Node no = node(po, ko);
+  if (__builtin_expect(!__builtin_isfinite(no.phi), 0) && own && a.nonfinite) *a.nonfinite = 1;
+#pragma unroll
+  for (int i = 0; i < EX; ++i)
+    if (km[i] >= 0) node(pm[i], km[i]);
   __syncthreads();
   // stage 2: mu and D on the tile plus 1 (Eqs. mu, mark3)
   for (int e = t; e < (R + 2) * (PS_C + 2); e += NT) {
@@ -738,23 +747,22 @@ __global__ void __launch_bounds__(64 * R) k_phi_pass(const StepArgs a) {
   __syncthreads();
   if (!own) return;
   // stage 3 (as in phi_tile_t1)
-  const float* m = s_mu + ko;
-  const float mux = t1_dx(m - PS_W, m, m + PS_W, 0), muy = t1_dy(m - PS_W, m, m + PS_W, 0);
-  const float rho = fmaf(c.a, no.phi, c.b);
-  const float s1 = -(no.phi * no.phi) * rcp(rho);
-  float fx = s1 * mux, fy = s1 * muy;
-  if (MODEL2) {
-    const float* dd = s_d + ko;
-    fx = fmaf(c.k2, t1_dx(dd - PS_W, dd, dd + PS_W, 0), fx);
-    fy = fmaf(c.k2, t1_dy(dd - PS_W, dd, dd + PS_W, 0), fy);
-  }
   if (REC) {
     const rsrc_t rrec = make_rsrc(a.phi_rec, nodes * 4u);
     stb_nt(rrec, no.phi, (uint32_t)xo * 4u, (uint32_t)yo * rb);
   }
   float g[9];
+  const float* m = s_mu + ko;
+  float dx = 0.0f, dy = 0.0f, fx, fy;
+  if (MODEL2) {
+    const float* dd = s_d + ko;
+    dx = t1_dx(dd - PS_W, dd, dd + PS_W, 0);
+    dy = t1_dy(dd - PS_W, dd, dd + PS_W, 0);
+  }
+  t1_force<MODEL2>(c, no.phi, t1_dx(m - PS_W, m, m + PS_W, 0), t1_dy(m - PS_W, m, m + PS_W, 0),
+                   dx, dy, fx, fy);
   collide_t1(c, no.phi, s_mu[ko], no.u, no.v, fx, fy, g);
-  finish_store<ST>(rdst, pitch, (uint32_t)xo, (uint32_t)yo, (double)no.phi + (double)no.lo, g);
+  finish_store<ST>(rdst, pitch, (uint32_t)xo, (uint32_t)yo, no.m, g);
 }
 #pragma clang fp contract(fast)
 

@@ -1,0 +1,75 @@
+"""Calls of several tau_g = 1 steps pass the sum of the populations from step to step
+(strips of 58 columns, 60 where populations are stored): the state they leave and the
+order parameter they record are bitwise those of single steps."""
+import numpy as np
+import pytest
+
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _populations(buf, nx, ny, storage):
+    """The stored values of a saved state without the padding of its rows."""
+    pitch = (nx + 31) // 32 * 32
+    if storage == 0:
+        return buf.view(torch.int32).view(ny, 9, pitch)[:, :, :nx].contiguous()
+    rows = buf.view(ny, 20 * pitch)
+    rest = rows[:, :4 * pitch].reshape(ny, pitch, 4)[:, :nx].reshape(ny, -1)
+    moving = rows[:, 4 * pitch:].reshape(ny, 8, pitch, 2)[:, :, :nx].reshape(ny, -1)
+    return torch.cat([rest, moving], 1)
+
+
+@pytest.mark.parametrize("storage", [0, 1, 2])
+@pytest.mark.parametrize("nx,ny", [(5, 4), (40, 23), (58, 64), (61, 7), (117, 65), (300, 517)])
+def test_many_steps_equal_single_steps(nx, ny, storage):
+    import paper_1805_00007_amd as lbm
+    rng = np.random.default_rng(nx * 1000 + ny)
+    phi0 = np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1)
+    tables = dict(ax=rng.uniform(-.04, .04, nx), ay=rng.uniform(-1, 1, ny),
+                  bx=rng.uniform(-.04, .04, nx), by=rng.uniform(-1, 1, ny),
+                  tf=np.cos(0.1 * np.arange(20)))
+    field = (rng.uniform(-.04, .04, (ny, nx)), rng.uniform(-.04, .04, (ny, nx)))
+    for model, vel in ((1, dict(velocity=tables)), (2, dict(velocity=tables)),
+                       (1, dict(field=field)), (2, dict(field=field))):
+        print(nx, ny, storage, model, list(vel), flush=True)
+        one, many, rec = (lbm.Solver(nx, ny, phi0, storage=storage, **vel,
+                                     **dict(workloads.PRESCRIBED, model=model))
+                          for _ in range(3))
+        phis = []
+        for _ in range(13):
+            phis.append(one.phi())
+            one.step(1)
+        many.step(2).step(4).step(7)
+        traj = torch.empty((13, ny, nx), dtype=torch.float32, device="cuda")
+        rec.record(6, traj).record(7, traj[6:])
+        ref = _populations(one.save_state()[0], nx, ny, storage)
+        assert torch.equal(_populations(many.save_state()[0], nx, ny, storage), ref)
+        assert torch.equal(_populations(rec.save_state()[0], nx, ny, storage), ref)
+        assert torch.equal(traj, torch.stack(phis))
+        for s in (one, many, rec):
+            s.close()
+
+
+@pytest.mark.parametrize("storage,nx,ny", [(0, 1024, 701), (1, 1901, 1100)])
+def test_single_step_march_equals_tiles(storage, nx, ny):
+    """Single steps by default (16-bit storage at this size: as a march), with marching and
+    with single-pass tiles, and a call of several steps: bitwise the same state."""
+    import paper_1805_00007_amd as lbm
+    rng = np.random.default_rng(7)
+    phi0 = np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1)
+    field = (rng.uniform(-.04, .04, (ny, nx)), rng.uniform(-.04, .04, (ny, nx)))
+    ref = None
+    for tiles in (None, (64, 8), (512, 16), (0, 8), "many"):
+        s = lbm.Solver(nx, ny, phi0, field=field, storage=storage, **workloads.PRESCRIBED)
+        if tiles == "many":
+            s.step(3)
+        else:
+            if tiles:
+                s.set_tiles(*tiles)
+            s.step(1).step(1).step(1)
+        got = _populations(s.save_state()[0], nx, ny, storage)
+        s.close()
+        ref = got if ref is None else ref
+        assert torch.equal(got, ref), tiles

@@ -427,8 +427,9 @@ def batch_leg(lbm, torch, steps=5000, plain_steps=200, check_steps=100):
                                 "schedule": "persistent" if persistent else "tile per workgroup"},
             "bitwise_equal_to_plain_after_%d" % check_steps: bool(same),
             "nonfinite": int(nonfinite),
-            "bytes_per_lu": 80,
-            "roofline": roofline(80, nodes, t_batch * 1e6, "k_phi_batch (all 64 lattices)",
+            "bytes_per_lu": round(run_bytes_per_lu(steps) + 8, 2),
+            "roofline": roofline(run_bytes_per_lu(steps) + 8, nodes, t_batch * 1e6,
+                                 "k_march_batch (all 64 lattices)",
                                  "profiles/phi_batch_batch64_kernel_trace.md")}
 
 

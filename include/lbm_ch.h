@@ -330,7 +330,9 @@ int lbm_ch_adjoint_static(lbm_ch_ctx* ctx, int64_t n_end, int64_t nsteps,
  * contiguous range of it, walked either by a persistent grid sized to the resident
  * capacity or by one workgroup per tile (lbm_ch_batch_set_schedule).  Results are
  * bitwise those of lbm_ch_step on each context.  Lattices with different tile widths
- * or kernel variants (velocity mode, Model-I/II) form groups of one launch each.
+ * or kernel variants (velocity mode, Model-I/II) form groups of one launch each.  Calls of
+ * several steps pass the sum field of tau_g = 1 lattices from step to step (lbm_ch_step),
+ * in strips of their own: there tiles and schedule govern calls of one step.
  * Supported: periodic lattices, LBM_CH_STORE_F32, model 1 or 2, prescribed velocity
  * without a time-factor table.  The contexts must outlive the batch; stepping a context on its
  * own between batch steps is allowed. */
@@ -369,7 +371,7 @@ int lbm_ch_batch_step(lbm_ch_batch* b, int64_t nsteps, int32_t use_graph, hipStr
 /* Bytes of a backup of every lattice's state (each rounded to 256 bytes). */
 size_t lbm_ch_batch_state_bytes(const lbm_ch_batch* b);
 
-/* Autotuner: time trial_steps >= 1 batch steps (after one untimed step) for both
+/* Autotuner: time trial_steps >= 1 single batch steps (after one untimed step) for both
  * schedules, every tile policy tx in {0, 64, 128, 256} and ty in {4, 8, 16, 32}, keep the
  * fastest, and
  * restore every lattice's state and step counter from `backup` (device memory of

@@ -296,13 +296,16 @@ static void default_tiles(const lbm_ch_params& p, int& tx_out, int& ty_out) {
 // least (rows + 2.3) b therefore fills whole rounds of the 256 CUs.  Against a sweep of
 // heights 3 .. 74 the choice is within 5 % at every size from 128^2 to 5000 x 3900
 // (2048^2: within 3 % of the best; 6, 12, 24 and 32 rows cost 12-20 % more).
-static int march_rows(int nx, int ny) {
-  const long strips = (nx + 57) / 58;
+struct MarchShape {  // lattices alike: strips of each, rows of each
+  int strips, ny;
+};
+static int march_rows(const MarchShape* m, int n) {
   int best = 4;
   double cost = 1e30;
   for (int ty = 4; ty <= 64; ++ty) {
-    const long blocks = (strips * ((ny + ty - 1) / ty) + 3) / 4;
-    const long b = (blocks + 255) / 256;
+    long waves = 0;
+    for (int i = 0; i < n; ++i) waves += (long)m[i].strips * ((m[i].ny + ty - 1) / ty);
+    const long b = ((waves + 3) / 4 + 255) / 256;
     const double t = (ty + 2.3) * (b == 1 ? 1.36 : (double)b);
     if (t < cost) {
       cost = t;
@@ -310,6 +313,10 @@ static int march_rows(int nx, int ny) {
     }
   }
   return best;
+}
+static int march_rows(int nx, int ny) {
+  const MarchShape m{march_strips(nx), ny};
+  return march_rows(&m, 1);
 }
 
 // Whether a single step runs as a march from populations to populations instead of with
@@ -496,7 +503,8 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
 static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi_out,
                            hipStream_t stream) {
   const int to = c->cur ^ (int)(nsteps & 1);
-  a.ty = march_rows(c->p.nx, c->p.ny);
+  a.mty = march_rows(c->p.nx, c->p.ny);
+  a.mstrips = march_strips(c->p.nx);
   for (int64_t s = 0; s < nsteps; ++s) {
     const bool first = s == 0, last = s == nsteps - 1;
     a.tf = time_factor(c, c->step);
@@ -1052,6 +1060,15 @@ struct BatchGroup {
   int total, grid;
 };
 
+// Neighbouring groups that differ in tile width only: one launch of a march.
+struct MarchGroup {
+  int vmode;
+  bool model2;
+  int first, count;  // range in the instance order
+  int start_off;     // offset of this group's first waves in the device start array
+  int total;         // waves
+};
+
 struct BatchExec {
   hipGraphExec_t exec;
   int64_t steps;
@@ -1070,6 +1087,7 @@ struct lbm_ch_batch {
   std::vector<int> hstart;
   std::vector<int> built_cur;  // ctx->cur of each instance when the tables were built
   std::vector<BatchGroup> groups;
+  std::vector<MarchGroup> marches;  // the tau_g = 1 lattices, for calls of several steps
   int tx_policy;  // 0: per-instance width, else one width for all
   int ty;
   int persistent; // 1: a resident-size grid strides over the tiles; 0: a tile per workgroup
@@ -1084,7 +1102,8 @@ struct lbm_ch_batch {
 static bool batch_live(const lbm_ch_batch* b) { return b && b->magic == BATCH_MAGIC; }
 
 static size_t batch_table_bytes(int32_t n) {
-  return align_up((size_t)n * sizeof(StepArgs)) + align_up((size_t)(2 * n + 1) * sizeof(int));
+  // arguments; starts of the tile groups and of the marches (count + 1 entries per group)
+  return align_up((size_t)n * sizeof(StepArgs)) + align_up((size_t)(4 * n) * sizeof(int));
 }
 
 // Width of instance tiles: the policy's width, or (policy 0) the widest of 256, 128, 64
@@ -1121,7 +1140,7 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
   }
   auto key = [&](int i) {
     const lbm_ch_ctx* c = b->ctx[i];
-    return txs[i] * 32 + c->vmode * 4 + (c->p.model == 2 ? 2 : 0) + (tau_one(c) ? 1 : 0);
+    return (c->vmode * 4 + (c->p.model == 2 ? 2 : 0) + (tau_one(c) ? 1 : 0)) * 1024 + txs[i];
   };
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
   b->hargs.assign(n, StepArgs{});
@@ -1158,6 +1177,9 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
     a.ux = c->ux; a.uy = c->uy;
     a.tf = time_factor(c, c->step);
     a.nonfinite = c->nf_dev;
+    a.msrc = c->m[0];
+    a.mdst = c->m[1];
+    a.mstrips = march_strips(c->p.nx);
     b->built_cur[i] = c->cur;
     b->hstart.push_back(g.total);
     g.total += a.nstrips * ((c->p.ny + ty - 1) / ty);
@@ -1172,6 +1194,28 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
       g.grid = want < resident ? want : (resident > 8 ? resident : 8);
     } else {
       g.grid = want;
+    }
+  }
+  b->marches.clear();
+  for (const BatchGroup& g : b->groups) {
+    if (!g.t1) continue;
+    if (b->marches.empty() || b->marches.back().vmode != g.vmode ||
+        b->marches.back().model2 != g.model2 ||
+        b->marches.back().first + b->marches.back().count != g.first)
+      b->marches.push_back(MarchGroup{g.vmode, g.model2, g.first, 0, 0, 0});
+    b->marches.back().count += g.count;
+  }
+  for (MarchGroup& m : b->marches) {
+    std::vector<MarchShape> shapes;
+    for (int k = m.first; k < m.first + m.count; ++k)
+      shapes.push_back(MarchShape{b->hargs[k].mstrips, b->hargs[k].ny});
+    const int ty = march_rows(shapes.data(), m.count);
+    m.start_off = (int)b->hstart.size();
+    for (int k = m.first; k < m.first + m.count; ++k) {
+      StepArgs& a = b->hargs[k];
+      a.mty = ty;
+      b->hstart.push_back(m.total);
+      m.total += a.mstrips * ((a.ny + ty - 1) / ty);
     }
   }
   e = hipMemcpyAsync(b->dargs, b->hargs.data(), n * sizeof(StepArgs), hipMemcpyHostToDevice,
@@ -1196,9 +1240,30 @@ static int batch_prepare(lbm_ch_batch* b, hipStream_t stream) {
   return stale ? batch_build(b, stream) : LBM_CH_OK;
 }
 
+// Calls of several steps march the tau_g = 1 lattices in the order-parameter form (64
+// lattices of sides 64-512, 20 steps and 64 read-outs: 3050 us with tiles, 1209 as
+// marches); the other lattices, and calls of one step, take the tiles.
 static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipStream_t s) {
+  const bool march = nsteps >= 2;
   for (int64_t k = 0; k < nsteps; ++k) {
+    if (march) {
+      for (const MarchGroup& m : b->marches) {
+        BatchArgs a{};
+        a.args = b->dargs + m.first;
+        a.start = b->dstart + m.start_off;
+        a.n = m.count;
+        a.total = m.total;
+        const bool first = k == 0, last = k == nsteps - 1;
+        // populations: the current buffer is the source, the one that nsteps single steps
+        // would leave current the target (instance entries hold src as of phase 0)
+        const int gpar = first ? (phase & 1) : (int)((phase + nsteps + 1) & 1);
+        const hipError_t e = launch_march_batch(m.vmode, m.model2, first, last, a, gpar,
+                                                (int)((k + 1) & 1), s);
+        if (e != hipSuccess) return e;
+      }
+    }
     for (const BatchGroup& g : b->groups) {
+      if (march && g.t1) continue;
       BatchArgs a{};
       a.args = b->dargs + g.first;
       a.start = b->dstart + g.start_off;
@@ -1377,7 +1442,9 @@ int lbm_ch_batch_autotune(lbm_ch_batch* b, void* backup, size_t backup_bytes,
       r = lbm_ch_batch_step(b, 1, 0, stream);  // rebuilds the tables; untimed
       if (r != LBM_CH_OK) break;
       e = hipEventRecord(e0, stream);
-      if (e == hipSuccess) r = lbm_ch_batch_step(b, trial_steps, 0, stream);
+      // single steps: the launches that the tile policy governs
+      for (int k = 0; e == hipSuccess && r == LBM_CH_OK && k < trial_steps; ++k)
+        r = lbm_ch_batch_step(b, 1, 0, stream);
       if (e == hipSuccess && r == LBM_CH_OK) e = hipEventRecord(e1, stream);
       if (e == hipSuccess && r == LBM_CH_OK) e = hipEventSynchronize(e1);
       float ms = 0.0f;

@@ -48,6 +48,7 @@ struct StepArgs {
   float* phi_rec;     // launch_phi_record only: phi of the source state (nx*ny), written
   const double* msrc; // order-parameter form (lbm_ch_march.hip): sums at t_n
   double* mdst;       // and at t_{n+1} (nx*ny each)
+  int mty, mstrips;   // its rows per wave and strips (march_strips)
   int* nonfinite;     // set to 1 when a phi summed in stage 1 is NaN or Inf (may be null)
 };
 
@@ -109,7 +110,9 @@ hipError_t launch_phi_record(int tx, int vmode, int model, bool t1, const StepAr
 // (lbm_ch_march.hip): periodic lattices, prescribed velocity, models 1 and 2, any storage
 // (march_ok).  from_g: the source is a.src (populations), else a.msrc; to_g: the result
 // goes to a.dst, else to a.mdst.  a.phi_rec (may be null) receives phi of the source
-// state.  a.ty rows per wave; strips and grid are set by the launcher.
+// state.  a.mty rows per wave, a.mstrips = march_strips(nx).
+constexpr int MARCH_OUT = 58;  // columns of a strip
+constexpr int march_strips(int nx) { return (nx + MARCH_OUT - 1) / MARCH_OUT; }
 bool march_ok(bool walls, int vmode, int model, bool t1);
 hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool to_g,
                             const StepArgs& a, hipStream_t s);
@@ -118,6 +121,11 @@ hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool
 int phi_batch_blocks_per_cu(int tx, int vmode, bool model2, bool t1);
 hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool t1, bool persistent,
                             const BatchArgs& b, int grid, hipStream_t s);
+// The same marches over the float32 lattices of a batch: b.start counts waves (strips of
+// chunks of mty rows) instead of tiles, b.total of them.  gpar, mpar: swap the population
+// or sum buffers of every instance.
+hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, const BatchArgs& b,
+                              int gpar, int mpar, hipStream_t s);
 hipError_t launch_ns_step(int tx, bool walls, int storage, const NsArgs& a, int nblocks,
                           hipStream_t s);
 // Single-launch coupled step (models 1 and 2): f and g of one time step, output tiles

@@ -66,8 +66,8 @@ using ic = std::integral_constant<int, N>;
 //   row r - 1: mu, D = div q, and theirs                                        (Eqs. mu, mark3)
 //   row r - 2: F = F1 + F2, the nine populations as storage ST keeps them       (Eqs. t0-phiu, geq, liangFi, LB)
 //   row r - 3: the sum of the populations pulled from rows r - 4 .. r - 2       (streaming)
-// The outer lanes of a strip lose one column of validity per stage: a strip yields 64 - 2M
-// columns, M = 2 where the populations are stored, 3 where their sums are.  A chunk of TY
+// The outer lanes of a strip lose one column of validity per stage, M = 2 or (sums) 3 on
+// each side, so a strip yields 58 columns.  A chunk of TY
 // rows marches through 2M more.
 //
 // VALU-bound: about 180 instructions per wave and row, 260 ns of a SIMD (FP64 ones and
@@ -81,7 +81,8 @@ template <int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
   constexpr int M = TO_G ? 2 : 3;
-  constexpr int OUT = 64 - 2 * M;
+  constexpr int OUT = MARCH_OUT;
+  static_assert(OUT <= 64 - 2 * M, "a strip and its margins are one wave");
   const Coef& c = a.c;
   const int nx = a.nx, ny = a.ny;
   const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
@@ -98,9 +99,9 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   if (REC) rrec = make_rsrc(a.phi_rec, nodes * 4u);
 
   const int lane = threadIdx.x & 63;
-  const int x0 = (L % a.nstrips) * OUT;
-  const int y0 = (L / a.nstrips) * a.ty;
-  const int rows = min(a.ty, ny - y0);
+  const int x0 = (L % a.mstrips) * OUT;
+  const int y0 = (L / a.mstrips) * a.mty;
+  const int rows = min(a.mty, ny - y0);
   const int xl = x0 - M + lane;
   const int x = ((xl % nx) + nx) % nx;
   const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
@@ -245,14 +246,52 @@ __global__ void __launch_bounds__(64 * MARCH_WAVES) k_phi_march(const StepArgs a
   if (L >= total) return;
   march_tile<VMODE, MODEL2, ST, FROM_G, TO_G, REC>(a, L);
 }
+
+// The marches of many lattices in one launch: wave L belongs to the instance whose range of
+// waves holds it, found by every lane testing one start each; its arguments are read
+// through the scalar cache (the tables are written before the launch).
+template <int VMODE, bool MODEL2, bool FROM_G, bool TO_G>
+__global__ void __launch_bounds__(64 * MARCH_WAVES)
+k_march_batch(const BatchArgs b, const int gpar, const int mpar) {
+  const int per = gridDim.x >> 3;
+  const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (L >= b.total) return;
+  int inst = -1;
+  for (int i = 0; i < b.n; i += 64) {
+    const int k = i + (int)(threadIdx.x & 63);
+    inst += __popcll(__ballot(k < b.n && b.start[k] <= L));
+  }
+  typedef const __attribute__((address_space(4))) uint32_t* scalar_words;
+  StepArgs a;
+  static_assert(sizeof(StepArgs) % 4 == 0, "whole words");
+  uint32_t words[sizeof(StepArgs) / 4];
+  const scalar_words src = (scalar_words)(uintptr_t)(b.args + inst);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(StepArgs) / 4); ++i) words[i] = src[i];
+  __builtin_memcpy(&a, words, sizeof(StepArgs));
+  if (gpar) {
+    const void* t = a.src;
+    a.src = a.dst;
+    a.dst = const_cast<void*>(t);
+  }
+  if (mpar) {
+    const double* t = a.msrc;
+    a.msrc = a.mdst;
+    a.mdst = const_cast<double*>(t);
+  }
+  const int first = ((const __attribute__((address_space(4))) int*)(uintptr_t)b.start)[inst];
+  march_tile<VMODE, MODEL2, ST_F32, FROM_G, TO_G, false>(a, L - first);
+}
 #pragma clang fp contract(fast)
 
+// Workgroups for `total` waves, a multiple of 8 (one band per XCD).
+int march_grid(int total) { return ((total + MARCH_WAVES - 1) / MARCH_WAVES + 7) / 8 * 8; }
+
 template <int ST, bool FROM_G, bool TO_G>
-hipError_t march_f(int vmode, bool model2, StepArgs a, hipStream_t s) {
-  constexpr int OUT = TO_G ? 60 : 58;
-  a.nstrips = (a.nx + OUT - 1) / OUT;
-  const int total = a.nstrips * ((a.ny + a.ty - 1) / a.ty);
-  const int grid = ((total + MARCH_WAVES - 1) / MARCH_WAVES + 7) / 8 * 8;
+hipError_t march_f(int vmode, bool model2, const StepArgs& a, hipStream_t s) {
+  const int total = a.mstrips * ((a.ny + a.mty - 1) / a.mty);
+  const int grid = march_grid(total);
   const bool rec = a.phi_rec != nullptr;
 #define LBM_MARCH(V, M2, R) \
   hipLaunchKernelGGL((k_phi_march<V, M2, ST, FROM_G, TO_G, R>), dim3(grid), dim3(64 * MARCH_WAVES), 0, s, a, total)
@@ -281,13 +320,33 @@ bool march_ok(bool walls, int vmode, int model, bool t1) {
 
 hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool to_g,
                             const StepArgs& a, hipStream_t s) {
-  if (!march_ok(false, vmode, model, true) || a.ty < 1) return hipErrorInvalidValue;
+  if (!march_ok(false, vmode, model, true) || a.mty < 1 || a.mstrips != march_strips(a.nx))
+    return hipErrorInvalidValue;
   switch (storage) {
     case ST_F32: return march_t<ST_F32>(vmode, model == 2, from_g, to_g, a, s);
     case ST_F16: return march_t<ST_F16>(vmode, model == 2, from_g, to_g, a, s);
     case ST_BF16: return march_t<ST_BF16>(vmode, model == 2, from_g, to_g, a, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, const BatchArgs& b,
+                              int gpar, int mpar, hipStream_t s) {
+  if (b.n <= 0 || b.total <= 0) return hipErrorInvalidValue;
+  const dim3 grid(march_grid(b.total)), block(64 * MARCH_WAVES);
+#define LBM_MB(V, M2, F, T) hipLaunchKernelGGL((k_march_batch<V, M2, F, T>), grid, block, 0, s, b, gpar, mpar)
+#define LBM_MB_FORM(V, M2)                                                       \
+  if (from_g) { if (to_g) return hipErrorInvalidValue; LBM_MB(V, M2, true, false); } \
+  else if (to_g) { LBM_MB(V, M2, false, true); }                                 \
+  else { LBM_MB(V, M2, false, false); }
+  if (vmode == VEL_SEP) {
+    if (model2) { LBM_MB_FORM(VEL_SEP, true) } else { LBM_MB_FORM(VEL_SEP, false) }
+  } else {
+    if (model2) { LBM_MB_FORM(VEL_FIELD, true) } else { LBM_MB_FORM(VEL_FIELD, false) }
+  }
+#undef LBM_MB_FORM
+#undef LBM_MB
+  return hipGetLastError();
 }
 
 }  // namespace lbmch

@@ -73,3 +73,32 @@ def test_single_step_march_equals_tiles(storage, nx, ny):
         s.close()
         ref = got if ref is None else ref
         assert torch.equal(got, ref), tiles
+
+
+def test_batch_marches_equal_single_steps():
+    """A batch call of several steps marches its tau_g = 1 lattices in launches of their own
+    (here one per kernel variant, more than 64 lattices in one of them) and leaves bitwise
+    the state of single steps, whatever the parity and with lattices at other tau_g beside."""
+    import paper_1805_00007_amd as lbm
+    rng = np.random.default_rng(3)
+    pairs = []
+    for i in range(74):
+        nx, ny = int(rng.integers(20, 130)), int(rng.integers(4, 90))
+        phi0 = np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1)
+        field = (rng.uniform(-.04, .04, (ny, nx)), rng.uniform(-.04, .04, (ny, nx)))
+        phys = dict(workloads.PRESCRIBED, model=1 if i % 25 == 3 else 2,
+                    tau_g=0.9 if i % 25 == 7 else 1.0)
+        pairs.append([lbm.Solver(nx, ny, phi0, field=field, **phys) for _ in range(2)])
+    b = lbm.Batch([p[0] for p in pairs])
+    for n, graph in ((3, False), (1, False), (4, True), (2, False), (5, True)):
+        b.step(n, graph=graph)
+        for _, one in pairs:
+            for _ in range(n):
+                one.step(1)
+        for got, one in pairs:
+            a, r = (_populations(s.save_state()[0], s.nx, s.ny, 0) for s in (got, one))
+            assert torch.equal(a, r), (n, graph, got.nx, got.ny)
+    b.close()
+    for p in pairs:
+        for s in p:
+            s.close()

@@ -7,15 +7,16 @@ a circle of radius 0.15 L at (L/2, 3L/4) in the time-reversing single vortex
 synthetic inputs shaped like the paper's deformation tests).
 
 A step is one launch of the fused kernel (phi, mu, F1 + F2, collision, streaming) over
-the whole lattice.  A call of several steps passes the sum of the populations (one FP64
-value per node) from step to step: its first step reads the nine float32 populations, its
-last one writes them.  Prints one JSON line:
+the whole lattice.  At tau_g = 1 steps pass the sum of the populations (one FP64 value
+per node) from one to the next, and the last step of a call writes the nine float32
+populations too.  Prints one JSON line:
   value        MLUPS = nx*ny*steps / time of the timed steps (inputs resident in HBM)
-  roofline     algorithmic bytes (16 B per node update, 44 in the first and the last step)
-               / average kernel duration from HIP events, against the 8 TB/s HBM peak;
-               single_step: the same for calls of one step (72 B per node update), traffic
-               = measured HBM bytes per launch from the committed rocprofv3 counter summary
-               (null when the kernel source changed since)
+  roofline     algorithmic bytes (16 B per node update, 52 in the last step of a call) /
+               average kernel duration from HIP events, against the 8 TB/s HBM peak;
+               single_step: the same for calls of one step
+  population_step  the step of any other tau_g, which reads and writes nine populations (72
+               B per node update); traffic = measured HBM bytes per launch from the
+               committed rocprofv3 counter summary (null when the kernel source changed)
   cpu_baseline the FP64 oracle on the host cores on a bounded number of steps
   accuracy     relative L2 of phi after 1000 steps against stored FP64 oracle samples
 """
@@ -34,13 +35,13 @@ sys.path.insert(0, ROOT)
 METRIC = ("MLUPS and % HBM peak (FP32 fused step, 2048^2) vs FP64 oracle accuracy; "
           "adjoint ms")
 HBM_PEAK_GBS = 8000.0
-BYTES_PER_LU = 72.0  # one step of its own: nine populations read, nine written
+BYTES_PER_LU = 72.0  # a population step: nine populations read, nine written
 
 
 def run_bytes_per_lu(steps, state=36.0):
-    """Bytes per node update of one call of `steps` steps: `state` bytes of populations in
-    and out, and 8 bytes of sum field written and read between steps."""
-    return (2.0 * state + 16.0 * (steps - 1)) / steps
+    """Bytes per node update of one call of `steps` steps at tau_g = 1: 8 bytes of sum field
+    read and written in every step, `state` bytes of populations written in the last."""
+    return 16.0 + state / steps
 
 
 # sources of the fused step kernel: a counter summary is used only while they are unchanged
@@ -170,6 +171,25 @@ def roofline(bytes_per_lu, nodes, us, kernel, profile, traffic=None):
             "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic, "kernel": kernel, "kernel_avg_us": round(us, 2),
             "profile": profile}
+
+
+def population_step(lbm, torch, steps=50, warm=5):
+    """The same workload at tau_g = 0.8: the step that needs all nine populations."""
+    import workloads
+    w = workloads.metric2048(steps=steps + warm)
+    s = lbm.solver_for(w, tau_g=0.8)
+    s.step(warm)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda.synchronize()
+    e0.record(s.stream)
+    s.step(steps)
+    e1.record(s.stream)
+    torch.cuda.synchronize()
+    us = e0.elapsed_time(e1) * 1e3 / steps
+    s.close()
+    return {"workload": "vortex2048 at tau_g = 0.8", "us_per_step": round(us, 2),
+            "roofline": roofline(BYTES_PER_LU, w.nx * w.ny, us, "k_phi_step",
+                                 "profiles/phi_step_vortex2048_traffic.txt", measured_traffic())}
 
 
 def storage_variant(lbm, torch, storage, steps):
@@ -445,6 +465,8 @@ def main():
                     help="only run a plain device copy of 1 GiB x 10 (counter calibration)")
     ap.add_argument("--rt-only", action="store_true",
                     help="only run the Rayleigh-Taylor leg (--steps timed, --warmup untimed)")
+    ap.add_argument("--population-only", action="store_true",
+                    help="only run the population step (--steps timed, --warmup untimed)")
     args = ap.parse_args()
     if args.copy_probe:
         import torch
@@ -478,6 +500,10 @@ def main():
         print(json.dumps({"rayleigh_taylor": rt_leg(lbm, torch, steps=args.steps,
                                                     warm=args.warmup)}), flush=True)
         return
+    if args.population_only:
+        print(json.dumps({"population_step": population_step(lbm, torch, steps=args.steps,
+                                                             warm=args.warmup)}), flush=True)
+        return
     w = workloads.metric2048(steps=args.steps + args.warmup)
     s = lbm.solver_for(w)
     stream = s.stream
@@ -505,6 +531,7 @@ def main():
     nprobe = min(200, max(20, args.steps // 5))
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
            for _ in range(nprobe)]
+    s.step(1)
     for a, b in evs:
         a.record(stream)
         s.step(1)
@@ -520,8 +547,8 @@ def main():
     lu = run_bytes_per_lu(args.steps)
     algo = lu * nodes
     achieved = algo / (k_ms * 1e-3) / 1e9
-    single = BYTES_PER_LU * nodes / (iso_ms * 1e-3) / 1e9
-    traffic = measured_traffic()
+    single_lu = run_bytes_per_lu(1)
+    single = single_lu * nodes / (iso_ms * 1e-3) / 1e9
     out = {
         "metric": METRIC,
         "value": round(mlups, 1),
@@ -546,16 +573,17 @@ def main():
                      "kernel": "k_phi_march (vector-ALU bound: sum field between steps)",
                      "kernel_avg_us": round(k_ms * 1e3, 2),
                      "algorithmic_bytes_per_launch": algo,
-                     "single_step": {"kernel": "k_phi_step", "traffic": traffic,
+                     "single_step": {"kernel": "k_phi_march, populations written",
                                      "isolated_launch_us": round(iso_ms * 1e3, 2),
                                      "achieved": round(single, 1),
                                      "frac": round(single / HBM_PEAK_GBS, 4),
-                                     "algorithmic_bytes_per_launch": BYTES_PER_LU * nodes}},
+                                     "algorithmic_bytes_per_launch": single_lu * nodes}},
     }
     if not args.no_accuracy:
         out["accuracy"] = accuracy(lbm, workloads.metric2048(steps=1000), torch)
         out["storage_variants"] = {name: storage_variant(lbm, torch, st, args.steps)
                                    for name, st in (("f16", 1), ("bf16", 2))}
+        out["population_step"] = population_step(lbm, torch)
         out["adjoint"] = adjoint_leg(lbm, torch)
         out["rayleigh_taylor"] = rt_leg(lbm, torch)
         out["batched"] = batch_leg(lbm, torch)

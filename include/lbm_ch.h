@@ -163,11 +163,11 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
  * NS step) on `stream`.  The step counter n advances by nsteps.  With NS and model 1 or
  * 2 a step is one launch that advances f and g together (velocity and pressure are
  * formed inside it and not stored; lbm_ch_moments recomputes them); model 3 runs the NS
- * step and then the phase-field step.  Periodic lattices with a prescribed velocity at
- * tau_g = 1, models 1 and 2: a call of several steps passes only the sum of the pulled
- * populations (one FP64 value per node, which at tau_g = 1 is the whole state) from step
- * to step and writes the populations in its last step; the state it leaves is bitwise
- * that of as many calls of one step.  Non-finite values:
+ * step and then the phase-field step.  Periodic lattices of more than
+ * 65536 nodes with a prescribed velocity at tau_g = 1, models 1 and 2, keep the sum of the
+ * pulled populations (one FP64 value per node, which at tau_g = 1 is the whole state)
+ * beside the populations: steps pass only that from one to the next, and the last step of
+ * a call writes the populations too.  Results are those of the populations alone.  Non-finite values:
  * every step kernel raises a flag of the context when a phi it sums from the
  * populations is NaN or Inf; the flag lives in 4 bytes of pinned host memory mapped
  * into the device (allocated by lbm_ch_init, freed by lbm_ch_destroy), so it lands on
@@ -214,10 +214,8 @@ int lbm_ch_load_state(lbm_ch_ctx* ctx, const void* src, size_t bytes, int64_t st
  * single-pass tiles of 64 columns x ty rows (ty 4, 8 or 16) that pull their rows and a
  * margin of 2 at once, for periodic float32 lattices with a prescribed velocity at
  * tau_g = 1, models 1 and 2 (LBM_CH_EINVAL elsewhere).  The default is chosen at init
- * from the lattice size and storage; it changes speed only, never results.  Calls that
- * pass the sum field from step to step (lbm_ch_step) choose their own strips, and so do
- * calls of one step on some of those lattices while the default is in force: setting a
- * shape makes it govern calls of one step.
+ * from the lattice size and storage; it changes speed only, never results.  Lattices that
+ * keep their sum field (lbm_ch_step) step in strips of their own, whatever the shape.
  *   Where single-pass tiles serve: with float32 storage below 2048^2 nodes, tx = 0 with
  *   ty = 4 up to 65536 nodes, else 16; with 16-bit storage at every size, ty = 4 up to
  *   65536 nodes, 8 below 2048^2, else 16.
@@ -253,10 +251,9 @@ int lbm_ch_default_tiles(const lbm_ch_params* params, int32_t* tx, int32_t* ty);
  * LBM_CH_EINVAL for other values of enable. */
 int lbm_ch_set_graphs(lbm_ch_ctx* ctx, int32_t enable);
 
-/* Autotuner: time trial_steps >= 1 single steps (after one untimed step) for each tile shape
+/* Autotuner: time trial_steps >= 1 steps (after one untimed step) for each tile shape
  * tx in {64, 128, 256, 512} (skipping widths with more than half the lanes idle) and ty in
- * {1, 2, 4, 8, 16, 32}, and the default (lbm_ch_set_tiles) where that has strips of its
- * own, keep the fastest, and restore the state and step counter from
+ * {1, 2, 4, 8, 16, 32} (one of them where the shape is without effect), keep the fastest, and restore the state and step counter from
  * `backup`, a caller device buffer of exactly lbm_ch_state_bytes(ctx) bytes.
  * Synchronises `stream`.  *best_us (may be NULL) receives the chosen shape's time per
  * step in microseconds. */
@@ -330,9 +327,9 @@ int lbm_ch_adjoint_static(lbm_ch_ctx* ctx, int64_t n_end, int64_t nsteps,
  * contiguous range of it, walked either by a persistent grid sized to the resident
  * capacity or by one workgroup per tile (lbm_ch_batch_set_schedule).  Results are
  * bitwise those of lbm_ch_step on each context.  Lattices with different tile widths
- * or kernel variants (velocity mode, Model-I/II) form groups of one launch each.  Calls of
- * several steps pass the sum field of tau_g = 1 lattices from step to step (lbm_ch_step),
- * in strips of their own: there tiles and schedule govern calls of one step.
+ * or kernel variants (velocity mode, Model-I/II) form groups of one launch each.  Lattices
+ * at tau_g = 1 pass their sum field from step to step (lbm_ch_step), in strips of their
+ * own: tiles and schedule govern the others.
  * Supported: periodic lattices, LBM_CH_STORE_F32, model 1 or 2, prescribed velocity
  * without a time-factor table.  The contexts must outlive the batch; stepping a context on its
  * own between batch steps is allowed. */
@@ -371,7 +368,7 @@ int lbm_ch_batch_step(lbm_ch_batch* b, int64_t nsteps, int32_t use_graph, hipStr
 /* Bytes of a backup of every lattice's state (each rounded to 256 bytes). */
 size_t lbm_ch_batch_state_bytes(const lbm_ch_batch* b);
 
-/* Autotuner: time trial_steps >= 1 single batch steps (after one untimed step) for both
+/* Autotuner: time trial_steps >= 1 batch steps (after one untimed step) for both
  * schedules, every tile policy tx in {0, 64, 128, 256} and ty in {4, 8, 16, 32}, keep the
  * fastest, and
  * restore every lattice's state and step counter from `backup` (device memory of

@@ -104,14 +104,14 @@ struct lbm_ch_ctx {
   void* g[2];
   float *f[2], *u, *v, *pr, *phi, *ztab, *xh;
   double *part, *diag;
-  double* m[2];  // sum fields of steps in the order-parameter form (over u, v, pr, phi)
+  double* m[2];  // sum fields of the order-parameter form (over u, v, pr, phi)
   int cur;  // index of the buffer holding the current state
   int64_t step;
   int vmode;  // internal VelMode of the prescribed velocity
   const float *ax, *ay, *bx, *by, *ux, *uy;
   std::vector<double> tf;
   int tx, ty, nstrips, nblocks, xcd_remap;
-  bool march1;  // single steps run as marches (march_call); a tile shape set by the caller clears it
+  bool keep;  // m[cur] is kept beside g[cur] (keeps_sum)
   int graphs;                     // lbm_ch_set_graphs: replay captured launch sequences
   hipStream_t cap;                // capture stream, created at the first capture
   std::vector<struct CtxExec> execs;  // cached executable graphs, most recently used last
@@ -319,32 +319,39 @@ static int march_rows(int nx, int ny) {
   return march_rows(&m, 1);
 }
 
-// Whether a single step runs as a march from populations to populations instead of with
-// the context's tiles: 16-bit storage on lattices of 2 million nodes and more (us for a
-// step and the read-out of phi, tile / march, half storage: 1280^2 26.6 / 26.9, 2048^2 71 /
-// 64, 3000^2 150 / 129, 4000^2 252 / 244).  With float32 storage the tiles, which store
-// whole lines, are ahead or level at most sizes (768^2 16.4 / 16.7, 1024^2 23.0 / 23.4,
-// 1792^2 76 / 75; the step alone at 4096^2 216 / 310).
-static bool march_single(const lbm_ch_params& p) {
-  const int64_t nodes = (int64_t)p.nx * p.ny;
-  return p.storage != LBM_CH_STORE_F32 && nodes >= 2000000 && nodes <= (16 << 20);
-}
-
-// Whether a call of nsteps steps runs as marches: several steps in the order-parameter
-// form (us a step in calls of 2 / 100 steps, tiles against marches: 384^2 7.2 / 6.0 against
-// 7.0 / 4.8, 2048^2 64 / 62 against 34 / 24; a lattice of 256^2 nodes or fewer would gain
-// 0.4 us in long calls and lose as much in short ones), single ones by march_single.
-static bool march_call(const lbm_ch_ctx* c, int64_t nsteps) {
-  if (c->p.velocity_mode == LBM_CH_VEL_NS || nsteps < 1) return false;
-  if (!march_ok(c->p.walls != 0, c->vmode, c->p.model, tau_one(c))) return false;
-  return nsteps == 1 ? c->march1 : (int64_t)c->p.nx * c->p.ny > 65536;
+// Whether a context keeps the sum field m of its state beside the populations and steps in
+// the order-parameter form (lbm_ch_march.hip), from 256^2 nodes up: below, a step of the
+// single-pass tile is as fast (us a step in calls of 40 steps, 128^2: 4.5 / 4.6) and calls
+// of one step faster.  m[cur] then belongs to g[cur] at every return.
+static bool keeps_sum(const lbm_ch_params& p, int vmode) {
+  return p.velocity_mode != LBM_CH_VEL_NS &&
+         march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0) &&
+         (int64_t)p.nx * p.ny > 65536;
 }
 
 static void choose_tiles(lbm_ch_ctx* c) {
   int tx, ty;
   default_tiles(c->p, tx, ty);
   apply_tiles(c, tx, ty);
-  c->march1 = march_single(c->p);
+}
+
+// The sum field of the current populations, where it is kept.
+static hipError_t refresh_sum(lbm_ch_ctx* c, hipStream_t stream) {
+  if (!c->keep) return hipSuccess;
+  return launch_sum_field(c->p.walls != 0, c->p.storage, c->g[c->cur], c->L.pitch, c->p.nx,
+                          c->p.ny, c->m[c->cur], stream);
+}
+
+// phi of the current state.
+static hipError_t phi_field(const lbm_ch_ctx* c, float* phi, hipStream_t stream) {
+  if (c->keep) return launch_phi_of_sum(c->m[c->cur], (int64_t)c->p.nx * c->p.ny, phi, stream);
+  return launch_phi_field(c->p.walls != 0, c->p.storage, c->g[c->cur], c->L.pitch, c->p.nx,
+                          c->p.ny, phi, stream);
+}
+
+// A float32 field of the workspace that holds no state.
+static float* scratch_field(const lbm_ch_ctx* c) {
+  return c->keep ? (float*)c->m[1 - c->cur] : c->phi;
 }
 
 extern "C" {
@@ -476,6 +483,7 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   if (vm != LBM_CH_VEL_NS && vel && vel->time_factor && vel->n_time_factor > 0)
     c->tf.assign(vel->time_factor, vel->time_factor + vel->n_time_factor);
   choose_tiles(c);
+  c->keep = keeps_sum(*p, c->vmode);
   c->magic = CTX_MAGIC;
 
   hipError_t e = launch_fill(z, 0.0f, 2 * (int64_t)(p->nx + p->ny), stream);
@@ -483,6 +491,7 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
     e = launch_init(p->walls != 0, c->vmode, p->storage, c->c, p->nx, p->ny, L.pitch, phi0,
                     c->ax, c->ay, c->bx, c->by, c->ux, c->uy, time_factor(c, 0), c->g[0],
                     c->f[0], stream);
+  if (e == hipSuccess) e = refresh_sum(c, stream);
   if (e != hipSuccess) {
     c->magic = 0;
     (void)hipHostFree(c->nf_host);
@@ -497,24 +506,22 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   return LBM_CH_OK;
 }
 
-// nsteps >= 1 steps at tau_g = 1 in the order-parameter form: the first reads the
-// populations, the last writes them (into the buffer that nsteps single steps would).
-// Before the last step the first has read the current buffer, so it may be the target.
+// nsteps >= 1 steps of a state kept in the order-parameter form; the last one writes the
+// populations, into the buffer that nsteps steps alternating between the two would.
 static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi_out,
                            hipStream_t stream) {
   const int to = c->cur ^ (int)(nsteps & 1);
   a.mty = march_rows(c->p.nx, c->p.ny);
   a.mstrips = march_strips(c->p.nx);
+  a.dst = c->g[to];
   for (int64_t s = 0; s < nsteps; ++s) {
-    const bool first = s == 0, last = s == nsteps - 1;
+    const int from = c->cur ^ (int)(s & 1);
     a.tf = time_factor(c, c->step);
-    a.src = c->g[c->cur];
-    a.dst = c->g[to];
-    a.msrc = c->m[(s + 1) & 1];
-    a.mdst = c->m[s & 1];
+    a.msrc = c->m[from];
+    a.mdst = c->m[1 - from];
     a.phi_rec = phi_out ? phi_out + (size_t)s * c->p.nx * c->p.ny : nullptr;
     const hipError_t e =
-        launch_phi_march(c->vmode, c->p.model, c->p.storage, first, last, a, stream);
+        launch_phi_march(c->vmode, c->p.model, c->p.storage, s == nsteps - 1, a, stream);
     if (e != hipSuccess) return hip_fail(e);
     c->step += 1;
   }
@@ -553,9 +560,7 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
   // Coupled steps of models 1 and 2 run as one launch (f and g together) on output tiles
   // of 64 columns x rows; model 3 keeps the two launches (NS step, then phase field).
   const bool fused = ns && (c->p.model == 1 || c->p.model == 2);
-  // Several steps at tau_g = 1 pass the sum field m between them (two FP64 fields in the
-  // workspace, whose single-precision fields steps of this kind do not use).
-  if (march_call(c, nsteps)) return run_steps_march(c, a, nsteps, phi_out, stream);
+  if (c->keep) return run_steps_march(c, a, nsteps, phi_out, stream);
   StepArgs r = a;
   int rt_rows = 0, rt_blocks = 0;
   if (fused) {
@@ -741,10 +746,9 @@ int lbm_ch_moments(lbm_ch_ctx* c, float* phi, float* mu, float* ux, float* uy, f
   const int nx = c->p.nx, ny = c->p.ny;
   const size_t fb = (size_t)nx * ny * sizeof(float);
   const bool ns = c->p.velocity_mode == LBM_CH_VEL_NS;
-  float* ph = phi ? phi : c->phi;
+  float* ph = phi ? phi : scratch_field(c);
   hipError_t e = hipSuccess;
-  if (phi || mu || ns)
-    e = launch_phi_field(walls, c->p.storage, c->g[c->cur], c->L.pitch, nx, ny, ph, stream);
+  if (phi || mu || ns) e = phi_field(c, ph, stream);
   if (e == hipSuccess && mu) e = launch_mu_field(walls, c->c, ph, nx, ny, mu, stream);
   if (e != hipSuccess) return hip_fail(e);
   if (ns) {
@@ -777,10 +781,10 @@ int lbm_ch_diagnostics(lbm_ch_ctx* c, const float* phi_ref, double* out, hipStre
   if (!out || ((uintptr_t)out & 7u) != 0) return LBM_CH_EINVAL;
   if (phi_ref && !aligned4(phi_ref)) return LBM_CH_EINVAL;
   const bool walls = c->p.walls != 0;
-  hipError_t e = launch_phi_field(walls, c->p.storage, c->g[c->cur], c->L.pitch, c->p.nx,
-                                  c->p.ny, c->phi, stream);
+  float* phi = scratch_field(c);
+  hipError_t e = phi_field(c, phi, stream);
   if (e == hipSuccess)
-    e = launch_diag(walls, c->c, c->phi, phi_ref, c->p.nx, c->p.ny, c->part, out, stream);
+    e = launch_diag(walls, c->c, phi, phi_ref, c->p.nx, c->p.ny, c->part, out, stream);
   return e == hipSuccess ? LBM_CH_OK : hip_fail(e);
 }
 
@@ -829,6 +833,7 @@ int lbm_ch_load_state(lbm_ch_ctx* c, const void* src, size_t bytes, int64_t step
     e = hipMemcpyAsync(c->f[c->cur], (const char*)src + g, f, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess && c->xh)
     e = hipMemcpyAsync(c->xh, (const char*)src + g + fo, x, hipMemcpyDeviceToDevice, stream);
+  if (e == hipSuccess) e = refresh_sum(c, stream);
   if (e != hipSuccess) return hip_fail(e);
   c->step = step;
   return LBM_CH_OK;
@@ -842,7 +847,6 @@ int lbm_ch_set_tiles(lbm_ch_ctx* c, int32_t tx, int32_t ty) {
     return LBM_CH_EINVAL;
   }
   apply_tiles(c, tx, ty);
-  c->march1 = false;
   return LBM_CH_OK;
 }
 
@@ -879,28 +883,19 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
   int btx = tx0, bty = ty0;
   const int nx = c->p.nx, ny = c->p.ny;
   const bool pass = pass_eligible(c->p);
-  const bool march0 = c->march1;
-  bool bmarch = false;
-  // xx = -1: the march between populations, where it serves (with the default tiles)
-  const bool march = c->p.velocity_mode != LBM_CH_VEL_NS &&
-                     march_ok(c->p.walls != 0, c->vmode, c->p.model, tau_one(c));
-  for (int xx : {-1, 0, 64, 128, 256, 512}) {
+  for (int xx : {0, 64, 128, 256, 512}) {
     if (e != hipSuccess) break;
+    if (c->keep && best >= 0.0f) break;  // steps in strips of their own: one shape times them
     if (xx == 0 && !pass) continue;
-    if (xx < 0 && !march) continue;
-    c->march1 = xx < 0;
     if (xx > 64 && xx / 2 >= nx) continue;  // more than half the lanes idle
     for (int yy : {1, 2, 4, 8, 16, 32}) {
       if (xx == 0 && yy != 4 && yy != 8 && yy != 16) continue;
-      if (xx < 0 && yy != 1) continue;
       if (yy > ny && yy > 2) continue;
-      if (xx >= 0) apply_tiles(c, xx, yy);
+      apply_tiles(c, xx, yy);
       r = run_steps(c, 1, nullptr, stream);  // untimed: first launch of this kernel shape
       if (r == LBM_CH_OK) {
         e = hipEventRecord(e0, stream);
-        // single steps: the launches that the tile shape governs
-        for (int k = 0; e == hipSuccess && r == LBM_CH_OK && k < trial_steps; ++k)
-          r = run_steps(c, 1, nullptr, stream);
+        if (e == hipSuccess) r = run_steps(c, trial_steps, nullptr, stream);
         if (e == hipSuccess && r == LBM_CH_OK) e = hipEventRecord(e1, stream);
         if (e == hipSuccess && r == LBM_CH_OK) e = hipEventSynchronize(e1);
       }
@@ -909,7 +904,6 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
       if (e != hipSuccess || r != LBM_CH_OK) break;
       if (best < 0.0f || ms < best) {
         best = ms;
-        bmarch = xx < 0;
         btx = xx;
         bty = yy;
       }
@@ -920,9 +914,7 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
   if (e1) (void)hipEventDestroy(e1);
   // restore the state and the step counter whatever happened above
   const bool ok = e == hipSuccess && r == LBM_CH_OK;
-  if (ok && bmarch) default_tiles(c->p, btx, bty);
   apply_tiles(c, ok ? btx : tx0, ok ? bty : ty0);
-  c->march1 = ok ? bmarch : march0;
   const int r2 = lbm_ch_load_state(c, backup, backup_bytes, step0, stream);
   if (e != hipSuccess) return hip_fail(e);
   if (r != LBM_CH_OK) return r;
@@ -1177,8 +1169,8 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
     a.ux = c->ux; a.uy = c->uy;
     a.tf = time_factor(c, c->step);
     a.nonfinite = c->nf_dev;
-    a.msrc = c->m[0];
-    a.mdst = c->m[1];
+    a.msrc = c->m[c->cur];
+    a.mdst = c->m[1 - c->cur];
     a.mstrips = march_strips(c->p.nx);
     b->built_cur[i] = c->cur;
     b->hstart.push_back(g.total);
@@ -1189,7 +1181,7 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
   for (BatchGroup& g : b->groups) {
     const int want = (g.total + 7) / 8 * 8;
     if (b->persistent) {
-      const int per_cu = phi_batch_blocks_per_cu(g.tx, g.vmode, g.model2, g.t1);
+      const int per_cu = phi_batch_blocks_per_cu(g.tx, g.vmode, g.model2);
       const int resident = b->cus * per_cu / 8 * 8;
       g.grid = want < resident ? want : (resident > 8 ? resident : 8);
     } else {
@@ -1240,37 +1232,34 @@ static int batch_prepare(lbm_ch_batch* b, hipStream_t stream) {
   return stale ? batch_build(b, stream) : LBM_CH_OK;
 }
 
-// Calls of several steps march the tau_g = 1 lattices in the order-parameter form (64
-// lattices of sides 64-512, 20 steps and 64 read-outs: 3050 us with tiles, 1209 as
-// marches); the other lattices, and calls of one step, take the tiles.
+// The tau_g = 1 lattices march in the order-parameter form (64 lattices of sides 64-512: 122
+// us a step with tiles, 46.6 as marches), the first step of a call from the populations
+// and the last one to both forms; the other lattices take the tiles.
 static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipStream_t s) {
-  const bool march = nsteps >= 2;
   for (int64_t k = 0; k < nsteps; ++k) {
-    if (march) {
-      for (const MarchGroup& m : b->marches) {
-        BatchArgs a{};
-        a.args = b->dargs + m.first;
-        a.start = b->dstart + m.start_off;
-        a.n = m.count;
-        a.total = m.total;
-        const bool first = k == 0, last = k == nsteps - 1;
-        // populations: the current buffer is the source, the one that nsteps single steps
-        // would leave current the target (instance entries hold src as of phase 0)
-        const int gpar = first ? (phase & 1) : (int)((phase + nsteps + 1) & 1);
-        const hipError_t e = launch_march_batch(m.vmode, m.model2, first, last, a, gpar,
-                                                (int)((k + 1) & 1), s);
-        if (e != hipSuccess) return e;
-      }
+    for (const MarchGroup& m : b->marches) {
+      BatchArgs a{};
+      a.args = b->dargs + m.first;
+      a.start = b->dstart + m.start_off;
+      a.n = m.count;
+      a.total = m.total;
+      const bool first = k == 0, last = k == nsteps - 1;
+      // instance entries hold the buffers as of phase 0: sources a.src, a.msrc, targets
+      // a.dst, a.mdst.  Step k goes from the buffers of phase + k to the others; the last
+      // one writes the populations of the buffer it leaves current.
+      const int par = (int)((phase + k) & 1);
+      const hipError_t e = launch_march_batch(m.vmode, m.model2, first, last, a, par, par, s);
+      if (e != hipSuccess) return e;
     }
     for (const BatchGroup& g : b->groups) {
-      if (march && g.t1) continue;
+      if (g.t1) continue;
       BatchArgs a{};
       a.args = b->dargs + g.first;
       a.start = b->dstart + g.start_off;
       a.n = g.count;
       a.total = g.total;
       a.parity = (int)((phase + k) & 1);
-      hipError_t e = launch_phi_batch(g.tx, g.vmode, g.model2, g.t1, b->persistent != 0, a, g.grid, s);
+      hipError_t e = launch_phi_batch(g.tx, g.vmode, g.model2, b->persistent != 0, a, g.grid, s);
       if (e != hipSuccess) return e;
     }
   }
@@ -1442,9 +1431,7 @@ int lbm_ch_batch_autotune(lbm_ch_batch* b, void* backup, size_t backup_bytes,
       r = lbm_ch_batch_step(b, 1, 0, stream);  // rebuilds the tables; untimed
       if (r != LBM_CH_OK) break;
       e = hipEventRecord(e0, stream);
-      // single steps: the launches that the tile policy governs
-      for (int k = 0; e == hipSuccess && r == LBM_CH_OK && k < trial_steps; ++k)
-        r = lbm_ch_batch_step(b, 1, 0, stream);
+      if (e == hipSuccess) r = lbm_ch_batch_step(b, trial_steps, 0, stream);
       if (e == hipSuccess && r == LBM_CH_OK) e = hipEventRecord(e1, stream);
       if (e == hipSuccess && r == LBM_CH_OK) e = hipEventSynchronize(e1);
       float ms = 0.0f;

@@ -118,15 +118,23 @@ __global__ void __launch_bounds__(256) k_init(const Coef c, int nx, int ny, uint
   }
 }
 
-template <bool WALLS, int ST>
+// The sum of the populations pulled to each node: phi (T = float), or the FP64 sum that
+// the order-parameter form of a tau_g = 1 state keeps.
+template <bool WALLS, int ST, class T>
 __global__ void __launch_bounds__(256) k_phi_field(const void* __restrict__ g, uint32_t pitch,
-                                                   int nx, int ny, float* __restrict__ phi) {
+                                                   int nx, int ny, T* __restrict__ phi) {
   const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
   if (x >= nx) return;
   float p[9];
   pull9<WALLS, ST>(make_rsrc(g, pop_bytes(ST, pitch, ny)), pitch, ny, y, x,
                    x == 0 ? nx - 1 : x - 1, x == nx - 1 ? 0 : x + 1, p);
-  phi[(uint32_t)y * nx + x] = sum9(p);
+  phi[(uint32_t)y * nx + x] = (T)sum9d(p);
+}
+
+__global__ void __launch_bounds__(256) k_phi_of_sum(const double* __restrict__ m, int64_t n,
+                                                    float* __restrict__ phi) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) phi[i] = (float)m[i];
 }
 
 template <bool WALLS>
@@ -500,24 +508,35 @@ hipError_t launch_init(bool walls, int vmode, int storage, const Coef& c, int nx
   return hipGetLastError();
 }
 
-hipError_t launch_phi_field(bool walls, int storage, const void* g, uint32_t pitch, int nx,
-                            int ny, float* phi, hipStream_t s) {
+template <class T>
+static hipError_t sum_field(bool walls, int storage, const void* g, uint32_t pitch, int nx, int ny,
+                            T* out, hipStream_t s) {
   const dim3 grid((nx + 255) / 256, ny);
+#define LBM_FIELD(ST)                                                                              \
+  if (walls) hipLaunchKernelGGL((k_phi_field<true, ST, T>), grid, dim3(256), 0, s, g, pitch, nx, ny, out); \
+  else hipLaunchKernelGGL((k_phi_field<false, ST, T>), grid, dim3(256), 0, s, g, pitch, nx, ny, out)
   switch (storage) {
-    case ST_F32:
-      if (walls) hipLaunchKernelGGL((k_phi_field<true, ST_F32>), grid, dim3(256), 0, s, g, pitch, nx, ny, phi);
-      else hipLaunchKernelGGL((k_phi_field<false, ST_F32>), grid, dim3(256), 0, s, g, pitch, nx, ny, phi);
-      break;
-    case ST_F16:
-      if (walls) hipLaunchKernelGGL((k_phi_field<true, ST_F16>), grid, dim3(256), 0, s, g, pitch, nx, ny, phi);
-      else hipLaunchKernelGGL((k_phi_field<false, ST_F16>), grid, dim3(256), 0, s, g, pitch, nx, ny, phi);
-      break;
-    case ST_BF16:
-      if (walls) hipLaunchKernelGGL((k_phi_field<true, ST_BF16>), grid, dim3(256), 0, s, g, pitch, nx, ny, phi);
-      else hipLaunchKernelGGL((k_phi_field<false, ST_BF16>), grid, dim3(256), 0, s, g, pitch, nx, ny, phi);
-      break;
+    case ST_F32: LBM_FIELD(ST_F32); break;
+    case ST_F16: LBM_FIELD(ST_F16); break;
+    case ST_BF16: LBM_FIELD(ST_BF16); break;
     default: return hipErrorInvalidValue;
   }
+#undef LBM_FIELD
+  return hipGetLastError();
+}
+
+hipError_t launch_phi_field(bool walls, int storage, const void* g, uint32_t pitch, int nx,
+                            int ny, float* phi, hipStream_t s) {
+  return sum_field(walls, storage, g, pitch, nx, ny, phi, s);
+}
+
+hipError_t launch_sum_field(bool walls, int storage, const void* g, uint32_t pitch, int nx, int ny,
+                            double* m, hipStream_t s) {
+  return sum_field(walls, storage, g, pitch, nx, ny, m, s);
+}
+
+hipError_t launch_phi_of_sum(const double* m, int64_t nodes, float* phi, hipStream_t s) {
+  hipLaunchKernelGGL(k_phi_of_sum, dim3((unsigned)((nodes + 255) / 256)), dim3(256), 0, s, m, nodes, phi);
   return hipGetLastError();
 }
 

@@ -106,24 +106,24 @@ hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int stora
 bool phi_record_fused(bool walls, int vmode, int model, int storage);
 hipError_t launch_phi_record(int tx, int vmode, int model, bool t1, const StepArgs& a,
                              int nblocks, hipStream_t s);
-// Marching steps between the population and order-parameter forms of a tau_g = 1 state
-// (lbm_ch_march.hip): periodic lattices, prescribed velocity, models 1 and 2, any storage
-// (march_ok).  from_g: the source is a.src (populations), else a.msrc; to_g: the result
-// goes to a.dst, else to a.mdst.  a.phi_rec (may be null) receives phi of the source
-// state.  a.mty rows per wave, a.mstrips = march_strips(nx).
+// Marching step of a tau_g = 1 state in the order-parameter form (lbm_ch_march.hip):
+// periodic lattices, prescribed velocity, models 1 and 2, any storage (march_ok).  From
+// a.msrc to a.mdst; to_g: the populations of the new state too, to a.dst.  a.phi_rec (may be
+// null) receives phi of the source state.  a.mty rows per wave, a.mstrips =
+// march_strips(nx).
 constexpr int MARCH_OUT = 58;  // columns of a strip
 constexpr int march_strips(int nx) { return (nx + MARCH_OUT - 1) / MARCH_OUT; }
 bool march_ok(bool walls, int vmode, int model, bool t1);
-hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool to_g,
-                            const StepArgs& a, hipStream_t s);
-// grid: a multiple of 8 workgroups.  persistent: the grid strides over the tiles (size
+hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const StepArgs& a,
+                            hipStream_t s);
+// The lattices of a batch at other tau_g.  grid: a multiple of 8 workgroups.  persistent: the grid strides over the tiles (size
 // it with phi_batch_blocks_per_cu); otherwise one tile per workgroup (grid >= tiles).
-int phi_batch_blocks_per_cu(int tx, int vmode, bool model2, bool t1);
-hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool t1, bool persistent,
-                            const BatchArgs& b, int grid, hipStream_t s);
+int phi_batch_blocks_per_cu(int tx, int vmode, bool model2);
+hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool persistent, const BatchArgs& b,
+                            int grid, hipStream_t s);
 // The same marches over the float32 lattices of a batch: b.start counts waves (strips of
-// chunks of mty rows) instead of tiles, b.total of them.  gpar, mpar: swap the population
-// or sum buffers of every instance.
+// chunks of mty rows) instead of tiles, b.total of them.  from_g: the source is the
+// populations a.src.  gpar, mpar: swap the population or sum buffers of every instance.
 hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, const BatchArgs& b,
                               int gpar, int mpar, hipStream_t s);
 hipError_t launch_ns_step(int tx, bool walls, int storage, const NsArgs& a, int nblocks,
@@ -142,6 +142,10 @@ hipError_t launch_init(bool walls, int vmode, int storage, const Coef& c, int nx
                        float tf, void* g, float* f, hipStream_t s);
 hipError_t launch_phi_field(bool walls, int storage, const void* g, uint32_t pitch, int nx,
                             int ny, float* phi, hipStream_t s);
+// The sum field m of a population state, and phi from it.
+hipError_t launch_sum_field(bool walls, int storage, const void* g, uint32_t pitch, int nx, int ny,
+                            double* m, hipStream_t s);
+hipError_t launch_phi_of_sum(const double* m, int64_t nodes, float* phi, hipStream_t s);
 hipError_t launch_mu_field(bool walls, const Coef& c, const float* phi, int nx, int ny,
                            float* mu, hipStream_t s);
 // One reverse step of the tau_g = 1 phi map (periodic); lam0 must not alias lam1.

@@ -4,9 +4,9 @@
 //
 // At tau_g = 1 the collision of Eq. LB keeps nothing of the pulled populations (g* =
 // g^eq + S/2), so between two steps the state is the field m(x) = sum_i g_i alone: one
-// FP64 value per node instead of nine populations.  A call of several steps reads the
-// populations once, passes m from step to step (16 bytes per node update instead of 72)
-// and writes the populations once, in its last step.  Every step still forms the nine
+// FP64 value per node instead of nine populations.  Such a state is kept in both forms: m
+// passes from step to step (16 bytes per node update instead of 72), and the last step of
+// a call writes the populations as well.  Every step still forms the nine
 // populations of a node exactly as the population kernels store them (collide_t1,
 // stored_values: the float32 values with their mass closure, or the decoded 16-bit
 // codes) and sums the pulled ones in the same order (sum9d), so the result is bitwise
@@ -80,18 +80,18 @@ using ic = std::integral_constant<int, N>;
 template <int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
-  constexpr int M = TO_G ? 2 : 3;
+  constexpr int M = 3;
   constexpr int OUT = MARCH_OUT;
-  static_assert(OUT <= 64 - 2 * M, "a strip and its margins are one wave");
+  static_assert(OUT == 64 - 2 * M, "a strip and its margins are one wave");
   const Coef& c = a.c;
   const int nx = a.nx, ny = a.ny;
   const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
   const uint32_t rb = (uint32_t)nx * 4u;
-  rsrc_t rsrc, rdst, ru, rv, rrec;
+  const rsrc_t rdst = make_rsrc(a.mdst, nodes * 8u);
+  rsrc_t rsrc, rgd, ru, rv, rrec;
   if (FROM_G) rsrc = make_rsrc(a.src, pop_bytes(ST, pitch, ny));
   else rsrc = make_rsrc(a.msrc, nodes * 8u);
-  if (TO_G) rdst = make_rsrc(a.dst, pop_bytes(ST, pitch, ny));
-  else rdst = make_rsrc(a.mdst, nodes * 8u);
+  if (TO_G) rgd = make_rsrc(a.dst, pop_bytes(ST, pitch, ny));
   if (VFIELD) {
     ru = make_rsrc(a.ux, nodes * 4u);
     rv = make_rsrc(a.uy, nodes * 4u);
@@ -109,7 +109,9 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   // each element size (8, 4 and 2 bytes: 0xFFFFFE00, 0xFFFFFF00 and, against at most 1.2e9
   // bytes of 16-bit state, 0x7FFFFF80), which drops the store
   const bool own = lane >= M && lane < M + OUT && xl < nx;
-  const uint32_t cst = own ? (uint32_t)x : 0x3FFFFFC0u;
+  constexpr uint32_t OOB = 0x3FFFFFC0u;
+  const uint32_t cst = own ? (uint32_t)x : OOB;
+  constexpr int K0 = 2 * M;  // rows that enter before the first row is stored
 
   float axc = 0.f, bxc = 0.f;
   if (!VFIELD) {
@@ -146,13 +148,13 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   auto row_x = [](float q) { return east(q) - west(q); };
   auto ddx = [&](float qm, float qp, float X0) { return row_dx(X0, row_x(qp + qm)); };
 
-  // Row K enters slot K % 3; stage: the last of the four above that this row runs.  yo:
-  // the row that is stored.
-  auto push = [&](auto K, auto STAGE, int yo) {
+  // Row K enters slot K % 3; stage: the last of the four above that this row runs.  The sum
+  // of row y0 + i is stored, and with TO_G the populations of the row after it.
+  auto push = [&](auto K, auto STAGE, int i) {
     constexpr int j = decltype(K)::value % 3, j1 = (j + 2) % 3, j2 = (j + 1) % 3;
     constexpr int stage = decltype(STAGE)::value;
     In& I = in[j];
-    const float phi_out = TO_G ? ph[j2] : ph[j];  // phi of the stored row
+    const float phi_out = ph[j];  // phi of row r - 3
     // --- row r
     if (FROM_G) m[j] = sum9d(I.g);
     else m[j] = I.m;
@@ -192,14 +194,13 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     }
     t1_force<MODEL2>(c, ph[j2], ddx(mu[j], mu[j1], xmu[j2]), row_dy(mu[j], mu[j1], hmu[j], hmu[j1]), dx, dy, fx, fy);
     collide_t1(c, ph[j2], mu[j2], u[j2], v[j2], fx, fy, g);
-    if (TO_G) {
-      if (stage < 3) return;
-      if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)yo * rb);
-      finish_store<ST, false>(rdst, pitch, cst, (uint32_t)yo, m[j2], g);
-      return;
-    }
     uint32_t h[9];
-    stored_values<ST>(m[j2], g, h);
+    if (TO_G && (stage == 3 || K == K0 - 1)) {
+      const bool in = stage < 3 || i + 1 < rows;
+      finish_store<ST, false>(rgd, pitch, in ? cst : OOB, (uint32_t)(in ? y0 + i + 1 : y0), m[j2], g);
+    } else {
+      stored_values<ST>(m[j2], g, h);
+    }
     // --- row r - 3: the groups of sum9d, each summed at its source column
     const double oc = ac + (double)g[4], ow = aw + (double)g[8], oe = ae + (double)g[7];
     ac = (double)g[0] + sc;
@@ -209,8 +210,8 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     sw = (double)g[5];
     se = (double)g[6];
     if (stage < 3) return;
-    if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)yo * rb);
-    stb64(rdst, oc + (west(ow) + east(oe)), cst * 8u, (uint32_t)yo * 2u * rb);
+    if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)(y0 + i) * rb);
+    stb64(rdst, oc + (west(ow) + east(oe)), cst * 8u, (uint32_t)(y0 + i) * 2u * rb);
   };
 
   fetch(in[0]);
@@ -220,31 +221,28 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   push(ic<1>{}, ic<0>{}, 0);
   push(ic<2>{}, ic<1>{}, 0);
   push(ic<3>{}, ic<1>{}, 0);
-  if (!TO_G) {
-    push(ic<4>{}, ic<2>{}, 0);
-    push(ic<5>{}, ic<2>{}, 0);
-  }
-  constexpr int K0 = 2 * M;
+  push(ic<4>{}, ic<2>{}, 0);
+  push(ic<K0 - 1>{}, ic<2>{}, -1);
 #pragma unroll 1
   for (int i = 0; i < rows; i += 3) {
-    push(ic<K0>{}, ic<3>{}, y0 + i);
+    push(ic<K0>{}, ic<3>{}, i);
     if (i + 1 >= rows) break;
-    push(ic<K0 + 1>{}, ic<3>{}, y0 + i + 1);
+    push(ic<K0 + 1>{}, ic<3>{}, i + 1);
     if (i + 2 >= rows) break;
-    push(ic<K0 + 2>{}, ic<3>{}, y0 + i + 2);
+    push(ic<K0 + 2>{}, ic<3>{}, i + 2);
   }
 }
 
 constexpr int MARCH_WAVES = 4;  // waves per workgroup (independent of each other)
 
-template <int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
+template <int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
 __global__ void __launch_bounds__(64 * MARCH_WAVES) k_phi_march(const StepArgs a, const int total) {
   // workgroup w runs on XCD w % 8: give each XCD a band of neighbouring strips and chunks
   const int per = gridDim.x >> 3;
   const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (L >= total) return;
-  march_tile<VMODE, MODEL2, ST, FROM_G, TO_G, REC>(a, L);
+  march_tile<VMODE, MODEL2, ST, false, TO_G, REC>(a, L);
 }
 
 // The marches of many lattices in one launch: wave L belongs to the instance whose range of
@@ -288,13 +286,13 @@ k_march_batch(const BatchArgs b, const int gpar, const int mpar) {
 // Workgroups for `total` waves, a multiple of 8 (one band per XCD).
 int march_grid(int total) { return ((total + MARCH_WAVES - 1) / MARCH_WAVES + 7) / 8 * 8; }
 
-template <int ST, bool FROM_G, bool TO_G>
+template <int ST, bool TO_G>
 hipError_t march_f(int vmode, bool model2, const StepArgs& a, hipStream_t s) {
   const int total = a.mstrips * ((a.ny + a.mty - 1) / a.mty);
   const int grid = march_grid(total);
   const bool rec = a.phi_rec != nullptr;
 #define LBM_MARCH(V, M2, R) \
-  hipLaunchKernelGGL((k_phi_march<V, M2, ST, FROM_G, TO_G, R>), dim3(grid), dim3(64 * MARCH_WAVES), 0, s, a, total)
+  hipLaunchKernelGGL((k_phi_march<V, M2, ST, TO_G, R>), dim3(grid), dim3(64 * MARCH_WAVES), 0, s, a, total)
   if (vmode == VEL_SEP) {
     if (model2) { if (rec) LBM_MARCH(VEL_SEP, true, true); else LBM_MARCH(VEL_SEP, true, false); }
     else { if (rec) LBM_MARCH(VEL_SEP, false, true); else LBM_MARCH(VEL_SEP, false, false); }
@@ -307,9 +305,8 @@ hipError_t march_f(int vmode, bool model2, const StepArgs& a, hipStream_t s) {
 }
 
 template <int ST>
-hipError_t march_t(int vmode, bool model2, bool from_g, bool to_g, const StepArgs& a, hipStream_t s) {
-  if (from_g) return to_g ? march_f<ST, true, true>(vmode, model2, a, s) : march_f<ST, true, false>(vmode, model2, a, s);
-  return to_g ? march_f<ST, false, true>(vmode, model2, a, s) : march_f<ST, false, false>(vmode, model2, a, s);
+hipError_t march_t(int vmode, bool model2, bool to_g, const StepArgs& a, hipStream_t s) {
+  return to_g ? march_f<ST, true>(vmode, model2, a, s) : march_f<ST, false>(vmode, model2, a, s);
 }
 
 }  // namespace
@@ -318,14 +315,14 @@ bool march_ok(bool walls, int vmode, int model, bool t1) {
   return !walls && t1 && (vmode == VEL_SEP || vmode == VEL_FIELD) && (model == 1 || model == 2);
 }
 
-hipError_t launch_phi_march(int vmode, int model, int storage, bool from_g, bool to_g,
-                            const StepArgs& a, hipStream_t s) {
+hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const StepArgs& a,
+                            hipStream_t s) {
   if (!march_ok(false, vmode, model, true) || a.mty < 1 || a.mstrips != march_strips(a.nx))
     return hipErrorInvalidValue;
   switch (storage) {
-    case ST_F32: return march_t<ST_F32>(vmode, model == 2, from_g, to_g, a, s);
-    case ST_F16: return march_t<ST_F16>(vmode, model == 2, from_g, to_g, a, s);
-    case ST_BF16: return march_t<ST_BF16>(vmode, model == 2, from_g, to_g, a, s);
+    case ST_F32: return march_t<ST_F32>(vmode, model == 2, to_g, a, s);
+    case ST_F16: return march_t<ST_F16>(vmode, model == 2, to_g, a, s);
+    case ST_BF16: return march_t<ST_BF16>(vmode, model == 2, to_g, a, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -336,7 +333,7 @@ hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, co
   const dim3 grid(march_grid(b.total)), block(64 * MARCH_WAVES);
 #define LBM_MB(V, M2, F, T) hipLaunchKernelGGL((k_march_batch<V, M2, F, T>), grid, block, 0, s, b, gpar, mpar)
 #define LBM_MB_FORM(V, M2)                                                       \
-  if (from_g) { if (to_g) return hipErrorInvalidValue; LBM_MB(V, M2, true, false); } \
+  if (from_g) { if (to_g) { LBM_MB(V, M2, true, true); } else { LBM_MB(V, M2, true, false); } } \
   else if (to_g) { LBM_MB(V, M2, false, true); }                                 \
   else { LBM_MB(V, M2, false, false); }
   if (vmode == VEL_SEP) {

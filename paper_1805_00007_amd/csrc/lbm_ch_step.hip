@@ -783,7 +783,7 @@ k_phi_step(const StepArgs a) {
 // is a multiple of 8, XCD x (workgroups w with w % 8 == x) gets the contiguous range
 // [x per, (x + 1) per), so vertically adjacent tiles of one lattice share an L2.  Same
 // register budget as the single-lattice kernel.
-template <int TX, int VMODE, bool MODEL2, bool T1>
+template <int TX, int VMODE, bool MODEL2>
 __global__ void __launch_bounds__(TX) __attribute__((amdgpu_waves_per_eu(WPE_PHI, 8)))
 k_phi_batch(const BatchArgs b) {
   int v = blockIdx.x;
@@ -803,7 +803,7 @@ k_phi_batch(const BatchArgs b) {
     a.src = a.dst;
     a.dst = const_cast<void*>(t);
   }
-  step_tile<TX, false, VMODE, MODEL2 ? 2 : 1, ST_F32, false, T1>(a, v - b.start[lo_i]);
+  phi_tile<TX, false, VMODE, MODEL2 ? 2 : 1, ST_F32>(a, v - b.start[lo_i]);
 }
 
 // Batched step, persistent: the tiles of many lattices (one instance table entry each)
@@ -814,7 +814,7 @@ k_phi_batch(const BatchArgs b) {
 #ifndef WPE_BATCH
 #define WPE_BATCH 3
 #endif
-template <int TX, int VMODE, bool MODEL2, bool T1>
+template <int TX, int VMODE, bool MODEL2>
 __global__ void __launch_bounds__(TX) __attribute__((amdgpu_waves_per_eu(WPE_BATCH, 8)))
 k_phi_batch_persistent(const BatchArgs b) {
   const int slots = gridDim.x >> 3;
@@ -840,7 +840,7 @@ k_phi_batch_persistent(const BatchArgs b) {
       a.src = a.dst;
       a.dst = const_cast<void*>(t);
     }
-    step_tile<TX, false, VMODE, MODEL2 ? 2 : 1, ST_F32, false, T1>(
+    phi_tile<TX, false, VMODE, MODEL2 ? 2 : 1, ST_F32>(
         a, v - __builtin_amdgcn_readfirstlane(b.start[inst]));
     __syncthreads();  // the LDS rings are reused by the next tile
   }
@@ -868,13 +868,13 @@ hipError_t phi_step_m(int model, bool t1, const StepArgs& a, int nb, hipStream_t
   return hipGetLastError();
 }
 
-template <int TX, bool PERSIST, bool T1>
+template <int TX, bool PERSIST>
 hipError_t phi_batch_t(int vmode, bool model2, const BatchArgs& b, int grid, hipStream_t s) {
 #define LBM_BATCH_LAUNCH(V, M)                                                                 \
   if (PERSIST)                                                                                 \
-    hipLaunchKernelGGL((k_phi_batch_persistent<TX, V, M, T1>), dim3(grid), dim3(TX), 0, s, b); \
+    hipLaunchKernelGGL((k_phi_batch_persistent<TX, V, M>), dim3(grid), dim3(TX), 0, s, b); \
   else                                                                                         \
-    hipLaunchKernelGGL((k_phi_batch<TX, V, M, T1>), dim3(grid), dim3(TX), 0, s, b)
+    hipLaunchKernelGGL((k_phi_batch<TX, V, M>), dim3(grid), dim3(TX), 0, s, b)
   if (vmode == VEL_SEP) {
     if (model2) { LBM_BATCH_LAUNCH(VEL_SEP, true); } else { LBM_BATCH_LAUNCH(VEL_SEP, false); }
   } else {
@@ -1017,16 +1017,15 @@ hipError_t launch_phi_step(int tx, bool walls, int vmode, int model, int storage
   }
 }
 
-int phi_batch_blocks_per_cu(int tx, int vmode, bool model2, bool t1) {
+int phi_batch_blocks_per_cu(int tx, int vmode, bool model2) {
   int nb = 0;
   hipError_t e = hipErrorInvalidValue;
   const bool sep = vmode == VEL_SEP;
-#define LBM_OCC1(T, T1)                                                                                                          \
-  e = sep ? (model2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_SEP, true, T1>, T, 0)    \
-                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_SEP, false, T1>, T, 0))   \
-          : (model2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_FIELD, true, T1>, T, 0)  \
-                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_FIELD, false, T1>, T, 0))
-#define LBM_OCC(T) if (t1) { LBM_OCC1(T, true); } else { LBM_OCC1(T, false); }
+#define LBM_OCC(T)                                                                                                           \
+  e = sep ? (model2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_SEP, true>, T, 0)     \
+                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_SEP, false>, T, 0))    \
+          : (model2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_FIELD, true>, T, 0)   \
+                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_phi_batch_persistent<T, VEL_FIELD, false>, T, 0))
   switch (tx) {
     case 64: LBM_OCC(64); break;
     case 128: LBM_OCC(128); break;
@@ -1034,29 +1033,25 @@ int phi_batch_blocks_per_cu(int tx, int vmode, bool model2, bool t1) {
     default: break;
   }
 #undef LBM_OCC
-#undef LBM_OCC1
   return e == hipSuccess && nb > 0 ? nb : 1;
 }
 
-template <bool PERSIST, bool T1>
+template <bool PERSIST>
 static hipError_t phi_batch_tx(int tx, int vmode, bool model2, const BatchArgs& b, int grid,
                                hipStream_t s) {
   switch (tx) {
-    case 64: return phi_batch_t<64, PERSIST, T1>(vmode, model2, b, grid, s);
-    case 128: return phi_batch_t<128, PERSIST, T1>(vmode, model2, b, grid, s);
-    case 256: return phi_batch_t<256, PERSIST, T1>(vmode, model2, b, grid, s);
+    case 64: return phi_batch_t<64, PERSIST>(vmode, model2, b, grid, s);
+    case 128: return phi_batch_t<128, PERSIST>(vmode, model2, b, grid, s);
+    case 256: return phi_batch_t<256, PERSIST>(vmode, model2, b, grid, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool t1, bool persistent,
-                            const BatchArgs& b, int grid, hipStream_t s) {
+hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool persistent, const BatchArgs& b,
+                            int grid, hipStream_t s) {
   if (grid <= 0 || (grid & 7) != 0 || b.n <= 0) return hipErrorInvalidValue;
-  if (persistent)
-    return t1 ? phi_batch_tx<true, true>(tx, vmode, model2, b, grid, s)
-              : phi_batch_tx<true, false>(tx, vmode, model2, b, grid, s);
-  return t1 ? phi_batch_tx<false, true>(tx, vmode, model2, b, grid, s)
-            : phi_batch_tx<false, false>(tx, vmode, model2, b, grid, s);
+  return persistent ? phi_batch_tx<true>(tx, vmode, model2, b, grid, s)
+                    : phi_batch_tx<false>(tx, vmode, model2, b, grid, s);
 }
 #endif  // LBM_STEP_16BIT_TU
 

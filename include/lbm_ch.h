@@ -163,11 +163,12 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
  * NS step) on `stream`.  The step counter n advances by nsteps.  With NS and model 1 or
  * 2 a step is one launch that advances f and g together (velocity and pressure are
  * formed inside it and not stored; lbm_ch_moments recomputes them); model 3 runs the NS
- * step and then the phase-field step.  Periodic lattices of more than
- * 65536 nodes with a prescribed velocity at tau_g = 1, models 1 and 2, keep the sum of the
- * pulled populations (one FP64 value per node, which at tau_g = 1 is the whole state)
- * beside the populations: steps pass only that from one to the next, and the last step of
- * a call writes the populations too.  Results are those of the populations alone.  Non-finite values:
+ * step and then the phase-field step.  Periodic lattices with a
+ * prescribed velocity at tau_g = 1, models 1 and 2, keep the sum of the pulled populations
+ * (one FP64 value per node, which at tau_g = 1 is the whole state) beside the populations:
+ * steps pass only that from one to the next, several in one launch on small lattices, and
+ * the last launch of a call writes the populations too.  Results are those of the
+ * populations alone.  Non-finite values:
  * every step kernel raises a flag of the context when a phi it sums from the
  * populations is NaN or Inf; the flag lives in 4 bytes of pinned host memory mapped
  * into the device (allocated by lbm_ch_init, freed by lbm_ch_destroy), so it lands on
@@ -210,15 +211,14 @@ int lbm_ch_load_state(lbm_ch_ctx* ctx, const void* src, size_t bytes, int64_t st
                       hipStream_t stream);
 
 /* Tile shape of the step kernels: tx columns (one lane each; 64, 128, 256 or 512) by
- * ty >= 1 rows per thread block (ty is clipped to ny), marching down the rows; or tx = 0:
- * single-pass tiles of 64 columns x ty rows (ty 4, 8 or 16) that pull their rows and a
- * margin of 2 at once, for periodic float32 lattices with a prescribed velocity at
- * tau_g = 1, models 1 and 2 (LBM_CH_EINVAL elsewhere).  The default is chosen at init
- * from the lattice size and storage; it changes speed only, never results.  Lattices that
- * keep their sum field (lbm_ch_step) step in strips of their own, whatever the shape.
- *   Where single-pass tiles serve: with float32 storage below 2048^2 nodes, tx = 0 with
- *   ty = 4 up to 65536 nodes, else 16; with 16-bit storage at every size, ty = 4 up to
- *   65536 nodes, 8 below 2048^2, else 16.
+ * ty >= 1 rows per thread block (ty is clipped to ny), marching down the rows; or tx = 0
+ * with ty 4, 8 or 16 for periodic lattices with a prescribed velocity at tau_g = 1, models
+ * 1 and 2 (LBM_CH_EINVAL elsewhere).  The default is chosen at init from the lattice size
+ * and storage; it changes speed only, never results.  Lattices that keep their sum field
+ * (lbm_ch_step) accept and report shapes, but step in launches of their own.
+ *   On those: with float32 storage below 2048^2 nodes, tx = 0 with ty = 4 up to 65536
+ *   nodes, else 16; with 16-bit storage at every size, ty = 4 up to 65536 nodes, 8 below
+ *   2048^2, else 16.
  *   Otherwise from 2048^2 nodes up: the widest, then tallest, shape with ty from 32 down to 1 that
  *   gives at least 512 blocks with float32 storage, 1024 with 16-bit; tx = 512 needs
  *   1024 blocks of ty = 8 with float32 storage (and takes ty = 16 once that gives 2048

@@ -140,12 +140,12 @@ static bool live(const lbm_ch_ctx* c) { return c && c->magic == CTX_MAGIC; }
 // tau_g = 1 exactly: the collision keeps none of the pulled populations (omega = 1).
 static bool tau_one(const lbm_ch_ctx* c) { return c->p.tau_g == 1.0; }
 
-// The single-pass tile (tx = 0 in lbm_ch_set_tiles) serves periodic lattices with a
-// prescribed velocity at tau_g = 1, models 1 and 2.
+// Tile shapes with tx = 0 belong to periodic lattices with a prescribed velocity at tau_g =
+// 1, models 1 and 2: those that step in the order-parameter form, in launches of their own.
 static bool pass_eligible(const lbm_ch_params& p) {
   const int vmode = p.velocity_mode == LBM_CH_VEL_FIELD ? VEL_FIELD
                     : p.velocity_mode == LBM_CH_VEL_SEPARABLE ? VEL_SEP : -1;
-  return vmode >= 0 && phi_pass_ok(p.walls != 0, vmode, p.model, p.storage, p.tau_g == 1.0);
+  return vmode >= 0 && march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0);
 }
 
 static float time_factor(const lbm_ch_ctx* c, int64_t n) {
@@ -162,7 +162,7 @@ static bool valid_tile(int tx, int ty) {
 static void apply_tiles(lbm_ch_ctx* c, int tx, int ty) {
   drop_graphs(c);  // the launch shape is part of every captured sequence
   const int nx = c->p.nx, ny = c->p.ny;
-  if (tx == 0) {  // single-pass tiles of 64 columns x ty rows (ty is a kernel constant)
+  if (tx == 0) {  // shape of a lattice that steps in launches of its own
     c->tx = 0;
     c->ty = ty;
     c->nstrips = (nx + 63) / 64;
@@ -184,8 +184,9 @@ static void apply_tiles(lbm_ch_ctx* c, int tx, int ty) {
 // gives at least 2 workgroups per CU on 256 CUs (float32), or 4 with 16-bit storage,
 // whose extra decode work per byte needs more waves in flight to cover memory latency;
 // the 512-column tile (8 waves per workgroup; half the halo columns of the 256-column
-// one) by the measured rules below.  Smaller lattices: the single-pass tile where it
-// serves, else the marching rule below; both from sweeps of every shape.
+// one) by the measured rules below.  Smaller lattices: the marching rule below.  Both from
+// sweeps of every shape.  Lattices in the order-parameter form keep the shapes (tx = 0)
+// that callers know for their sizes, without effect on their steps.
 // lbm_ch_set_tiles overrides; lbm_ch_autotune measures.
 static void default_tiles(const lbm_ch_params& p, int& tx_out, int& ty_out) {
   const int nx = p.nx, ny = p.ny;
@@ -199,12 +200,6 @@ static void default_tiles(const lbm_ch_params& p, int& tx_out, int& ty_out) {
   const bool f32 = p.storage == LBM_CH_STORE_F32;
   const long nodes = (long)nx * ny;
   if (pass_eligible(p) && (!f32 || nodes < (4L << 20))) {
-    // single-pass tiles where they serve: below 2048^2 with float32 storage (us per step,
-    // marching default / single pass: 256^2 6.78 / 4.77 (4 rows); 512^2 9.27 / 5.93,
-    // 768^2 16.1 / 12.8, 1536^2 44.0 / 39.7 (16 rows); 1024^2 20.6 / 21.0; from 2048^2
-    // up the march is faster: 61.5 / 66.4), at every size with 16-bit storage (256^2
-    // 7.07 / 4.75 (4 rows); 768^2 17.5 / 9.7, 1536^2 42.6 / 26.8 (8 rows); 2048^2
-    // 52.4 / 42.9, 4096^2 243 / 199 (16 rows))
     tx_out = 0;
     ty_out = nodes <= 65536 ? 4 : (f32 || nodes >= (4L << 20)) ? 16 : 8;
     return;
@@ -320,13 +315,35 @@ static int march_rows(int nx, int ny) {
 }
 
 // Whether a context keeps the sum field m of its state beside the populations and steps in
-// the order-parameter form (lbm_ch_march.hip), from 256^2 nodes up: below, a step of the
-// single-pass tile is as fast (us a step in calls of 40 steps, 128^2: 4.5 / 4.6) and calls
-// of one step faster.  m[cur] then belongs to g[cur] at every return.
+// the order-parameter form (lbm_ch_march.hip).  m[cur] then belongs to g[cur] at every
+// return.
 static bool keeps_sum(const lbm_ch_params& p, int vmode) {
   return p.velocity_mode != LBM_CH_VEL_NS &&
-         march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0) &&
-         (int64_t)p.nx * p.ny > 65536;
+         march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0);
+}
+
+// How a lattice too small for marches takes its steps (launch_phi_block): region rows and
+// steps per launch, or rows = 0 for marches.  A workgroup fills a CU, so a shape serves while
+// its grid fits the 256 CUs at once; the more steps a launch takes, the smaller its output
+// and the larger its grid.  Us a step, float32, calls of 120 steps (march; 16 rows x 2
+// steps; 32 x 4; 32 x 3; 32 x 2), the shape taken first: 128^2 2.70 (16 x 2; march 4.71,
+// 32 x 4 2.90), 201 x 187 2.73 (16 x 2; 4.81, 3.04), 256^2 3.05 (32 x 4; 4.84, 16 x 2
+// 3.76), 300^2 3.55 (32 x 3; 4.82, 32 x 4 5.59), 384^2 3.70 (32 x 3; 4.96), 512^2 5.57
+// (march; 32 x 3 6.80).  Single steps: 16 rows x 1 (128^2 4.54, 300^2 5.21; march 5.42,
+// 5.89) while that fits.
+struct BlockPlan {
+  int rows, steps;
+};
+static BlockPlan block_plan(int nx, int ny, int64_t nsteps) {
+  auto fits = [&](int rows, int t) {
+    const int w = 64 - 6 * t, h = rows - 6 * t;
+    return (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h) <= 256;
+  };
+  if (nsteps == 1) return fits(16, 1) ? BlockPlan{16, 1} : BlockPlan{0, 1};
+  if (fits(16, 2)) return BlockPlan{16, 2};
+  for (int t : {4, 3, 2})
+    if (fits(32, t)) return BlockPlan{32, t};
+  return BlockPlan{0, 1};
 }
 
 static void choose_tiles(lbm_ch_ctx* c) {
@@ -506,24 +523,46 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   return LBM_CH_OK;
 }
 
-// nsteps >= 1 steps of a state kept in the order-parameter form; the last one writes the
-// populations, into the buffer that nsteps steps alternating between the two would.
+// nsteps >= 1 steps of a state kept in the order-parameter form; the last launch writes the
+// populations too, into the buffers that nsteps steps alternating between the two would.
 static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi_out,
                            hipStream_t stream) {
   const int to = c->cur ^ (int)(nsteps & 1);
-  a.mty = march_rows(c->p.nx, c->p.ny);
-  a.mstrips = march_strips(c->p.nx);
+  const size_t nodes = (size_t)c->p.nx * c->p.ny;
+  const BlockPlan plan = block_plan(c->p.nx, c->p.ny, nsteps);
+  // launches: as few as the plan allows, but two where one would read and write m[to]
+  int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
+  if (launches == 1 && to == c->cur) launches = 2;
+  if (plan.rows == 0) {
+    a.mty = march_rows(c->p.nx, c->p.ny);
+    a.mstrips = march_strips(c->p.nx);
+  }
   a.dst = c->g[to];
-  for (int64_t s = 0; s < nsteps; ++s) {
-    const int from = c->cur ^ (int)(s & 1);
-    a.tf = time_factor(c, c->step);
-    a.msrc = c->m[from];
-    a.mdst = c->m[1 - from];
-    a.phi_rec = phi_out ? phi_out + (size_t)s * c->p.nx * c->p.ny : nullptr;
-    const hipError_t e =
-        launch_phi_march(c->vmode, c->p.model, c->p.storage, s == nsteps - 1, a, stream);
+  // the sums go from buffer to buffer through m[1 - to] and the population buffer that is
+  // not the target, whose populations no launch reads, and end in m[to]
+  double* const between[2] = {c->m[1 - to], (double*)c->g[1 - to]};
+  int next = c->cur == to ? 0 : 1;
+  a.msrc = c->m[c->cur];
+  for (int64_t l = 0, done = 0; l < launches; ++l) {
+    const bool last = l == launches - 1;
+    const int64_t k = (nsteps - done) / (launches - l) + ((nsteps - done) % (launches - l) != 0);
+    a.mdst = last ? c->m[to] : between[next];
+    next ^= 1;
+    a.phi_rec = phi_out ? phi_out + (size_t)done * nodes : nullptr;
+    hipError_t e;
+    if (plan.rows == 0) {
+      a.tf = time_factor(c, c->step);
+      e = launch_phi_march(c->vmode, c->p.model, c->p.storage, last, a, stream);
+    } else {
+      BlockSteps b{};
+      b.steps = (int)k;
+      for (int i = 0; i < b.steps; ++i) b.tf[i] = time_factor(c, c->step + i);
+      e = launch_phi_block(plan.rows, c->vmode, c->p.model, c->p.storage, last, a, b, stream);
+    }
     if (e != hipSuccess) return hip_fail(e);
-    c->step += 1;
+    a.msrc = a.mdst;
+    done += k;
+    c->step += k;
   }
   c->cur = to;
   return LBM_CH_OK;
@@ -604,20 +643,10 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
     a.xh = c->xh;
     a.xfirst = c->step == 0 ? 1 : 0;
     float* rec = phi_out ? phi_out + (size_t)s * c->p.nx * c->p.ny : nullptr;
-    if (c->tx == 0) {  // single-pass tiles (record phi themselves with float32 storage)
-      e = hipSuccess;
-      if (rec && c->p.storage != LBM_CH_STORE_F32)
-        e = launch_phi_field(walls, c->p.storage, c->g[src], c->L.pitch, c->p.nx, c->p.ny,
-                             rec, stream);
-      else
-        a.phi_rec = rec;
-      if (e == hipSuccess)
-        e = launch_phi_pass(c->ty, vmode, c->p.model, c->p.storage, a, c->nblocks, stream);
-      a.phi_rec = nullptr;
-    } else if (rec && phi_record_fused(walls, vmode, c->p.model, c->p.storage)) {
+    if (rec && phi_record_fused(walls, vmode, c->p.model, c->p.storage)) {
       // the step writes phi of its source state itself
       a.phi_rec = rec;
-      e = launch_phi_record(c->tx, vmode, c->p.model, tau_one(c), a, c->nblocks, stream);
+      e = launch_phi_record(c->tx, vmode, c->p.model, a, c->nblocks, stream);
       a.phi_rec = nullptr;
     } else {
       if (rec) {
@@ -855,7 +884,7 @@ int lbm_ch_default_tiles(const lbm_ch_params* p, int32_t* tx, int32_t* ty) {
   int x, y;
   default_tiles(*p, x, y);
   *tx = x;
-  *ty = (x != 0 && y > p->ny) ? p->ny : y;  // single-pass rows are a kernel constant
+  *ty = (x != 0 && y > p->ny) ? p->ny : y;  // shapes with tx = 0 are not clipped
   return LBM_CH_OK;
 }
 

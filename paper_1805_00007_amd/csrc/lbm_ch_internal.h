@@ -86,16 +86,6 @@ uint32_t population_bytes(int storage, uint32_t pitch, uint32_t ny);
 // prescribed velocity (other cases ignore it).
 hipError_t launch_phi_step(int tx, bool walls, int vmode, int model, int storage, bool t1,
                            const StepArgs& a, int nblocks, hipStream_t s);
-// The single-pass tau_g = 1 tile (64 columns x rows, rows 4, 8 or 16; nblocks =
-// ceil(nx / 64) ceil(ny / rows); a.nstrips = ceil(nx / 64)): periodic lattices with a
-// prescribed velocity, models 1 and 2, any storage (phi_pass_ok); with float32 storage
-// it writes phi of the source state to a.phi_rec when that is set (16-bit: a.phi_rec
-// must be null).  The 16-bit instances are in lbm_ch_step16.hip (launch_phi_pass16).
-bool phi_pass_ok(bool walls, int vmode, int model, int storage, bool t1);
-hipError_t launch_phi_pass(int rows, int vmode, int model, int storage, const StepArgs& a,
-                           int nblocks, hipStream_t s);
-hipError_t launch_phi_pass16(int rows, int vmode, int model, int storage, const StepArgs& a,
-                             int nblocks, hipStream_t s);
 // The 16-bit storage cases of launch_phi_step (storage ST_F16 / ST_BF16), defined in
 // lbm_ch_step16.hip.
 hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int storage, bool t1,
@@ -104,8 +94,8 @@ hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int stora
 // forms anyway).  Periodic float32 lattices with a prescribed velocity (VEL_SEP or
 // VEL_FIELD) and model 1 or 2 only; hipErrorInvalidValue otherwise.
 bool phi_record_fused(bool walls, int vmode, int model, int storage);
-hipError_t launch_phi_record(int tx, int vmode, int model, bool t1, const StepArgs& a,
-                             int nblocks, hipStream_t s);
+hipError_t launch_phi_record(int tx, int vmode, int model, const StepArgs& a, int nblocks,
+                             hipStream_t s);
 // Marching step of a tau_g = 1 state in the order-parameter form (lbm_ch_march.hip):
 // periodic lattices, prescribed velocity, models 1 and 2, any storage (march_ok).  From
 // a.msrc to a.mdst; to_g: the populations of the new state too, to a.dst.  a.phi_rec (may be
@@ -116,6 +106,16 @@ constexpr int march_strips(int nx) { return (nx + MARCH_OUT - 1) / MARCH_OUT; }
 bool march_ok(bool walls, int vmode, int model, bool t1);
 hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const StepArgs& a,
                             hipStream_t s);
+// Up to BLOCK_STEPS marching steps in one launch (small lattices), on regions of 64 columns
+// x `rows` (16 or 32) rows; b.tf: the time factor of each.  phi of step k's source goes to
+// a.phi_rec + k nx ny.
+constexpr int BLOCK_STEPS = 5;
+struct BlockSteps {
+  int steps;
+  float tf[BLOCK_STEPS];
+};
+hipError_t launch_phi_block(int rows, int vmode, int model, int storage, bool to_g,
+                            const StepArgs& a, const BlockSteps& b, hipStream_t s);
 // The lattices of a batch at other tau_g.  grid: a multiple of 8 workgroups.  persistent: the grid strides over the tiles (size
 // it with phi_batch_blocks_per_cu); otherwise one tile per workgroup (grid >= tiles).
 int phi_batch_blocks_per_cu(int tx, int vmode, bool model2);

@@ -281,6 +281,153 @@ k_march_batch(const BatchArgs b, const int gpar, const int mpar) {
   const int first = ((const __attribute__((address_space(4))) int*)(uintptr_t)b.start)[inst];
   march_tile<VMODE, MODEL2, ST_F32, FROM_G, TO_G, false>(a, L - first);
 }
+
+// Several steps of one launch, for lattices too small to fill the chip with marches, where
+// a step is a launch and a trip to memory: a workgroup of 16 waves loads m on a region of
+// 64 columns x 16 K rows (a lane per column, K rows per wave) and takes T steps on it,
+// the valid part shrinking by 3 nodes on every side in each; it yields 64 - 6 T columns
+// x 16 K - 6 T rows.  x neighbours come from the adjacent lanes, y neighbours through LDS
+// in four stages a step (those of march_tile), a barrier after each of the first three.
+// Every value is formed as in march_tile, so results are bitwise the same.
+template <int K, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
+__global__ void __launch_bounds__(1024) k_phi_block(const StepArgs a, const BlockSteps b) {
+  constexpr bool VFIELD = VMODE == VEL_FIELD;
+  constexpr int RR = 16 * K;
+  __shared__ float s_ph[RR][64], s_hp[RR][64], s_qx[RR][64], s_qy[RR][64], s_hq[RR][64];
+  __shared__ float s_mu[RR][64], s_hm[RR][64], s_d[RR][64], s_hd[RR][64];
+  __shared__ float s_g[6][RR][64];  // g_2, g_5, g_6 and g_4, g_7, g_8
+  const Coef& c = a.c;
+  const int nx = a.nx, ny = a.ny, T = b.steps;
+  const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
+  const uint32_t rb = (uint32_t)nx * 4u;
+  const int outc = 64 - 6 * T, outr = RR - 6 * T;
+  const int strips = (nx + outc - 1) / outc;
+  const int x0 = (int)(blockIdx.x % strips) * outc, y0 = (int)(blockIdx.x / strips) * outr;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int xl = x0 - 3 * T + lane;
+  const int x = ((xl % nx) + nx) % nx;
+  const bool own = lane >= 3 * T && lane < 3 * T + outc && xl < nx;
+  constexpr uint32_t OOB = 0x3FFFFFC0u;  // as in march_tile
+  const uint32_t cst = own ? (uint32_t)x : OOB;
+  const rsrc_t rsrc = make_rsrc(a.msrc, nodes * 8u), rdst = make_rsrc(a.mdst, nodes * 8u);
+  const rsrc_t rgd = make_rsrc(a.dst, TO_G ? pop_bytes(ST, pitch, ny) : 0u);
+
+  float axc = 0.f, bxc = 0.f, va[K], vb[K];
+  double m[K];
+  int yw[K];      // lattice row
+  bool ownr[K];   // a row this workgroup stores
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int r = w * K + k, y = y0 - 3 * T + r;
+    yw[k] = ((y % ny) + ny) % ny;
+    ownr[k] = r >= 3 * T && r < 3 * T + outr && y < ny;
+    m[k] = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)yw[k] * 2u * rb);
+    if (VFIELD) {
+      va[k] = a.ux[(uint32_t)yw[k] * nx + x];
+      vb[k] = a.uy[(uint32_t)yw[k] * nx + x];
+    } else {
+      va[k] = ld_uniform(a.ay, yw[k]);
+      vb[k] = ld_uniform(a.by, yw[k]);
+    }
+  }
+  if (!VFIELD) {
+    axc = a.ax[x];
+    bxc = a.bx[x];
+  }
+  auto row_x = [](float q) { return east(q) - west(q); };
+  auto ddx = [&](float qm, float q0, float qp) { return row_dx(row_x(q0), row_x(qp + qm)); };
+
+#pragma unroll 1
+  for (int s = 0; s < T; ++s) {
+    const float tf = b.tf[s];
+    const bool last = s == T - 1;
+    float ph[K], u[K], v[K], hp[K], qx[K], mu[K], dv[K], g[K][9];
+    // rows that stage q of step s still has to form
+    auto active = [&](int r, int q) { return r >= 3 * s + q && r < RR - 3 * s - q; };
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int r = w * K + k;
+      if (!active(r, 0)) continue;
+      ph[k] = (float)m[k];
+      if (__builtin_expect(!__builtin_isfinite(ph[k]), 0) && own && ownr[k] && a.nonfinite)
+        *a.nonfinite = 1;
+      u[k] = VFIELD ? tf * va[k] : axc * (va[k] * tf);
+      v[k] = VFIELD ? tf * vb[k] : bxc * (vb[k] * tf);
+      hp[k] = east(ph[k]) + west(ph[k]);
+      s_ph[r][lane] = ph[k];
+      s_hp[r][lane] = hp[k];
+      if (MODEL2) {
+        qx[k] = ph[k] * u[k];
+        const float qy = ph[k] * v[k];
+        s_qx[r][lane] = qx[k];
+        s_qy[r][lane] = qy;
+        s_hq[r][lane] = east(qy) + west(qy);
+      }
+      if (REC && ownr[k]) {
+        const rsrc_t rrec = make_rsrc(a.phi_rec + (size_t)s * nodes, nodes * 4u);
+        stb(rrec, ph[k], cst * 4u, (uint32_t)yw[k] * rb);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int r = w * K + k;
+      if (!active(r, 1)) continue;
+      mu[k] = t1_mu(c, ph[k], row_lap(s_ph[r - 1][lane], ph[k], s_ph[r + 1][lane], s_hp[r - 1][lane],
+                                      hp[k], s_hp[r + 1][lane]));
+      s_mu[r][lane] = mu[k];
+      s_hm[r][lane] = east(mu[k]) + west(mu[k]);
+      if (MODEL2) {
+        dv[k] = ddx(s_qx[r - 1][lane], qx[k], s_qx[r + 1][lane]) +
+                row_dy(s_qy[r - 1][lane], s_qy[r + 1][lane], s_hq[r - 1][lane], s_hq[r + 1][lane]);
+        s_d[r][lane] = dv[k];
+        s_hd[r][lane] = east(dv[k]) + west(dv[k]);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int r = w * K + k;
+      if (!active(r, 2)) continue;
+      float dx = 0.f, dy = 0.f, fx, fy;
+      const float mm = s_mu[r - 1][lane], mp = s_mu[r + 1][lane];
+      if (MODEL2) {
+        const float dm = s_d[r - 1][lane], dp = s_d[r + 1][lane];
+        dx = ddx(dm, dv[k], dp);
+        dy = row_dy(dm, dp, s_hd[r - 1][lane], s_hd[r + 1][lane]);
+      }
+      t1_force<MODEL2>(c, ph[k], ddx(mm, mu[k], mp), row_dy(mm, mp, s_hm[r - 1][lane], s_hm[r + 1][lane]),
+                       dx, dy, fx, fy);
+      collide_t1(c, ph[k], mu[k], u[k], v[k], fx, fy, g[k]);
+      if (TO_G && last && ownr[k]) {
+        finish_store<ST, false>(rgd, pitch, cst, (uint32_t)yw[k], m[k], g[k]);
+      } else {
+        uint32_t h[9];
+        stored_values<ST>(m[k], g[k], h);
+      }
+      s_g[0][r][lane] = g[k][2];
+      s_g[1][r][lane] = g[k][5];
+      s_g[2][r][lane] = g[k][6];
+      s_g[3][r][lane] = g[k][4];
+      s_g[4][r][lane] = g[k][7];
+      s_g[5][r][lane] = g[k][8];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int r = w * K + k;
+      if (!active(r, 3)) continue;
+      const double oc = ((double)g[k][0] + (double)s_g[0][r - 1][lane]) + (double)s_g[3][r + 1][lane];
+      const double ow = ((double)g[k][1] + (double)s_g[1][r - 1][lane]) + (double)s_g[5][r + 1][lane];
+      const double oe = ((double)g[k][3] + (double)s_g[2][r - 1][lane]) + (double)s_g[4][r + 1][lane];
+      m[k] = oc + (west(ow) + east(oe));
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k)
+    if (ownr[k]) stb64(rdst, m[k], cst * 8u, (uint32_t)yw[k] * 2u * rb);
+}
 #pragma clang fp contract(fast)
 
 // Workgroups for `total` waves, a multiple of 8 (one band per XCD).
@@ -304,6 +451,31 @@ hipError_t march_f(int vmode, bool model2, const StepArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int K, int ST, bool TO_G>
+hipError_t block_f(int vmode, bool model2, const StepArgs& a, const BlockSteps& b, hipStream_t s) {
+  const int outc = 64 - 6 * b.steps, outr = 16 * K - 6 * b.steps;
+  if (b.steps < 1 || b.steps > BLOCK_STEPS || outr < 1) return hipErrorInvalidValue;
+  const int grid = ((a.nx + outc - 1) / outc) * ((a.ny + outr - 1) / outr);
+  const bool rec = a.phi_rec != nullptr;
+#define LBM_BLOCK(V, M2, R) \
+  hipLaunchKernelGGL((k_phi_block<K, V, M2, ST, TO_G, R>), dim3(grid), dim3(1024), 0, s, a, b)
+  if (vmode == VEL_SEP) {
+    if (model2) { if (rec) LBM_BLOCK(VEL_SEP, true, true); else LBM_BLOCK(VEL_SEP, true, false); }
+    else { if (rec) LBM_BLOCK(VEL_SEP, false, true); else LBM_BLOCK(VEL_SEP, false, false); }
+  } else {
+    if (model2) { if (rec) LBM_BLOCK(VEL_FIELD, true, true); else LBM_BLOCK(VEL_FIELD, true, false); }
+    else { if (rec) LBM_BLOCK(VEL_FIELD, false, true); else LBM_BLOCK(VEL_FIELD, false, false); }
+  }
+#undef LBM_BLOCK
+  return hipGetLastError();
+}
+
+template <int K, int ST>
+hipError_t block_t(int vmode, bool model2, bool to_g, const StepArgs& a, const BlockSteps& b,
+                   hipStream_t s) {
+  return to_g ? block_f<K, ST, true>(vmode, model2, a, b, s) : block_f<K, ST, false>(vmode, model2, a, b, s);
+}
+
 template <int ST>
 hipError_t march_t(int vmode, bool model2, bool to_g, const StepArgs& a, hipStream_t s) {
   return to_g ? march_f<ST, true>(vmode, model2, a, s) : march_f<ST, false>(vmode, model2, a, s);
@@ -325,6 +497,21 @@ hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const 
     case ST_BF16: return march_t<ST_BF16>(vmode, model == 2, to_g, a, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_phi_block(int rows, int vmode, int model, int storage, bool to_g,
+                            const StepArgs& a, const BlockSteps& b, hipStream_t s) {
+  if (!march_ok(false, vmode, model, true) || (rows != 16 && rows != 32)) return hipErrorInvalidValue;
+#define LBM_BLOCK_ST(ST)                                                        \
+  return rows == 16 ? block_t<1, ST>(vmode, model == 2, to_g, a, b, s)          \
+                    : block_t<2, ST>(vmode, model == 2, to_g, a, b, s)
+  switch (storage) {
+    case ST_F32: LBM_BLOCK_ST(ST_F32);
+    case ST_F16: LBM_BLOCK_ST(ST_F16);
+    case ST_BF16: LBM_BLOCK_ST(ST_BF16);
+    default: return hipErrorInvalidValue;
+  }
+#undef LBM_BLOCK_ST
 }
 
 hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, const BatchArgs& b,

@@ -602,170 +602,6 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, int L) {
     phi_tile<TX, WALLS, VMODE, MODEL, ST, REC>(a, L);
 }
 
-// ---------------------------------------------------------------------------------
-// Single-pass tile of the tau_g = 1 step (periodic lattice, float32 populations,
-// prescribed velocity, models 1 and 2): for small lattices, where a march is a chain of
-// dependent row loads.  A workgroup owns 64 columns x R rows (one wave per row) and
-// issues every pull it needs at once: its own nodes and a margin of 2 (phi, and q =
-// phi u for model 2); then mu and D on the tile plus 1, then stage 3 on the tile.  The
-// margins are recomputed by each workgroup that needs them (L2 hits), so the workgroup
-// waits for memory once.  Every value is formed by the same expressions as in
-// phi_tile_t1, so results are bitwise those of the marching tiles.
-#pragma clang fp contract(off)
-constexpr int PS_C = 64;          // output columns per workgroup
-constexpr int PS_W = PS_C + 4;    // region row length (margin 2 on each side)
-
-template <int R, int VMODE, bool MODEL2, bool REC, int ST>
-__global__ void __launch_bounds__(64 * R) k_phi_pass(const StepArgs a) {
-  constexpr int NT = 64 * R;
-  constexpr int N = (R + 4) * PS_W;
-  constexpr int NX = N - R * PS_C;                 // margin nodes
-  constexpr int EX = (NX + NT - 1) / NT;
-  __shared__ float s_ph[N], s_mu[N], s_qx[MODEL2 ? N : 1], s_qy[MODEL2 ? N : 1],
-      s_d[MODEL2 ? N : 1];
-  const Coef& c = a.c;
-  const int nx = a.nx, ny = a.ny;
-  const uint32_t pitch = a.pitch;
-  const rsrc_t rsrc = make_rsrc(a.src, pop_bytes(ST, pitch, ny));
-  const rsrc_t rdst = make_rsrc(a.dst, pop_bytes(ST, pitch, ny));
-  int L = blockIdx.x;
-  if (a.xcd_remap) {
-    const int per = gridDim.x >> 3;
-    L = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  }
-  const int x0 = (L % a.nstrips) * PS_C;
-  const int y0 = (L / a.nstrips) * R;
-  const int t = threadIdx.x;
-  const uint32_t nodes = (uint32_t)nx * ny;
-  const uint32_t rb = (uint32_t)nx * 4u;
-
-  // region node (rr, cc) <-> lattice row y0 - 2 + rr, column x0 - 2 + cc (periodic);
-  // x0 - 2 + cc lies in [-2, nx + 64] and y0 - 2 + rr in [-2, ny + R]
-  auto col = [&](int cc) {
-    int x = x0 - 2 + cc;
-    if (nx >= PS_W) return x < 0 ? x + nx : (x >= nx ? x - nx : x);
-    return (x % nx + nx) % nx;
-  };
-  auto row = [&](int rr) {
-    int y = y0 - 2 + rr;
-    if (ny >= R + 4) return y < 0 ? y + ny : (y >= ny ? y - ny : y);
-    return (y % ny + ny) % ny;
-  };
-  // stage 1 at one region node: the pull of the populations with the velocity factors, then
-  // the sum m, phi, the velocity as phi_tile_t1 forms it, and q = phi u into the region
-  struct Pull {
-    float g[9], a, b, ax, bx;
-  };
-  struct Node {
-    double m;
-    float phi, u, v;
-  };
-  auto pull = [&](auto lanes, int rr, int cc, Pull& P) {
-    const int x = col(cc), y = row(rr);
-    const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
-    if constexpr (decltype(lanes)::value)
-      pull9_lanes<false, ST>(rsrc, pitch, ny, y, (uint32_t)x, xm, xp, P.g);
-    else
-      pull9<false, ST>(rsrc, pitch, ny, y, (uint32_t)x, xm, xp, P.g);
-    if (VMODE == VEL_SEP) {
-      P.a = a.ay[y];
-      P.b = a.by[y];
-      P.ax = a.ax[x];
-      P.bx = a.bx[x];
-    } else {
-      const uint32_t k = (uint32_t)y * nx + x;
-      P.a = a.ux[k];
-      P.b = a.uy[k];
-    }
-  };
-  auto node = [&](const Pull& P, int k) {
-    Node n;
-    n.m = sum9d(P.g);
-    n.phi = (float)n.m;
-    const float f = a.tf;  // periodic: the row parity factor is 1
-    n.u = VMODE == VEL_SEP ? P.ax * (P.a * f) : f * P.a;
-    n.v = VMODE == VEL_SEP ? P.bx * (P.b * f) : f * P.b;
-    s_ph[k] = n.phi;
-    if (MODEL2) {
-      s_qx[k] = n.phi * n.u;
-      s_qy[k] = n.phi * n.v;
-    }
-    return n;
-  };
-  using OWN = std::false_type;
-  using MARGIN = std::true_type;
-
-  // own node: column x0 + (t % 64), row y0 + t / 64 (the same for a whole wave)
-  static_assert(PS_C == 64, "one wave per tile row");
-  const int tw = __builtin_amdgcn_readfirstlane(t / PS_C);
-  const int ro = 2 + tw, co = 2 + t % PS_C, ko = ro * PS_W + co;
-  const int xo = x0 + t % PS_C, yo = y0 + tw;
-  const bool own = xo < nx && yo < ny;
-
-  // every pull is issued before the first is used
-  Pull po, pm[EX];
-  pull(OWN{}, ro, co, po);
-  int km[EX];
-#pragma unroll
-  for (int i = 0; i < EX; ++i) {
-    const int e = t + i * NT;
-    km[i] = -1;
-    if (e < NX) {
-      int rr, cc;  // the band of width 2 around the tile, row by row
-      if (e < 2 * PS_W) {
-        rr = e / PS_W;
-        cc = e % PS_W;
-      } else if (e < 2 * PS_W + 4 * R) {
-        const int q = e - 2 * PS_W;
-        rr = 2 + q / 4;
-        const int k = q % 4;
-        cc = k < 2 ? k : PS_C + k;
-      } else {
-        const int q = e - 2 * PS_W - 4 * R;
-        rr = 2 + R + q / PS_W;
-        cc = q % PS_W;
-      }
-      pull(MARGIN{}, rr, cc, pm[i]);
-      km[i] = rr * PS_W + cc;
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  const Node no = node(po, ko);
-  if (__builtin_expect(!__builtin_isfinite(no.phi), 0) && own && a.nonfinite) *a.nonfinite = 1;
-#pragma unroll
-  for (int i = 0; i < EX; ++i)
-    if (km[i] >= 0) node(pm[i], km[i]);
-  __syncthreads();
-  // stage 2: mu and D on the tile plus 1 (Eqs. mu, mark3)
-  for (int e = t; e < (R + 2) * (PS_C + 2); e += NT) {
-    const int k = (1 + e / (PS_C + 2)) * PS_W + 1 + e % (PS_C + 2);
-    s_mu[k] = t1_mu(c, s_ph[k], t1_lap(s_ph + k - PS_W, s_ph + k, s_ph + k + PS_W, 0));
-    if (MODEL2)
-      s_d[k] = t1_dx(s_qx + k - PS_W, s_qx + k, s_qx + k + PS_W, 0) +
-               t1_dy(s_qy + k - PS_W, s_qy + k, s_qy + k + PS_W, 0);
-  }
-  __syncthreads();
-  if (!own) return;
-  // stage 3 (as in phi_tile_t1)
-  if (REC) {
-    const rsrc_t rrec = make_rsrc(a.phi_rec, nodes * 4u);
-    stb_nt(rrec, no.phi, (uint32_t)xo * 4u, (uint32_t)yo * rb);
-  }
-  float g[9];
-  const float* m = s_mu + ko;
-  float dx = 0.0f, dy = 0.0f, fx, fy;
-  if (MODEL2) {
-    const float* dd = s_d + ko;
-    dx = t1_dx(dd - PS_W, dd, dd + PS_W, 0);
-    dy = t1_dy(dd - PS_W, dd, dd + PS_W, 0);
-  }
-  t1_force<MODEL2>(c, no.phi, t1_dx(m - PS_W, m, m + PS_W, 0), t1_dy(m - PS_W, m, m + PS_W, 0),
-                   dx, dy, fx, fy);
-  collide_t1(c, no.phi, s_mu[ko], no.u, no.v, fx, fy, g);
-  finish_store<ST>(rdst, pitch, (uint32_t)xo, (uint32_t)yo, no.m, g);
-}
-#pragma clang fp contract(fast)
-
 template <int TX, bool WALLS, int VMODE, int MODEL, int ST, bool REC = false, bool T1 = false>
 __global__ void __launch_bounds__(TX)
 __attribute__((amdgpu_waves_per_eu(MODEL == 3 ? 3 : WPE_PHI, 8)))
@@ -848,7 +684,7 @@ k_phi_batch_persistent(const BatchArgs b) {
 
 template <int TX, bool WALLS, int VMODE, int ST>
 hipError_t phi_step_m(int model, bool t1, const StepArgs& a, int nb, hipStream_t s) {
-  if constexpr (t1_ok<VMODE, 2, ST>()) {
+  if constexpr (WALLS && t1_ok<VMODE, 2, ST>()) {  // periodic lattices: lbm_ch_march.hip
     if (t1 && (model == 1 || model == 2)) {
       if (model == 2)
         hipLaunchKernelGGL((k_phi_step<TX, WALLS, VMODE, 2, ST, false, true>), dim3(nb), dim3(TX), 0, s, a);
@@ -913,32 +749,6 @@ hipError_t phi_step_t(int tx, bool walls, int vmode, int model, bool t1, const S
   }
 }
 
-template <int R, int ST>
-hipError_t phi_pass_r(int vmode, bool model2, bool rec, const StepArgs& a, int nb, hipStream_t s) {
-#define LBM_PASS(V, M, RC) hipLaunchKernelGGL((k_phi_pass<R, V, M, RC, ST>), dim3(nb), dim3(64 * R), 0, s, a)
-  if (vmode == VEL_SEP) {
-    if (model2) { if (rec) LBM_PASS(VEL_SEP, true, true); else LBM_PASS(VEL_SEP, true, false); }
-    else { if (rec) LBM_PASS(VEL_SEP, false, true); else LBM_PASS(VEL_SEP, false, false); }
-  } else {
-    if (model2) { if (rec) LBM_PASS(VEL_FIELD, true, true); else LBM_PASS(VEL_FIELD, true, false); }
-    else { if (rec) LBM_PASS(VEL_FIELD, false, true); else LBM_PASS(VEL_FIELD, false, false); }
-  }
-#undef LBM_PASS
-  return hipGetLastError();
-}
-
-template <int ST>
-hipError_t phi_pass_t(int rows, int vmode, int model, const StepArgs& a, int nb, hipStream_t s) {
-  const bool rec = a.phi_rec != nullptr, m2 = model == 2;
-  if (rec && ST != ST_F32) return hipErrorInvalidValue;  // 16-bit: phi recorded apart
-  switch (rows) {
-    case 4: return phi_pass_r<4, ST>(vmode, m2, rec, a, nb, s);
-    case 8: return phi_pass_r<8, ST>(vmode, m2, rec, a, nb, s);
-    case 16: return phi_pass_r<16, ST>(vmode, m2, rec, a, nb, s);
-    default: return hipErrorInvalidValue;
-  }
-}
-
 }  // namespace
 
 #ifdef LBM_STEP_16BIT_TU
@@ -952,24 +762,16 @@ hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int stora
     default: return hipErrorInvalidValue;
   }
 }
-hipError_t launch_phi_pass16(int rows, int vmode, int model, int storage, const StepArgs& a,
-                             int nblocks, hipStream_t s) {
-  switch (storage) {
-    case ST_F16: return phi_pass_t<ST_F16>(rows, vmode, model, a, nblocks, s);
-    case ST_BF16: return phi_pass_t<ST_BF16>(rows, vmode, model, a, nblocks, s);
-    default: return hipErrorInvalidValue;
-  }
-}
 #else
 bool phi_record_fused(bool walls, int vmode, int model, int storage) {
   return !walls && storage == ST_F32 && (vmode == VEL_SEP || vmode == VEL_FIELD) &&
          (model == 1 || model == 2);
 }
 
-template <int TX, bool T1>
+template <int TX>
 static hipError_t phi_record_t(int vmode, int model, const StepArgs& a, int nb, hipStream_t s) {
 #define LBM_REC_LAUNCH(V, M) \
-  hipLaunchKernelGGL((k_phi_step<TX, false, V, M, ST_F32, true, T1>), dim3(nb), dim3(TX), 0, s, a)
+  hipLaunchKernelGGL((k_phi_step<TX, false, V, M, ST_F32, true>), dim3(nb), dim3(TX), 0, s, a)
   if (vmode == VEL_SEP) {
     if (model == 2) { LBM_REC_LAUNCH(VEL_SEP, 2); } else { LBM_REC_LAUNCH(VEL_SEP, 1); }
   } else {
@@ -979,32 +781,16 @@ static hipError_t phi_record_t(int vmode, int model, const StepArgs& a, int nb, 
   return hipGetLastError();
 }
 
-hipError_t launch_phi_record(int tx, int vmode, int model, bool t1, const StepArgs& a,
-                             int nblocks, hipStream_t s) {
+hipError_t launch_phi_record(int tx, int vmode, int model, const StepArgs& a, int nblocks,
+                             hipStream_t s) {
   if (!phi_record_fused(false, vmode, model, ST_F32) || !a.phi_rec) return hipErrorInvalidValue;
   switch (tx) {
-    case 64: return t1 ? phi_record_t<64, true>(vmode, model, a, nblocks, s)
-                       : phi_record_t<64, false>(vmode, model, a, nblocks, s);
-    case 128: return t1 ? phi_record_t<128, true>(vmode, model, a, nblocks, s)
-                        : phi_record_t<128, false>(vmode, model, a, nblocks, s);
-    case 256: return t1 ? phi_record_t<256, true>(vmode, model, a, nblocks, s)
-                        : phi_record_t<256, false>(vmode, model, a, nblocks, s);
-    case 512: return t1 ? phi_record_t<512, true>(vmode, model, a, nblocks, s)
-                        : phi_record_t<512, false>(vmode, model, a, nblocks, s);
+    case 64: return phi_record_t<64>(vmode, model, a, nblocks, s);
+    case 128: return phi_record_t<128>(vmode, model, a, nblocks, s);
+    case 256: return phi_record_t<256>(vmode, model, a, nblocks, s);
+    case 512: return phi_record_t<512>(vmode, model, a, nblocks, s);
     default: return hipErrorInvalidValue;
   }
-}
-
-bool phi_pass_ok(bool walls, int vmode, int model, int storage, bool t1) {
-  return !walls && t1 && (vmode == VEL_SEP || vmode == VEL_FIELD) && (model == 1 || model == 2) &&
-         (storage == ST_F32 || storage == ST_F16 || storage == ST_BF16);
-}
-
-hipError_t launch_phi_pass(int rows, int vmode, int model, int storage, const StepArgs& a,
-                           int nblocks, hipStream_t s) {
-  if (!phi_pass_ok(false, vmode, model, storage, true)) return hipErrorInvalidValue;
-  if (storage != ST_F32) return launch_phi_pass16(rows, vmode, model, storage, a, nblocks, s);
-  return phi_pass_t<ST_F32>(rows, vmode, model, a, nblocks, s);
 }
 
 hipError_t launch_phi_step(int tx, bool walls, int vmode, int model, int storage, bool t1,

@@ -1,6 +1,7 @@
-"""Calls of several tau_g = 1 steps pass the sum of the populations from step to step
-(strips of 58 columns, 60 where populations are stored): the state they leave and the
-order parameter they record are bitwise those of single steps."""
+"""tau_g = 1 steps pass the sum of the populations from one to the next: as marches in
+strips of 58 columns, or several in one launch on regions of 64 columns x 16 or 32 rows
+where the lattice is small.  The state a call leaves and the order parameter it records
+are bitwise those of single steps."""
 import numpy as np
 import pytest
 
@@ -22,7 +23,8 @@ def _populations(buf, nx, ny, storage):
 
 
 @pytest.mark.parametrize("storage", [0, 1, 2])
-@pytest.mark.parametrize("nx,ny", [(5, 4), (40, 23), (58, 64), (61, 7), (117, 65), (300, 517)])
+@pytest.mark.parametrize("nx,ny", [(5, 4), (40, 23), (58, 64), (61, 7), (117, 65), (256, 250), (250, 300),
+                                   (300, 517), (701, 640)])
 def test_many_steps_equal_single_steps(nx, ny, storage):
     import paper_1805_00007_amd as lbm
     rng = np.random.default_rng(nx * 1000 + ny)
@@ -52,27 +54,33 @@ def test_many_steps_equal_single_steps(nx, ny, storage):
             s.close()
 
 
-@pytest.mark.parametrize("storage,nx,ny", [(0, 1024, 701), (1, 1901, 1100)])
-def test_single_step_march_equals_tiles(storage, nx, ny):
-    """Single steps by default (16-bit storage at this size: as a march), with marching and
-    with single-pass tiles, and a call of several steps: bitwise the same state."""
+@pytest.mark.parametrize("storage", [0, 1])
+def test_loaded_state_steps_as_the_saved_one(storage):
+    """The sum field kept beside the populations follows a loaded state, also into a batch
+    and back, whatever stepped before."""
     import paper_1805_00007_amd as lbm
     rng = np.random.default_rng(7)
+    nx, ny = 130, 90
     phi0 = np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1)
     field = (rng.uniform(-.04, .04, (ny, nx)), rng.uniform(-.04, .04, (ny, nx)))
-    ref = None
-    for tiles in (None, (64, 8), (512, 16), (0, 8), "many"):
-        s = lbm.Solver(nx, ny, phi0, field=field, storage=storage, **workloads.PRESCRIBED)
-        if tiles == "many":
-            s.step(3)
-        else:
-            if tiles:
-                s.set_tiles(*tiles)
-            s.step(1).step(1).step(1)
-        got = _populations(s.save_state()[0], nx, ny, storage)
-        s.close()
-        ref = got if ref is None else ref
-        assert torch.equal(got, ref), tiles
+    s = lbm.Solver(nx, ny, phi0, field=field, storage=storage, **workloads.PRESCRIBED)
+    s.step(5)
+    saved = s.save_state()
+    ref = s.step(9).phi()
+    for n in (1, 2, 7):
+        s.step(n)
+        s.load_state(*saved)
+        assert torch.equal(s.step(4).step(5).phi(), ref), n
+    if storage == 0:
+        s.load_state(*saved)
+        b = lbm.Batch([s])
+        b.step(2)
+        s.step(3)
+        b.step(1)
+        s.step(3)
+        b.close()
+        assert torch.equal(s.phi(), ref)
+    s.close()
 
 
 def test_batch_marches_equal_single_steps():

@@ -215,7 +215,8 @@ int lbm_ch_load_state(lbm_ch_ctx* ctx, const void* src, size_t bytes, int64_t st
  * with ty 4, 8 or 16 for periodic lattices with a prescribed velocity at tau_g = 1, models
  * 1 and 2 (LBM_CH_EINVAL elsewhere).  The default is chosen at init from the lattice size
  * and storage; it changes speed only, never results.  Lattices that keep their sum field
- * (lbm_ch_step) accept and report shapes, but step in launches of their own.
+ * (lbm_ch_step) accept and report shapes, but step in launches of their own.  Some lattices
+ * with a prescribed velocity at other tau_g also do so until a shape is set.
  *   On those: with float32 storage below 2048^2 nodes, tx = 0 with ty = 4 up to 65536
  *   nodes, else 16; with 16-bit storage at every size, ty = 4 up to 65536 nodes, 8 below
  *   2048^2, else 16.

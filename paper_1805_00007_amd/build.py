@@ -11,6 +11,7 @@ LIB = os.path.join(HERE, "liblbm_ch.so")
 SOURCES = [os.path.join(HERE, "csrc", "lbm_ch_step.hip"),
            os.path.join(HERE, "csrc", "lbm_ch_step16.hip"),
            os.path.join(HERE, "csrc", "lbm_ch_march.hip"),
+           os.path.join(HERE, "csrc", "lbm_ch_pop.hip"),
            os.path.join(HERE, "csrc", "lbm_ch_ns.hip"),
            os.path.join(HERE, "csrc", "lbm_ch_aux.hip"),
            os.path.join(HERE, "csrc", "lbm_ch_api.cpp")]

@@ -112,6 +112,7 @@ struct lbm_ch_ctx {
   std::vector<double> tf;
   int tx, ty, nstrips, nblocks, xcd_remap;
   bool keep;  // m[cur] is kept beside g[cur] (keeps_sum)
+  bool pop;   // population steps run as marches (pop_march_ok; off once a tile shape is set)
   int graphs;                     // lbm_ch_set_graphs: replay captured launch sequences
   hipStream_t cap;                // capture stream, created at the first capture
   std::vector<struct CtxExec> execs;  // cached executable graphs, most recently used last
@@ -322,6 +323,21 @@ static bool keeps_sum(const lbm_ch_params& p, int vmode) {
          march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0);
 }
 
+// Whether the population step of a prescribed flow at another tau_g runs as a march in
+// registers (lbm_ch_pop.hip) instead of with tiles.  Us a step at tau_g = 0.8, tile / march,
+// float32 Model-II: 128^2 6.4 / 6.4, 256^2 6.9 / 6.6, 512^2 9.8 / 8.4, 768^2 17.1 / 11.8, 1500
+// x 1003 32.8 / 21.8, 1792^2 60 / 41; 2048^2 63 / 71, 4096^2 218 / 315: beyond the 256 MB
+// cache behind L2 the march's strips, which store parts of lines, lose to the tiles.  Model
+// 3 with walls 128^2 7.2 / 7.3, 768^2 18.9 / 13.0.  Half storage 1792^2 54 / 33, 4096^2 227 /
+// 195.
+static bool pop_march_ok(const lbm_ch_params& p) {
+  if (p.velocity_mode == LBM_CH_VEL_NS || p.tau_g == 1.0) return false;
+  const int64_t nodes = (int64_t)p.nx * p.ny;
+  if (nodes < 30000) return false;
+  if (p.storage != LBM_CH_STORE_F32) return nodes <= (20 << 20);
+  return nodes * (p.model == 3 ? 88 : 72) <= (256 << 20);
+}
+
 // How a lattice too small for marches takes its steps (launch_phi_block): region rows and
 // steps per launch, or rows = 0 for marches.  A workgroup fills a CU, so a shape serves while
 // its grid fits the 256 CUs at once; the more steps a launch takes, the smaller its output
@@ -501,6 +517,7 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
     c->tf.assign(vel->time_factor, vel->time_factor + vel->n_time_factor);
   choose_tiles(c);
   c->keep = keeps_sum(*p, c->vmode);
+  c->pop = pop_march_ok(*p);
   c->magic = CTX_MAGIC;
 
   hipError_t e = launch_fill(z, 0.0f, 2 * (int64_t)(p->nx + p->ny), stream);
@@ -600,6 +617,12 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
   // of 64 columns x rows; model 3 keeps the two launches (NS step, then phase field).
   const bool fused = ns && (c->p.model == 1 || c->p.model == 2);
   if (c->keep) return run_steps_march(c, a, nsteps, phi_out, stream);
+  const bool pop_march = c->pop;
+  if (pop_march) {
+    const MarchShape m{pop_march_strips(c->p.nx), c->p.ny};
+    a.mstrips = m.strips;
+    a.mty = march_rows(&m, 1);
+  }
   StepArgs r = a;
   int rt_rows = 0, rt_blocks = 0;
   if (fused) {
@@ -648,6 +671,8 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
       a.phi_rec = rec;
       e = launch_phi_record(c->tx, vmode, c->p.model, a, c->nblocks, stream);
       a.phi_rec = nullptr;
+    } else if (pop_march && !rec) {
+      e = launch_pop_march(walls, vmode, c->p.model, c->p.storage, a, stream);
     } else {
       if (rec) {
         e = launch_phi_field(walls, c->p.storage, c->g[src], c->L.pitch, c->p.nx, c->p.ny,
@@ -876,6 +901,7 @@ int lbm_ch_set_tiles(lbm_ch_ctx* c, int32_t tx, int32_t ty) {
     return LBM_CH_EINVAL;
   }
   apply_tiles(c, tx, ty);
+  c->pop = false;
   return LBM_CH_OK;
 }
 
@@ -914,7 +940,7 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
   const bool pass = pass_eligible(c->p);
   for (int xx : {0, 64, 128, 256, 512}) {
     if (e != hipSuccess) break;
-    if (c->keep && best >= 0.0f) break;  // steps in strips of their own: one shape times them
+    if ((c->keep || c->pop) && best >= 0.0f) break;  // launches of their own: one trial times them
     if (xx == 0 && !pass) continue;
     if (xx > 64 && xx / 2 >= nx) continue;  // more than half the lanes idle
     for (int yy : {1, 2, 4, 8, 16, 32}) {

@@ -106,6 +106,13 @@ constexpr int march_strips(int nx) { return (nx + MARCH_OUT - 1) / MARCH_OUT; }
 bool march_ok(bool walls, int vmode, int model, bool t1);
 hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const StepArgs& a,
                             hipStream_t s);
+// Population step of any tau_g as a march in registers (lbm_ch_pop.hip): prescribed
+// velocity, every model and storage (model 3: float32).  a.mty rows per wave, a.mstrips =
+// pop_march_strips(nx).
+constexpr int POP_MARCH_OUT = 60;
+constexpr int pop_march_strips(int nx) { return (nx + POP_MARCH_OUT - 1) / POP_MARCH_OUT; }
+hipError_t launch_pop_march(bool walls, int vmode, int model, int storage, const StepArgs& a,
+                            hipStream_t s);
 // Up to BLOCK_STEPS marching steps in one launch (small lattices), on regions of 64 columns
 // x `rows` (16 or 32) rows; b.tf: the time factor of each.  phi of step k's source goes to
 // a.phi_rec + k nx ny.

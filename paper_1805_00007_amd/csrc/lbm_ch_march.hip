@@ -12,6 +12,7 @@
 // codes) and sums the pulled ones in the same order (sum9d), so the result is bitwise
 // that of single steps.
 #include "lbm_ch_device.h"
+#include "lbm_ch_lanes.h"
 #include "lbm_ch_stencil.h"
 
 #include <type_traits>
@@ -21,27 +22,6 @@ namespace {
 
 #pragma clang fp contract(off)
 
-// The value of the lane to the west (x - 1) and to the east (x + 1): whole-wave shifts by
-// one lane; the lane at the end gets 0.
-__device__ __forceinline__ int west_i(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true); }
-__device__ __forceinline__ int east_i(int v) { return __builtin_amdgcn_mov_dpp(v, 0x130, 0xf, 0xf, true); }
-__device__ __forceinline__ float west(float v) {
-  return __builtin_bit_cast(float, west_i(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ float east(float v) {
-  return __builtin_bit_cast(float, east_i(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ double west(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)west_i((int)(uint32_t)u), hi = (uint32_t)west_i((int)(u >> 32));
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double east(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)east_i((int)(uint32_t)u), hi = (uint32_t)east_i((int)(u >> 32));
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ double ldb64(rsrc_t r, uint32_t voff, uint32_t soff) {
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
@@ -49,15 +29,6 @@ __device__ __forceinline__ double ldb64(rsrc_t r, uint32_t voff, uint32_t soff) 
 __device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_t soff) {
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
 }
-// A table read at a wave-uniform index through the scalar cache (never written while a
-// step runs).
-__device__ __forceinline__ float ld_uniform(const float* p, int i) {
-  return ((const __attribute__((address_space(4))) float*)(uintptr_t)p)[i];
-}
-
-template <int N>
-using ic = std::integral_constant<int, N>;
-
 // One wave marches up TY rows of a strip of 64 lanes, one lane per column, with every
 // rolling row in registers and the x neighbours from the adjacent lanes (DPP shifts): no
 // LDS and no barrier, so waves never wait for each other.  Row r enters (pulled or

@@ -110,3 +110,34 @@ def test_batch_marches_equal_single_steps():
     for p in pairs:
         for s in p:
             s.close()
+
+
+@pytest.mark.parametrize("storage,model", [(0, 1), (0, 2), (0, 3), (1, 1), (1, 2), (2, 2)])
+@pytest.mark.parametrize("nx,ny", [(180, 170), (181, 197), (59, 700), (8000, 4)])
+def test_population_march_equals_tiles(nx, ny, storage, model):
+    """The population step at tau_g != 1 as a march in registers (the default at these
+    sizes) leaves bitwise the state of the tiles, with and without walls, for separable
+    and stored velocities."""
+    import paper_1805_00007_amd as lbm
+    rng = np.random.default_rng(nx + ny)
+    phi0 = np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1)
+    tables = dict(ax=rng.uniform(-.04, .04, nx), ay=rng.uniform(-1, 1, ny),
+                  bx=rng.uniform(-.04, .04, nx), by=rng.uniform(-1, 1, ny),
+                  tf=np.cos(0.1 * np.arange(20)))
+    field = (rng.uniform(-.04, .04, (ny, nx)), rng.uniform(-.04, .04, (ny, nx)))
+    for walls, vel, tau in ((0, dict(velocity=tables), 0.8), (1, dict(velocity=tables), 1.3),
+                            (0, dict(field=field), 1.3), (1, dict(field=field), 0.8)):
+        print(nx, ny, storage, model, walls, list(vel), flush=True)
+        got = []
+        for tiles in (None, (64, 8)):
+            s = lbm.Solver(nx, ny, phi0, storage=storage, walls=walls, **vel,
+                           **dict(workloads.PRESCRIBED, model=model, tau_g=tau))
+            if tiles:
+                s.set_tiles(*tiles)
+            s.step(6)
+            got.append(s.save_state()[0])
+            s.close()
+        size = ny * 20 * ((nx + 31) // 32 * 32) if storage else ny * 36 * ((nx + 31) // 32 * 32)
+        a, b = (_populations(x[:size], nx, ny, storage) for x in got)
+        assert torch.equal(a, b)
+        assert torch.equal(got[0][size:], got[1][size:])  # model 3: its history

@@ -163,10 +163,10 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
  * NS step) on `stream`.  The step counter n advances by nsteps.  With NS and model 1 or
  * 2 a step is one launch that advances f and g together (velocity and pressure are
  * formed inside it and not stored; lbm_ch_moments recomputes them); model 3 runs the NS
- * step and then the phase-field step.  Periodic lattices with a
+ * step and then the phase-field step.  Lattices with a
  * prescribed velocity at tau_g = 1, models 1 and 2, keep the sum of the pulled populations
  * (one FP64 value per node, which at tau_g = 1 is the whole state) beside the populations:
- * steps pass only that from one to the next, several in one launch on small lattices, and
+ * steps pass only that from one to the next, several in one launch on small periodic lattices, and
  * the last launch of a call writes the populations too.  Results are those of the
  * populations alone.  Non-finite values:
  * every step kernel raises a flag of the context when a phi it sums from the
@@ -254,7 +254,8 @@ int lbm_ch_set_graphs(lbm_ch_ctx* ctx, int32_t enable);
 
 /* Autotuner: time trial_steps >= 1 steps (after one untimed step) for each tile shape
  * tx in {64, 128, 256, 512} (skipping widths with more than half the lanes idle) and ty in
- * {1, 2, 4, 8, 16, 32} (one of them where the shape is without effect), keep the fastest, and restore the state and step counter from
+ * {1, 2, 4, 8, 16, 32} (one of them where the shape is without effect), keep the fastest,
+ * and restore the state and step counter from
  * `backup`, a caller device buffer of exactly lbm_ch_state_bytes(ctx) bytes.
  * Synchronises `stream`.  *best_us (may be NULL) receives the chosen shape's time per
  * step in microseconds. */

@@ -19,8 +19,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          # no packed-FP32 instructions in the device code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
-# per-source code-generation options: the 16-bit step kernels fit their register budget
-# only without machine-level loop-invariant code motion (see lbm_ch_step16.hip)
+# per-source code-generation options: the 16-bit step kernels are built without
+# machine-level loop-invariant code motion (see lbm_ch_step16.hip)
 EXTRA = {"lbm_ch_step16.hip": ["-mllvm", "-disable-machine-licm"]}
 
 

@@ -146,7 +146,7 @@ static bool tau_one(const lbm_ch_ctx* c) { return c->p.tau_g == 1.0; }
 static bool pass_eligible(const lbm_ch_params& p) {
   const int vmode = p.velocity_mode == LBM_CH_VEL_FIELD ? VEL_FIELD
                     : p.velocity_mode == LBM_CH_VEL_SEPARABLE ? VEL_SEP : -1;
-  return vmode >= 0 && march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0);
+  return vmode >= 0 && !p.walls && march_ok(vmode, p.model, p.tau_g == 1.0);
 }
 
 static float time_factor(const lbm_ch_ctx* c, int64_t n) {
@@ -319,8 +319,7 @@ static int march_rows(int nx, int ny) {
 // the order-parameter form (lbm_ch_march.hip).  m[cur] then belongs to g[cur] at every
 // return.
 static bool keeps_sum(const lbm_ch_params& p, int vmode) {
-  return p.velocity_mode != LBM_CH_VEL_NS &&
-         march_ok(p.walls != 0, vmode, p.model, p.tau_g == 1.0);
+  return p.velocity_mode != LBM_CH_VEL_NS && march_ok(vmode, p.model, p.tau_g == 1.0);
 }
 
 // Whether the population step of a prescribed flow at another tau_g runs as a march in
@@ -546,7 +545,8 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
                            hipStream_t stream) {
   const int to = c->cur ^ (int)(nsteps & 1);
   const size_t nodes = (size_t)c->p.nx * c->p.ny;
-  const BlockPlan plan = block_plan(c->p.nx, c->p.ny, nsteps);
+  // across walls a region would have to mirror its rows anew in every step: marches
+  const BlockPlan plan = c->p.walls ? BlockPlan{0, 1} : block_plan(c->p.nx, c->p.ny, nsteps);
   // launches: as few as the plan allows, but two where one would read and write m[to]
   int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
   if (launches == 1 && to == c->cur) launches = 2;
@@ -566,10 +566,15 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
     a.mdst = last ? c->m[to] : between[next];
     next ^= 1;
     a.phi_rec = phi_out ? phi_out + (size_t)done * nodes : nullptr;
-    hipError_t e;
+    hipError_t e = hipSuccess;
     if (plan.rows == 0) {
       a.tf = time_factor(c, c->step);
-      e = launch_phi_march(c->vmode, c->p.model, c->p.storage, last, a, stream);
+      if (c->p.walls && a.phi_rec) {
+        e = launch_phi_of_sum(a.msrc, (int64_t)nodes, a.phi_rec, stream);
+        a.phi_rec = nullptr;
+      }
+      if (e == hipSuccess)
+        e = launch_phi_march(c->p.walls != 0, c->vmode, c->p.model, c->p.storage, last, a, stream);
     } else {
       BlockSteps b{};
       b.steps = (int)k;
@@ -679,8 +684,7 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
                              rec, stream);
         if (e != hipSuccess) return hip_fail(e);
       }
-      e = launch_phi_step(c->tx, walls, vmode, c->p.model, c->p.storage, tau_one(c), a, c->nblocks,
-                          stream);
+      e = launch_phi_step(c->tx, walls, vmode, c->p.model, c->p.storage, a, c->nblocks, stream);
     }
     if (e != hipSuccess) return hip_fail(e);
     c->cur = dst;

@@ -82,13 +82,11 @@ enum VelMode { VEL_SEP = 0, VEL_FIELD = 1, VEL_NSFIELD = 2 };
 uint32_t population_bytes(int storage, uint32_t pitch, uint32_t ny);
 
 // Launchers (return hipGetLastError() of the launch).
-// t1: tau_g = 1 (omega = 1), which selects the reduced tile for models 1 and 2 with a
-// prescribed velocity (other cases ignore it).
-hipError_t launch_phi_step(int tx, bool walls, int vmode, int model, int storage, bool t1,
+hipError_t launch_phi_step(int tx, bool walls, int vmode, int model, int storage,
                            const StepArgs& a, int nblocks, hipStream_t s);
 // The 16-bit storage cases of launch_phi_step (storage ST_F16 / ST_BF16), defined in
 // lbm_ch_step16.hip.
-hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int storage, bool t1,
+hipError_t launch_phi_step16(int tx, bool walls, int vmode, int model, int storage,
                              const StepArgs& a, int nblocks, hipStream_t s);
 // The same step that also writes phi of the source state to a.phi_rec (the sums stage 1
 // forms anyway).  Periodic float32 lattices with a prescribed velocity (VEL_SEP or
@@ -97,15 +95,15 @@ bool phi_record_fused(bool walls, int vmode, int model, int storage);
 hipError_t launch_phi_record(int tx, int vmode, int model, const StepArgs& a, int nblocks,
                              hipStream_t s);
 // Marching step of a tau_g = 1 state in the order-parameter form (lbm_ch_march.hip):
-// periodic lattices, prescribed velocity, models 1 and 2, any storage (march_ok).  From
+// prescribed velocity, models 1 and 2, any storage (march_ok).  From
 // a.msrc to a.mdst; to_g: the populations of the new state too, to a.dst.  a.phi_rec (may be
-// null) receives phi of the source state.  a.mty rows per wave, a.mstrips =
+// null, and is with walls) receives phi of the source state.  a.mty rows per wave, a.mstrips =
 // march_strips(nx).
 constexpr int MARCH_OUT = 58;  // columns of a strip
 constexpr int march_strips(int nx) { return (nx + MARCH_OUT - 1) / MARCH_OUT; }
-bool march_ok(bool walls, int vmode, int model, bool t1);
-hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const StepArgs& a,
-                            hipStream_t s);
+bool march_ok(int vmode, int model, bool t1);
+hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g,
+                            const StepArgs& a, hipStream_t s);
 // Population step of any tau_g as a march in registers (lbm_ch_pop.hip): prescribed
 // velocity, every model and storage (model 3: float32).  a.mty rows per wave, a.mstrips =
 // pop_march_strips(nx).
@@ -113,7 +111,7 @@ constexpr int POP_MARCH_OUT = 60;
 constexpr int pop_march_strips(int nx) { return (nx + POP_MARCH_OUT - 1) / POP_MARCH_OUT; }
 hipError_t launch_pop_march(bool walls, int vmode, int model, int storage, const StepArgs& a,
                             hipStream_t s);
-// Up to BLOCK_STEPS marching steps in one launch (small lattices), on regions of 64 columns
+// Up to BLOCK_STEPS marching steps in one launch (small periodic lattices), on regions of 64 columns
 // x `rows` (16 or 32) rows; b.tf: the time factor of each.  phi of step k's source goes to
 // a.phi_rec + k nx ny.
 constexpr int BLOCK_STEPS = 5;

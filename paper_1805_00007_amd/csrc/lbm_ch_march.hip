@@ -37,7 +37,8 @@ __device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_
 //   row r - 1: mu, D = div q, and theirs                                        (Eqs. mu, mark3)
 //   row r - 2: F = F1 + F2, the nine populations as storage ST keeps them       (Eqs. t0-phiu, geq, liangFi, LB)
 //   row r - 3: the sum of the populations pulled from rows r - 4 .. r - 2       (streaming)
-// The outer lanes of a strip lose one column of validity per stage, M = 2 or (sums) 3 on
+// Across walls the stencils see mirrored rows (velocity odd) and populations that leave
+// come back at their own node.  The outer lanes of a strip lose one column of validity per stage, M = 2 or (sums) 3 on
 // each side, so a strip yields 58 columns.  A chunk of TY
 // rows marches through 2M more.
 //
@@ -48,7 +49,7 @@ __device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_
 // that writes populations take 35 and 41 us at 2048^2; the latter keeps the default cache
 // policy, because a strip's 240-byte rows are parts of lines that the neighbouring strip
 // completes in L2 (both steps together 67 us, non-temporal 96).
-template <int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
+template <bool WALLS, int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
   constexpr int M = 3;
@@ -92,23 +93,30 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
 
   struct In {
     double m;
-    float g[9], a, b;
+    float g[9], a, b, f;  // f: time factor of the row's velocity, odd across a wall
   };
   In in[3];
   // rows enter in order from y0 - M; past the last needed row the load repeats it (in cache)
-  int lrow = ((y0 - M) % ny + ny) % ny;
+  int lrow = WALLS ? y0 - M : ((y0 - M) % ny + ny) % ny;
   int left = rows + 2 * M;
   auto fetch = [&](In& I) {
-    if (FROM_G) pull9<false, ST>(rsrc, pitch, ny, lrow, (uint32_t)x, xm, xp, I.g);
-    else I.m = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)lrow * 2u * rb);
-    if (VFIELD) {
-      I.a = ldb(ru, (uint32_t)x * 4u, (uint32_t)lrow * rb);
-      I.b = ldb(rv, (uint32_t)x * 4u, (uint32_t)lrow * rb);
-    } else {
-      I.a = ld_uniform(a.ay, lrow);
-      I.b = ld_uniform(a.by, lrow);
+    int row = lrow;
+    I.f = a.tf;
+    if (WALLS) {
+      float sg;
+      row = row_of<true>(lrow, ny, sg);
+      I.f = a.tf * sg;
     }
-    if (--left > 0) lrow = lrow + 1 == ny ? 0 : lrow + 1;
+    if (FROM_G) pull9<WALLS, ST>(rsrc, pitch, ny, row, (uint32_t)x, xm, xp, I.g);
+    else I.m = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)row * 2u * rb);
+    if (VFIELD) {
+      I.a = ldb(ru, (uint32_t)x * 4u, (uint32_t)row * rb);
+      I.b = ldb(rv, (uint32_t)x * 4u, (uint32_t)row * rb);
+    } else {
+      I.a = ld_uniform(a.ay, row);
+      I.b = ld_uniform(a.by, row);
+    }
+    if (--left > 0) lrow = !WALLS && lrow + 1 == ny ? 0 : lrow + 1;
   };
 
   double m[3];
@@ -132,11 +140,11 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     ph[j] = (float)m[j];
     if (__builtin_expect(!__builtin_isfinite(ph[j]), 0) && a.nonfinite) *a.nonfinite = 1;
     if (VFIELD) {
-      u[j] = a.tf * I.a;
-      v[j] = a.tf * I.b;
+      u[j] = I.f * I.a;
+      v[j] = I.f * I.b;
     } else {
-      u[j] = axc * (I.a * a.tf);
-      v[j] = bxc * (I.b * a.tf);
+      u[j] = axc * (I.a * I.f);
+      v[j] = bxc * (I.b * I.f);
     }
     fetch(I);
     hph[j] = east(ph[j]) + west(ph[j]);
@@ -173,7 +181,18 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
       stored_values<ST>(m[j2], g, h);
     }
     // --- row r - 3: the groups of sum9d, each summed at its source column
-    const double oc = ac + (double)g[4], ow = aw + (double)g[8], oe = ae + (double)g[7];
+    double i4 = g[4], i8 = g[8], i7 = g[7];  // what row r - 3 receives from this row
+    if (WALLS && y0 + i + 1 == ny) {  // half-way bounce-back: g_2, g_6, g_5 of row r - 3 itself
+      i4 = sc;
+      i8 = east(se);
+      i7 = west(sw);
+    }
+    const double oc = ac + i4, ow = aw + i8, oe = ae + i7;
+    if (WALLS && y0 + i + 1 == 0) {  // g_4, g_7, g_8 of this row in place of the row below
+      sc = (double)g[4];
+      sw = east((double)g[7]);
+      se = west((double)g[8]);
+    }
     ac = (double)g[0] + sc;
     aw = (double)g[1] + sw;
     ae = (double)g[3] + se;
@@ -192,7 +211,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   push(ic<1>{}, ic<0>{}, 0);
   push(ic<2>{}, ic<1>{}, 0);
   push(ic<3>{}, ic<1>{}, 0);
-  push(ic<4>{}, ic<2>{}, 0);
+  push(ic<4>{}, ic<2>{}, -2);
   push(ic<K0 - 1>{}, ic<2>{}, -1);
 #pragma unroll 1
   for (int i = 0; i < rows; i += 3) {
@@ -206,14 +225,14 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
 
 constexpr int MARCH_WAVES = 4;  // waves per workgroup (independent of each other)
 
-template <int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
+template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
 __global__ void __launch_bounds__(64 * MARCH_WAVES) k_phi_march(const StepArgs a, const int total) {
   // workgroup w runs on XCD w % 8: give each XCD a band of neighbouring strips and chunks
   const int per = gridDim.x >> 3;
   const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (L >= total) return;
-  march_tile<VMODE, MODEL2, ST, false, TO_G, REC>(a, L);
+  march_tile<WALLS, VMODE, MODEL2, ST, false, TO_G, REC>(a, L);
 }
 
 // The marches of many lattices in one launch: wave L belongs to the instance whose range of
@@ -250,7 +269,7 @@ k_march_batch(const BatchArgs b, const int gpar, const int mpar) {
     a.mdst = const_cast<double*>(t);
   }
   const int first = ((const __attribute__((address_space(4))) int*)(uintptr_t)b.start)[inst];
-  march_tile<VMODE, MODEL2, ST_F32, FROM_G, TO_G, false>(a, L - first);
+  march_tile<false, VMODE, MODEL2, ST_F32, FROM_G, TO_G, false>(a, L - first);
 }
 
 // Several steps of one launch, for lattices too small to fill the chip with marches, where
@@ -405,19 +424,23 @@ __global__ void __launch_bounds__(1024) k_phi_block(const StepArgs a, const Bloc
 int march_grid(int total) { return ((total + MARCH_WAVES - 1) / MARCH_WAVES + 7) / 8 * 8; }
 
 template <int ST, bool TO_G>
-hipError_t march_f(int vmode, bool model2, const StepArgs& a, hipStream_t s) {
+hipError_t march_f(bool walls, int vmode, bool model2, const StepArgs& a, hipStream_t s) {
   const int total = a.mstrips * ((a.ny + a.mty - 1) / a.mty);
-  const int grid = march_grid(total);
+  const dim3 grid(march_grid(total)), block(64 * MARCH_WAVES);
   const bool rec = a.phi_rec != nullptr;
-#define LBM_MARCH(V, M2, R) \
-  hipLaunchKernelGGL((k_phi_march<V, M2, ST, TO_G, R>), dim3(grid), dim3(64 * MARCH_WAVES), 0, s, a, total)
+  if (walls && rec) return hipErrorInvalidValue;
+#define LBM_MARCH(W, V, M2, R) \
+  hipLaunchKernelGGL((k_phi_march<W, V, M2, ST, TO_G, R>), grid, block, 0, s, a, total)
+#define LBM_MARCH_FORM(V, M2)                         \
+  if (walls) LBM_MARCH(true, V, M2, false);           \
+  else if (rec) LBM_MARCH(false, V, M2, true);        \
+  else LBM_MARCH(false, V, M2, false)
   if (vmode == VEL_SEP) {
-    if (model2) { if (rec) LBM_MARCH(VEL_SEP, true, true); else LBM_MARCH(VEL_SEP, true, false); }
-    else { if (rec) LBM_MARCH(VEL_SEP, false, true); else LBM_MARCH(VEL_SEP, false, false); }
+    if (model2) { LBM_MARCH_FORM(VEL_SEP, true); } else { LBM_MARCH_FORM(VEL_SEP, false); }
   } else {
-    if (model2) { if (rec) LBM_MARCH(VEL_FIELD, true, true); else LBM_MARCH(VEL_FIELD, true, false); }
-    else { if (rec) LBM_MARCH(VEL_FIELD, false, true); else LBM_MARCH(VEL_FIELD, false, false); }
+    if (model2) { LBM_MARCH_FORM(VEL_FIELD, true); } else { LBM_MARCH_FORM(VEL_FIELD, false); }
   }
+#undef LBM_MARCH_FORM
 #undef LBM_MARCH
   return hipGetLastError();
 }
@@ -448,31 +471,32 @@ hipError_t block_t(int vmode, bool model2, bool to_g, const StepArgs& a, const B
 }
 
 template <int ST>
-hipError_t march_t(int vmode, bool model2, bool to_g, const StepArgs& a, hipStream_t s) {
-  return to_g ? march_f<ST, true>(vmode, model2, a, s) : march_f<ST, false>(vmode, model2, a, s);
+hipError_t march_t(bool walls, int vmode, bool model2, bool to_g, const StepArgs& a, hipStream_t s) {
+  return to_g ? march_f<ST, true>(walls, vmode, model2, a, s)
+              : march_f<ST, false>(walls, vmode, model2, a, s);
 }
 
 }  // namespace
 
-bool march_ok(bool walls, int vmode, int model, bool t1) {
-  return !walls && t1 && (vmode == VEL_SEP || vmode == VEL_FIELD) && (model == 1 || model == 2);
+bool march_ok(int vmode, int model, bool t1) {
+  return t1 && (vmode == VEL_SEP || vmode == VEL_FIELD) && (model == 1 || model == 2);
 }
 
-hipError_t launch_phi_march(int vmode, int model, int storage, bool to_g, const StepArgs& a,
-                            hipStream_t s) {
-  if (!march_ok(false, vmode, model, true) || a.mty < 1 || a.mstrips != march_strips(a.nx))
+hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g,
+                            const StepArgs& a, hipStream_t s) {
+  if (!march_ok(vmode, model, true) || a.mty < 1 || a.mstrips != march_strips(a.nx))
     return hipErrorInvalidValue;
   switch (storage) {
-    case ST_F32: return march_t<ST_F32>(vmode, model == 2, to_g, a, s);
-    case ST_F16: return march_t<ST_F16>(vmode, model == 2, to_g, a, s);
-    case ST_BF16: return march_t<ST_BF16>(vmode, model == 2, to_g, a, s);
+    case ST_F32: return march_t<ST_F32>(walls, vmode, model == 2, to_g, a, s);
+    case ST_F16: return march_t<ST_F16>(walls, vmode, model == 2, to_g, a, s);
+    case ST_BF16: return march_t<ST_BF16>(walls, vmode, model == 2, to_g, a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t launch_phi_block(int rows, int vmode, int model, int storage, bool to_g,
                             const StepArgs& a, const BlockSteps& b, hipStream_t s) {
-  if (!march_ok(false, vmode, model, true) || (rows != 16 && rows != 32)) return hipErrorInvalidValue;
+  if (!march_ok(vmode, model, true) || (rows != 16 && rows != 32)) return hipErrorInvalidValue;
 #define LBM_BLOCK_ST(ST)                                                        \
   return rows == 16 ? block_t<1, ST>(vmode, model == 2, to_g, a, b, s)          \
                     : block_t<2, ST>(vmode, model == 2, to_g, a, b, s)

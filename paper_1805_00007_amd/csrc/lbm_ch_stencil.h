@@ -3,8 +3,8 @@
 // same wherever it is inlined: compiled without implicit multiply-add contraction, with
 // every fused multiply-add written out.  Kernels that compute one value at several
 // places (unrolled copies of a march, halo and own nodes of a tile) use these, so that
-// their results do not depend on the tile shape.  Used by the tau_g = 1 tile
-// (lbm_ch_step.hip) and the single-launch coupled step (lbm_ch_ns.hip); included by the
+// their results do not depend on the tile shape.  Used by the marches and blocks of
+// lbm_ch_march.hip and the single-launch coupled step (lbm_ch_ns.hip); included by the
 // kernel sources only.
 #pragma once
 

@@ -83,6 +83,36 @@ def test_loaded_state_steps_as_the_saved_one(storage):
     s.close()
 
 
+@pytest.mark.parametrize("nx,ny", [(5, 4), (58, 11), (59, 64), (130, 37)])
+def test_walled_marches_against_the_oracle(nx, ny):
+    """tau_g = 1 between walls (marches with mirrored rows and bounce-back), single steps and
+    calls of several, with the recorded order parameter: bitwise alike, and the oracle's phi
+    after 13 steps to 13 steps of ~150 float32 roundings (6e-8 each, at most 1e-6 a step in
+    phi of order 1)."""
+    import oracle
+    import paper_1805_00007_amd as lbm
+    rng = np.random.default_rng(nx + ny)
+    phi0 = np.float32(np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1))
+    U, V = (np.float32(rng.uniform(-.04, .04, (ny, nx))) for _ in range(2))
+    for model in (1, 2):
+        phys = dict(workloads.PRESCRIBED, model=model)
+        one, many = (lbm.Solver(nx, ny, phi0, field=(U, V), walls=1, **phys) for _ in range(2))
+        phis = []
+        for _ in range(13):
+            phis.append(one.phi())
+            one.step(1)
+        traj = torch.empty((6, ny, nx), dtype=torch.float32, device="cuda")
+        many.step(5).record(6, traj).step(2)
+        assert torch.equal(traj, torch.stack(phis[5:11]))
+        assert torch.equal(one.phi(), many.phi())
+        p = oracle.Params(nx=nx, ny=ny, walls=1, **phys)
+        ref = oracle.State(p, phi0.astype(np.float64), U.astype(np.float64),
+                           V.astype(np.float64)).run(13).phi
+        assert np.abs(one.phi().double().cpu().numpy() - ref).max() <= 1.3e-5
+        one.close()
+        many.close()
+
+
 def test_batch_marches_equal_single_steps():
     """A batch call of several steps marches its tau_g = 1 lattices in launches of their own
     (here one per kernel variant, more than 64 lattices in one of them) and leaves bitwise

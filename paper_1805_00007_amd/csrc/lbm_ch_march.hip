@@ -42,13 +42,15 @@ __device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_
 // each side, so a strip yields 58 columns.  A chunk of TY
 // rows marches through 2M more.
 //
-// VALU-bound: about 180 instructions per wave and row, 260 ns of a SIMD (FP64 ones and
-// lane shifts take 4.3-5 cycles, float32 ones 2.9).  2048^2 float32: 26 us a step (67 MB,
-// 2.6 TB/s of cached traffic) against 61.5 us for the population step's 302 MB; 4096^2 80
-// us against 216; half storage 2048^2 30 us against 44.  The step that reads and the step
-// that writes populations take 35 and 41 us at 2048^2; the latter keeps the default cache
-// policy, because a strip's 240-byte rows are parts of lines that the neighbouring strip
-// completes in L2 (both steps together 67 us, non-temporal 96).
+// VALU-bound: about 150 vector instructions per wave and row (FP64 ones and lane shifts
+// take 4.3-5 cycles, float32 ones 2.9); at 2048^2, two waves a SIMD, the VALU is busy 72 %
+// of the launch, and HBM carries 73 MB of the 67 MB a step needs.  2048^2 float32: 26 us a
+// step against 61.5 us for the population step's 302 MB; 4096^2 80 us against 216; half
+// storage 2048^2 30 us against 44.  The step that writes the populations too takes 40 us at
+// 2048^2 (5.1 TB/s); those stores keep the default cache policy, because a strip's rows are
+// parts of lines that the neighbouring strip completes in L2.  A row holds no branch: phi
+// that is NaN or Inf is reported after the march (a test in every row cost 2-3 % at 2048^2,
+// 10 % of a batch).
 template <bool WALLS, int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
@@ -122,6 +124,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   double m[3];
   float ph[3], hph[3], u[3], v[3], qx[3], xqx[3], qy[3], hqy[3];
   float mu[3], xmu[3], hmu[3], dv[3], xd[3], hd[3];
+  bool bad = false;  // a phi that is NaN or Inf (reported at the end: no branch in a row)
   double ac = 0.0, aw = 0.0, ae = 0.0, sc = 0.0, sw = 0.0, se = 0.0;
 
   auto row_x = [](float q) { return east(q) - west(q); };
@@ -138,7 +141,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     if (FROM_G) m[j] = sum9d(I.g);
     else m[j] = I.m;
     ph[j] = (float)m[j];
-    if (__builtin_expect(!__builtin_isfinite(ph[j]), 0) && a.nonfinite) *a.nonfinite = 1;
+    bad |= !__builtin_isfinite(ph[j]);
     if (VFIELD) {
       u[j] = I.f * I.a;
       v[j] = I.f * I.b;
@@ -221,6 +224,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     if (i + 2 >= rows) break;
     push(ic<K0 + 2>{}, ic<3>{}, i + 2);
   }
+  if (bad && a.nonfinite) *a.nonfinite = 1;
 }
 
 constexpr int MARCH_WAVES = 4;  // waves per workgroup (independent of each other)

@@ -216,7 +216,7 @@ def storage_variant(lbm, torch, storage, steps):
            "timed_steps": steps, "bytes_per_lu": round(lu, 2), "tiles": list(tiles),
            "effective_GBps": round(w.nx * w.ny * lu / (ms * 1e-3) / 1e9, 1),
            "roofline": roofline(lu, w.nx * w.ny, ms * 1e3, kernel,
-                                "profiles/phi_step_vortex2048_16bit_kernel_trace.md")}
+                                "profiles/marches_kernel_trace.md")}
     if os.path.exists(GOLDEN):
         g = np.load(GOLDEN)
         s = lbm.solver_for(workloads.metric2048(steps=1000), storage=storage)
@@ -450,7 +450,7 @@ def batch_leg(lbm, torch, steps=5000, plain_steps=200, check_steps=100):
             "bytes_per_lu": round(run_bytes_per_lu(steps) + 8, 2),
             "roofline": roofline(run_bytes_per_lu(steps) + 8, nodes, t_batch * 1e6,
                                  "k_march_batch (all 64 lattices)",
-                                 "profiles/phi_batch_batch64_kernel_trace.md")}
+                                 "profiles/marches_kernel_trace.md")}
 
 
 def main():

@@ -1291,9 +1291,9 @@ static int batch_prepare(lbm_ch_batch* b, hipStream_t stream) {
   return stale ? batch_build(b, stream) : LBM_CH_OK;
 }
 
-// The tau_g = 1 lattices march in the order-parameter form (64 lattices of sides 64-512: 122
-// us a step with tiles, 46.6 as marches), the first step of a call from the populations
-// and the last one to both forms; the other lattices take the tiles.
+// The tau_g = 1 lattices march in the order-parameter form, as they do on their own (64
+// lattices of sides 64-512: 122 us a step with tiles, 46.6 as marches; the last step of a
+// call writes the populations too, 103 us); the other lattices take the tiles.
 static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipStream_t s) {
   for (int64_t k = 0; k < nsteps; ++k) {
     for (const MarchGroup& m : b->marches) {
@@ -1302,12 +1302,10 @@ static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipS
       a.start = b->dstart + m.start_off;
       a.n = m.count;
       a.total = m.total;
-      const bool first = k == 0, last = k == nsteps - 1;
-      // instance entries hold the buffers as of phase 0: sources a.src, a.msrc, targets
-      // a.dst, a.mdst.  Step k goes from the buffers of phase + k to the others; the last
-      // one writes the populations of the buffer it leaves current.
-      const int par = (int)((phase + k) & 1);
-      const hipError_t e = launch_march_batch(m.vmode, m.model2, first, last, a, par, par, s);
+      // instance entries hold the buffers as of phase 0: step k goes from the buffers of
+      // phase + k to the others
+      a.parity = (int)((phase + k) & 1);
+      const hipError_t e = launch_march_batch(m.vmode, m.model2, k == nsteps - 1, a, s);
       if (e != hipSuccess) return e;
     }
     for (const BatchGroup& g : b->groups) {

@@ -127,10 +127,8 @@ int phi_batch_blocks_per_cu(int tx, int vmode, bool model2);
 hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool persistent, const BatchArgs& b,
                             int grid, hipStream_t s);
 // The same marches over the float32 lattices of a batch: b.start counts waves (strips of
-// chunks of mty rows) instead of tiles, b.total of them.  from_g: the source is the
-// populations a.src.  gpar, mpar: swap the population or sum buffers of every instance.
-hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, const BatchArgs& b,
-                              int gpar, int mpar, hipStream_t s);
+// chunks of mty rows) instead of tiles, b.total of them; to_g also writes the populations.
+hipError_t launch_march_batch(int vmode, bool model2, bool to_g, const BatchArgs& b, hipStream_t s);
 hipError_t launch_ns_step(int tx, bool walls, int storage, const NsArgs& a, int nblocks,
                           hipStream_t s);
 // Single-launch coupled step (models 1 and 2): f and g of one time step, output tiles

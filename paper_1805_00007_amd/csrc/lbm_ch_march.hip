@@ -51,7 +51,7 @@ __device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_
 // parts of lines that the neighbouring strip completes in L2.  A row holds no branch: phi
 // that is NaN or Inf is reported after the march (a test in every row cost 2-3 % at 2048^2,
 // 10 % of a batch).
-template <bool WALLS, int VMODE, bool MODEL2, int ST, bool FROM_G, bool TO_G, bool REC>
+template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
   constexpr int M = 3;
@@ -62,9 +62,8 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
   const uint32_t rb = (uint32_t)nx * 4u;
   const rsrc_t rdst = make_rsrc(a.mdst, nodes * 8u);
-  rsrc_t rsrc, rgd, ru, rv, rrec;
-  if (FROM_G) rsrc = make_rsrc(a.src, pop_bytes(ST, pitch, ny));
-  else rsrc = make_rsrc(a.msrc, nodes * 8u);
+  const rsrc_t rsrc = make_rsrc(a.msrc, nodes * 8u);
+  rsrc_t rgd, ru, rv, rrec;
   if (TO_G) rgd = make_rsrc(a.dst, pop_bytes(ST, pitch, ny));
   if (VFIELD) {
     ru = make_rsrc(a.ux, nodes * 4u);
@@ -78,7 +77,6 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   const int rows = min(a.mty, ny - y0);
   const int xl = x0 - M + lane;
   const int x = ((xl % nx) + nx) % nx;
-  const uint32_t xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
   // columns this strip stores; the other lanes store at an offset beyond any buffer for
   // each element size (8, 4 and 2 bytes: 0xFFFFFE00, 0xFFFFFF00 and, against at most 1.2e9
   // bytes of 16-bit state, 0x7FFFFF80), which drops the store
@@ -95,7 +93,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
 
   struct In {
     double m;
-    float g[9], a, b, f;  // f: time factor of the row's velocity, odd across a wall
+    float a, b, f;  // f: time factor of the row's velocity, odd across a wall
   };
   In in[3];
   // rows enter in order from y0 - M; past the last needed row the load repeats it (in cache)
@@ -109,8 +107,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
       row = row_of<true>(lrow, ny, sg);
       I.f = a.tf * sg;
     }
-    if (FROM_G) pull9<WALLS, ST>(rsrc, pitch, ny, row, (uint32_t)x, xm, xp, I.g);
-    else I.m = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)row * 2u * rb);
+    I.m = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)row * 2u * rb);
     if (VFIELD) {
       I.a = ldb(ru, (uint32_t)x * 4u, (uint32_t)row * rb);
       I.b = ldb(rv, (uint32_t)x * 4u, (uint32_t)row * rb);
@@ -138,8 +135,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     In& I = in[j];
     const float phi_out = ph[j];  // phi of row r - 3
     // --- row r
-    if (FROM_G) m[j] = sum9d(I.g);
-    else m[j] = I.m;
+    m[j] = I.m;
     ph[j] = (float)m[j];
     bad |= !__builtin_isfinite(ph[j]);
     if (VFIELD) {
@@ -236,15 +232,14 @@ __global__ void __launch_bounds__(64 * MARCH_WAVES) k_phi_march(const StepArgs a
   const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (L >= total) return;
-  march_tile<WALLS, VMODE, MODEL2, ST, false, TO_G, REC>(a, L);
+  march_tile<WALLS, VMODE, MODEL2, ST, TO_G, REC>(a, L);
 }
 
 // The marches of many lattices in one launch: wave L belongs to the instance whose range of
 // waves holds it, found by every lane testing one start each; its arguments are read
 // through the scalar cache (the tables are written before the launch).
-template <int VMODE, bool MODEL2, bool FROM_G, bool TO_G>
-__global__ void __launch_bounds__(64 * MARCH_WAVES)
-k_march_batch(const BatchArgs b, const int gpar, const int mpar) {
+template <int VMODE, bool MODEL2, bool TO_G>
+__global__ void __launch_bounds__(64 * MARCH_WAVES) k_march_batch(const BatchArgs b) {
   const int per = gridDim.x >> 3;
   const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -262,18 +257,14 @@ k_march_batch(const BatchArgs b, const int gpar, const int mpar) {
 #pragma unroll
   for (int i = 0; i < (int)(sizeof(StepArgs) / 4); ++i) words[i] = src[i];
   __builtin_memcpy(&a, words, sizeof(StepArgs));
-  if (gpar) {
-    const void* t = a.src;
-    a.src = a.dst;
-    a.dst = const_cast<void*>(t);
-  }
-  if (mpar) {
+  if (b.parity) {
+    a.dst = const_cast<void*>(a.src);
     const double* t = a.msrc;
     a.msrc = a.mdst;
     a.mdst = const_cast<double*>(t);
   }
   const int first = ((const __attribute__((address_space(4))) int*)(uintptr_t)b.start)[inst];
-  march_tile<false, VMODE, MODEL2, ST_F32, FROM_G, TO_G, false>(a, L - first);
+  march_tile<false, VMODE, MODEL2, ST_F32, TO_G, false>(a, L - first);
 }
 
 // Several steps of one launch, for lattices too small to fill the chip with marches, where
@@ -513,21 +504,17 @@ hipError_t launch_phi_block(int rows, int vmode, int model, int storage, bool to
 #undef LBM_BLOCK_ST
 }
 
-hipError_t launch_march_batch(int vmode, bool model2, bool from_g, bool to_g, const BatchArgs& b,
-                              int gpar, int mpar, hipStream_t s) {
+hipError_t launch_march_batch(int vmode, bool model2, bool to_g, const BatchArgs& b, hipStream_t s) {
   if (b.n <= 0 || b.total <= 0) return hipErrorInvalidValue;
   const dim3 grid(march_grid(b.total)), block(64 * MARCH_WAVES);
-#define LBM_MB(V, M2, F, T) hipLaunchKernelGGL((k_march_batch<V, M2, F, T>), grid, block, 0, s, b, gpar, mpar)
-#define LBM_MB_FORM(V, M2)                                                       \
-  if (from_g) { if (to_g) { LBM_MB(V, M2, true, true); } else { LBM_MB(V, M2, true, false); } } \
-  else if (to_g) { LBM_MB(V, M2, false, true); }                                 \
-  else { LBM_MB(V, M2, false, false); }
+#define LBM_MB(V, M2)                                                                \
+  if (to_g) hipLaunchKernelGGL((k_march_batch<V, M2, true>), grid, block, 0, s, b);  \
+  else hipLaunchKernelGGL((k_march_batch<V, M2, false>), grid, block, 0, s, b)
   if (vmode == VEL_SEP) {
-    if (model2) { LBM_MB_FORM(VEL_SEP, true) } else { LBM_MB_FORM(VEL_SEP, false) }
+    if (model2) { LBM_MB(VEL_SEP, true); } else { LBM_MB(VEL_SEP, false); }
   } else {
-    if (model2) { LBM_MB_FORM(VEL_FIELD, true) } else { LBM_MB_FORM(VEL_FIELD, false) }
+    if (model2) { LBM_MB(VEL_FIELD, true); } else { LBM_MB(VEL_FIELD, false); }
   }
-#undef LBM_MB_FORM
 #undef LBM_MB
   return hipGetLastError();
 }

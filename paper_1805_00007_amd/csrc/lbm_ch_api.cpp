@@ -345,7 +345,9 @@ static bool pop_march_ok(const lbm_ch_params& p) {
 // 32 x 4 2.90), 201 x 187 2.73 (16 x 2; 4.81, 3.04), 256^2 3.05 (32 x 4; 4.84, 16 x 2
 // 3.76), 300^2 3.55 (32 x 3; 4.82, 32 x 4 5.59), 384^2 3.70 (32 x 3; 4.96), 512^2 5.57
 // (march; 32 x 3 6.80).  Single steps: 16 rows x 1 (128^2 4.54, 300^2 5.21; march 5.42,
-// 5.89) while that fits.
+// 5.89) while that fits.  So too calls of two, which are two launches of one step (one would
+// read and write the same sums): us a call, 16 rows / 32 rows / march: 300^2 10.7 / 13.9 /
+// 11.0, 384^2 13.9 / 14.4 / 11.4, with half storage 384^2 15.2 / 15.1 / 11.5.
 struct BlockPlan {
   int rows, steps;
 };
@@ -354,7 +356,7 @@ static BlockPlan block_plan(int nx, int ny, int64_t nsteps) {
     const int w = 64 - 6 * t, h = rows - 6 * t;
     return (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h) <= 256;
   };
-  if (nsteps == 1) return fits(16, 1) ? BlockPlan{16, 1} : BlockPlan{0, 1};
+  if (nsteps <= 2) return fits(16, 1) ? BlockPlan{16, 1} : BlockPlan{0, 1};
   if (fits(16, 2)) return BlockPlan{16, 2};
   for (int t : {4, 3, 2})
     if (fits(32, t)) return BlockPlan{32, t};

@@ -1294,7 +1294,7 @@ static int batch_prepare(lbm_ch_batch* b, hipStream_t stream) {
 }
 
 // The tau_g = 1 lattices march in the order-parameter form, as they do on their own (64
-// lattices of sides 64-512: 122 us a step with tiles, 46.6 as marches; the last step of a
+// lattices of sides 64-512: 122 us a step with tiles, 42.4 as marches; the last step of a
 // call writes the populations too, 103 us); the other lattices take the tiles.
 static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipStream_t s) {
   for (int64_t k = 0; k < nsteps; ++k) {

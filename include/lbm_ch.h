@@ -70,7 +70,10 @@
  * Every call returns an lbm_ch_status; no exception crosses the ABI.  On an
  * invalid argument nothing is enqueued and the context is unchanged.  A HIP
  * runtime error is returned as LBM_CH_EHIP (lbm_ch_last_hip_error() gives the
- * code).  Calls on one context must not overlap in time from several host threads.
+ * code).  If it struck after earlier launches of the same call had overwritten the state,
+ * the state is lost: calls that step or read it return LBM_CH_ESTATE until
+ * lbm_ch_load_state; otherwise state and step counter are those of the last step that was
+ * enqueued whole.  Calls on one context must not overlap in time from several host threads.
  */
 #ifndef LBM_CH_H
 #define LBM_CH_H
@@ -92,7 +95,7 @@ typedef enum {
   LBM_CH_EUNSUPPORTED = -2, /* valid but not implemented combination                */
   LBM_CH_EHIP = -3,         /* HIP runtime error                                    */
   LBM_CH_ENONFINITE = -4,   /* the order parameter holds NaN or Inf                 */
-  LBM_CH_ESTATE = -5        /* call out of order (e.g. NULL or destroyed context)   */
+  LBM_CH_ESTATE = -5        /* call out of order (NULL or destroyed context, lost state) */
 } lbm_ch_status;
 
 enum {

@@ -113,6 +113,7 @@ struct lbm_ch_ctx {
   int tx, ty, nstrips, nblocks, xcd_remap;
   bool keep;  // m[cur] is kept beside g[cur] (keeps_sum)
   bool pop;   // population steps run as marches (pop_march_ok; off once a tile shape is set)
+  bool lost;  // a launch failed after others of its call had overwritten the state
   int graphs;                     // lbm_ch_set_graphs: replay captured launch sequences
   hipStream_t cap;                // capture stream, created at the first capture
   std::vector<struct CtxExec> execs;  // cached executable graphs, most recently used last
@@ -137,6 +138,8 @@ static void drop_graphs(lbm_ch_ctx* c) {
 static constexpr uint32_t CTX_MAGIC = 0x4c424d43u;
 
 static bool live(const lbm_ch_ctx* c) { return c && c->magic == CTX_MAGIC; }
+// A context whose state can be read and stepped; a lost one takes lbm_ch_load_state first.
+static bool usable(const lbm_ch_ctx* c) { return live(c) && !c->lost; }
 
 // tau_g = 1 exactly: the collision keeps none of the pulled populations (omega = 1).
 static bool tau_one(const lbm_ch_ctx* c) { return c->p.tau_g == 1.0; }
@@ -562,6 +565,14 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
   double* const between[2] = {c->m[1 - to], (double*)c->g[1 - to]};
   int next = c->cur == to ? 0 : 1;
   a.msrc = c->m[c->cur];
+  // Sums between launches go to m[1 - to] and g[1 - to].  For an even count these hold no
+  // state, so a launch that fails leaves the state as it was before the call; for an odd one
+  // they are m[cur] and g[cur], lost once the first launch is enqueued.
+  auto fail = [&](hipError_t e, int64_t launched) {
+    c->lost = launched > 0 && to != c->cur;
+    return hip_fail(e);
+  };
+  const int64_t n0 = c->step;
   for (int64_t l = 0, done = 0; l < launches; ++l) {
     const bool last = l == launches - 1;
     const int64_t k = (nsteps - done) / (launches - l) + ((nsteps - done) % (launches - l) != 0);
@@ -570,7 +581,7 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
     a.phi_rec = phi_out ? phi_out + (size_t)done * nodes : nullptr;
     hipError_t e = hipSuccess;
     if (plan.rows == 0) {
-      a.tf = time_factor(c, c->step);
+      a.tf = time_factor(c, n0 + done);
       if (c->p.walls && a.phi_rec) {
         e = launch_phi_of_sum(a.msrc, (int64_t)nodes, a.phi_rec, stream);
         a.phi_rec = nullptr;
@@ -580,15 +591,15 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
     } else {
       BlockSteps b{};
       b.steps = (int)k;
-      for (int i = 0; i < b.steps; ++i) b.tf[i] = time_factor(c, c->step + i);
+      for (int i = 0; i < b.steps; ++i) b.tf[i] = time_factor(c, n0 + done + i);
       e = launch_phi_block(plan.rows, c->vmode, c->p.model, c->p.storage, last, a, b, stream);
     }
-    if (e != hipSuccess) return hip_fail(e);
+    if (e != hipSuccess) return fail(e, l);
     a.msrc = a.mdst;
     done += k;
-    c->step += k;
   }
   c->cur = to;
+  c->step = n0 + nsteps;
   return LBM_CH_OK;
 }
 
@@ -770,6 +781,7 @@ static int graph_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_
   if (r < 0) {  // nothing ran: the captured host-side updates are undone
     c->cur = cur0;
     c->step = step0;
+    c->lost = false;
   }
   return r;
 }
@@ -782,7 +794,7 @@ static bool nonfinite_seen(const lbm_ch_ctx* c) {
 }
 
 int lbm_ch_step(lbm_ch_ctx* c, int64_t nsteps, hipStream_t stream) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   if (nsteps < 0) return LBM_CH_EINVAL;
   if (nonfinite_seen(c)) return LBM_CH_ENONFINITE;
   return graph_steps(c, nsteps, nullptr, stream);
@@ -798,7 +810,7 @@ int lbm_ch_set_graphs(lbm_ch_ctx* c, int32_t enable) {
 
 int lbm_ch_moments(lbm_ch_ctx* c, float* phi, float* mu, float* ux, float* uy, float* p,
                    hipStream_t stream) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   float* outs[5] = {phi, mu, ux, uy, p};
   for (float* o : outs)
     if (o && !aligned4(o)) return LBM_CH_EINVAL;
@@ -837,7 +849,7 @@ int lbm_ch_moments(lbm_ch_ctx* c, float* phi, float* mu, float* ux, float* uy, f
 }
 
 int lbm_ch_diagnostics(lbm_ch_ctx* c, const float* phi_ref, double* out, hipStream_t stream) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   if (!out || ((uintptr_t)out & 7u) != 0) return LBM_CH_EINVAL;
   if (phi_ref && !aligned4(phi_ref)) return LBM_CH_EINVAL;
   const bool walls = c->p.walls != 0;
@@ -849,7 +861,7 @@ int lbm_ch_diagnostics(lbm_ch_ctx* c, const float* phi_ref, double* out, hipStre
 }
 
 int lbm_ch_check_finite(lbm_ch_ctx* c, hipStream_t stream) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   int r = lbm_ch_diagnostics(c, nullptr, c->diag, stream);
   if (r != LBM_CH_OK) return r;
   double h[8];
@@ -869,7 +881,7 @@ size_t lbm_ch_state_bytes(const lbm_ch_ctx* c) {
 }
 
 int lbm_ch_save_state(lbm_ch_ctx* c, void* dst, size_t bytes, hipStream_t stream) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   if (!dst || bytes != lbm_ch_state_bytes(c)) return LBM_CH_EINVAL;
   const size_t g = c->L.g_state, f = c->L.f_state;
   const size_t fo = c->f[0] ? f : 0, x = (size_t)2 * c->p.nx * c->p.ny * sizeof(float);
@@ -889,12 +901,15 @@ int lbm_ch_load_state(lbm_ch_ctx* c, const void* src, size_t bytes, int64_t step
   const size_t g = c->L.g_state, f = c->L.f_state;
   const size_t fo = c->f[0] ? f : 0, x = (size_t)2 * c->p.nx * c->p.ny * sizeof(float);
   hipError_t e = hipMemcpyAsync(c->g[c->cur], src, g, hipMemcpyDeviceToDevice, stream);
-  if (e == hipSuccess && c->f[0])
+  if (e != hipSuccess) return hip_fail(e);
+  c->lost = true;  // until the whole state is enqueued
+  if (c->f[0])
     e = hipMemcpyAsync(c->f[c->cur], (const char*)src + g, f, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess && c->xh)
     e = hipMemcpyAsync(c->xh, (const char*)src + g + fo, x, hipMemcpyDeviceToDevice, stream);
   if (e == hipSuccess) e = refresh_sum(c, stream);
   if (e != hipSuccess) return hip_fail(e);
+  c->lost = false;
   c->step = step;
   return LBM_CH_OK;
 }
@@ -930,7 +945,7 @@ int lbm_ch_get_tiles(const lbm_ch_ctx* c, int32_t* tx, int32_t* ty) {
 
 int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t trial_steps,
                     hipStream_t stream, float* best_us) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   if (!backup || backup_bytes != lbm_ch_state_bytes(c) || trial_steps < 1)
     return LBM_CH_EINVAL;
   const int64_t step0 = c->step;
@@ -989,7 +1004,7 @@ size_t lbm_ch_adjoint_scratch_bytes(const lbm_ch_params* p) {
 }
 
 int lbm_ch_record(lbm_ch_ctx* c, int64_t nsteps, float* phi_traj, hipStream_t stream) {
-  if (!live(c)) return LBM_CH_ESTATE;
+  if (!usable(c)) return LBM_CH_ESTATE;
   if (nsteps < 0) return LBM_CH_EINVAL;
   if (nonfinite_seen(c)) return LBM_CH_ENONFINITE;
   if (nsteps == 0) return LBM_CH_OK;
@@ -1285,18 +1300,21 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
 static int batch_prepare(lbm_ch_batch* b, hipStream_t stream) {
   bool stale = !b->built;
   for (size_t i = 0; i < b->ctx.size() && !stale; ++i) {
-    if (!live(b->ctx[i])) return LBM_CH_ESTATE;
+    if (!usable(b->ctx[i])) return LBM_CH_ESTATE;
     stale = b->ctx[i]->cur != (b->built_cur[i] ^ b->phase);
   }
   for (lbm_ch_ctx* c : b->ctx)
-    if (!live(c)) return LBM_CH_ESTATE;
+    if (!usable(c)) return LBM_CH_ESTATE;
   return stale ? batch_build(b, stream) : LBM_CH_OK;
 }
 
 // The tau_g = 1 lattices march in the order-parameter form, as they do on their own (64
 // lattices of sides 64-512: 122 us a step with tiles, 42.4 as marches; the last step of a
 // call writes the populations too, 103 us); the other lattices take the tiles.
-static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipStream_t s) {
+// *launched counts the launches enqueued.
+static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipStream_t s,
+                                int64_t* launched) {
+  *launched = 0;
   for (int64_t k = 0; k < nsteps; ++k) {
     for (const MarchGroup& m : b->marches) {
       BatchArgs a{};
@@ -1309,6 +1327,7 @@ static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipS
       a.parity = (int)((phase + k) & 1);
       const hipError_t e = launch_march_batch(m.vmode, m.model2, k == nsteps - 1, a, s);
       if (e != hipSuccess) return e;
+      *launched += 1;
     }
     for (const BatchGroup& g : b->groups) {
       if (g.t1) continue;
@@ -1320,6 +1339,7 @@ static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipS
       a.parity = (int)((phase + k) & 1);
       hipError_t e = launch_phi_batch(g.tx, g.vmode, g.model2, b->persistent != 0, a, g.grid, s);
       if (e != hipSuccess) return e;
+      *launched += 1;
     }
   }
   return hipSuccess;
@@ -1418,9 +1438,14 @@ int lbm_ch_batch_step(lbm_ch_batch* b, int64_t nsteps, int32_t use_graph, hipStr
     if (live(m) && nonfinite_seen(m)) return LBM_CH_ENONFINITE;
   int r = batch_prepare(b, stream);
   if (r != LBM_CH_OK || nsteps == 0) return r;
+  int64_t launched = 0;
   if (!use_graph) {
-    hipError_t e = batch_enqueue(b, nsteps, b->phase, stream);
-    if (e != hipSuccess) return hip_fail(e);
+    hipError_t e = batch_enqueue(b, nsteps, b->phase, stream, &launched);
+    if (e != hipSuccess) {  // some lattices stepped, some did not, and their buffers are mixed
+      if (launched > 0)
+        for (lbm_ch_ctx* m : b->ctx) m->lost = true;
+      return hip_fail(e);
+    }
     batch_advance(b, nsteps);
     return LBM_CH_OK;
   }
@@ -1431,7 +1456,7 @@ int lbm_ch_batch_step(lbm_ch_batch* b, int64_t nsteps, int32_t use_graph, hipStr
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e);
-    hipError_t el = batch_enqueue(b, nsteps, b->phase, b->cap);
+    hipError_t el = batch_enqueue(b, nsteps, b->phase, b->cap, &launched);
     e = hipStreamEndCapture(b->cap, &graph);
     if (el != hipSuccess) e = el;
     if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
@@ -1460,7 +1485,7 @@ int lbm_ch_batch_autotune(lbm_ch_batch* b, void* backup, size_t backup_bytes,
                           int32_t trial_steps, hipStream_t stream, float* best_us) {
   if (!batch_live(b)) return LBM_CH_ESTATE;
   for (lbm_ch_ctx* c : b->ctx)
-    if (!live(c)) return LBM_CH_ESTATE;
+    if (!usable(c)) return LBM_CH_ESTATE;
   if (!backup || ((uintptr_t)backup % ALIGN) != 0 ||
       backup_bytes != lbm_ch_batch_state_bytes(b) || trial_steps < 1)
     return LBM_CH_EINVAL;

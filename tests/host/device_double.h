@@ -1,0 +1,19 @@
+// What a test can set and see of the CPU device in device_double.cpp.
+#pragma once
+
+#include <functional>
+#include <map>
+#include <string>
+#include <vector>
+
+namespace dbl {
+struct Step {
+  float tf;
+  int n;
+};
+extern int fail_in;                       // launches until one fails (-1: none does)
+extern std::map<std::string, int> count;  // launches of each kind
+extern std::vector<Step> steps;           // time factors in the order of the steps
+// microseconds of a launch of the given kind and shape, as events see it (none: 0)
+extern std::function<float(const std::string&, int)> cost;
+}  // namespace dbl

@@ -1,0 +1,172 @@
+// Checks of the launch sequences of the host side of the library on the CPU device of
+// device_double.cpp.  Run with the name of a check; exits non-zero if it fails.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <memory>
+
+#include "device_double.h"
+#include "lbm_ch.h"
+
+static int fails = 0;
+#define EXPECT(cond, ...)                                              \
+  do {                                                                 \
+    if (!(cond)) {                                                     \
+      fprintf(stderr, "%s:%d: expected %s: ", __FILE__, __LINE__, #cond); \
+      fprintf(stderr, __VA_ARGS__);                                    \
+      fprintf(stderr, "\n");                                           \
+      ++fails;                                                         \
+    }                                                                  \
+  } while (0)
+
+static lbm_ch_params params(int nx, int ny, double tau = 1.0) {
+  lbm_ch_params p;
+  memset(&p, 0, sizeof p);
+  p.nx = nx; p.ny = ny; p.model = 2; p.tau_g = tau; p.mobility = 0.01;
+  p.sigma = 0.01; p.width = 4.0; p.phi_a = 1.0; p.phi_b = -1.0;
+  p.rho_a = 1.0; p.rho_b = 1.0; p.tau_f = 0.8;
+  return p;
+}
+
+struct Lattice {
+  lbm_ch_params p;
+  void* ws;
+  lbm_ch_ctx* c = nullptr;
+  std::vector<float> phi;
+  std::vector<char> state;
+  explicit Lattice(const lbm_ch_params& q, const std::vector<double>& tf = {}) : p(q) {
+    const size_t n = lbm_ch_workspace_bytes(&p);
+    ws = aligned_alloc(256, n);
+    phi.resize((size_t)p.nx * p.ny);
+    lbm_ch_velocity v;
+    memset(&v, 0, sizeof v);
+    v.time_factor = tf.empty() ? nullptr : tf.data();
+    v.n_time_factor = (int64_t)tf.size();
+    EXPECT(lbm_ch_init(&c, &p, &v, ws, n, phi.data(), nullptr) == LBM_CH_OK, "init");
+    state.resize(lbm_ch_state_bytes(c));
+  }
+  Lattice(const Lattice&) = delete;
+  ~Lattice() {
+    lbm_ch_destroy(c);
+    free(ws);
+  }
+  // steps taken by the state as the read-out sees it (-1: refused)
+  double seen() {
+    return lbm_ch_moments(c, phi.data(), nullptr, nullptr, nullptr, nullptr, nullptr) == LBM_CH_OK
+               ? phi[0] : -1.0;
+  }
+  // and as its saved populations hold it
+  double saved() {
+    if (lbm_ch_save_state(c, state.data(), state.size(), nullptr) != LBM_CH_OK) return -1.0;
+    double v;
+    memcpy(&v, state.data(), sizeof v);
+    return v;
+  }
+};
+
+// Sums, populations and step counter of a usable context say the same, now and later.
+static void consistent(Lattice& l, const char* what) {
+  for (int n : {0, 3, 2, 1, 4}) {
+    EXPECT(lbm_ch_step(l.c, n, nullptr) == LBM_CH_OK, "%s", what);
+    const double at = (double)lbm_ch_step_count(l.c);
+    EXPECT(l.seen() == at && l.saved() == at, "%s: step %g, phi of %g, populations of %g", what,
+           at, l.seen(), l.saved());
+  }
+}
+
+// A launch that fails in the middle of a call either leaves state and step counter
+// consistent, or a context that refuses every call on its state until one is loaded.
+static void failed_launch() {
+  for (int walls : {0, 1})
+    for (double tau : {1.0, 0.8})
+      for (int nx : {64, 300, 700})
+        for (int graphs : {0, 1})
+          for (int record : {0, 1})
+            for (int n = 1; n <= 9; ++n)
+              for (int at = 0; at < 2 * n + 1; ++at) {
+                lbm_ch_params p = params(nx, 60, tau);
+                p.walls = walls;
+                Lattice l(p);
+                lbm_ch_set_graphs(l.c, graphs);
+                EXPECT(lbm_ch_step(l.c, 2, nullptr) == LBM_CH_OK, "step");
+                EXPECT(l.saved() == 2.0, "saved");
+                const std::vector<char> two = l.state;
+                std::vector<float> traj(record ? (size_t)n * nx * 60 : 0);
+                dbl::fail_in = at;
+                const int r = record ? lbm_ch_record(l.c, n, traj.data(), nullptr)
+                                     : lbm_ch_step(l.c, n, nullptr);
+                if (dbl::fail_in >= 0 || r == LBM_CH_OK) {  // fewer launches than that
+                  dbl::fail_in = -1;
+                  EXPECT(r == LBM_CH_OK && l.seen() == 2 + n, "no failure");
+                  continue;
+                }
+                char what[120];
+                snprintf(what, sizeof what, "walls %d tau %g nx %d graphs %d record %d: launch %d of %d steps",
+                         walls, tau, nx, graphs, record, at, n);
+                EXPECT(r == LBM_CH_EHIP, "%s", what);
+                if (l.seen() >= 0) {
+                  consistent(l, what);
+                  continue;
+                }
+                float us;
+                EXPECT(at > 0, "%s: nothing was overwritten", what);
+                EXPECT(lbm_ch_step(l.c, 1, nullptr) == LBM_CH_ESTATE, "%s", what);
+                EXPECT(lbm_ch_record(l.c, 0, nullptr, nullptr) == LBM_CH_ESTATE, "%s", what);
+                EXPECT(lbm_ch_check_finite(l.c, nullptr) == LBM_CH_ESTATE, "%s", what);
+                EXPECT(l.saved() == -1.0, "%s", what);
+                EXPECT(lbm_ch_autotune(l.c, l.state.data(), l.state.size(), 1, nullptr, &us) ==
+                           LBM_CH_ESTATE, "%s", what);
+                EXPECT(lbm_ch_load_state(l.c, two.data(), two.size(), 2, nullptr) == LBM_CH_OK, "%s", what);
+                consistent(l, what);
+              }
+}
+
+// The same for a batch, and for a load that fails between its copies and its sums.
+static void failed_batch_and_load() {
+  for (int n = 1; n <= 6; ++n)
+    for (int at = 0; at < 2 * n; ++at) {
+      Lattice a(params(64, 48)), b(params(80, 50, 0.9));
+      lbm_ch_ctx* cs[2] = {a.c, b.c};
+      const size_t nb = lbm_ch_batch_workspace_bytes(2);
+      void* ws = aligned_alloc(256, (nb + 255) / 256 * 256);
+      lbm_ch_batch* batch = nullptr;
+      EXPECT(lbm_ch_batch_create(&batch, cs, 2, ws, nb) == LBM_CH_OK, "create");
+      EXPECT(lbm_ch_batch_step(batch, 3, 0, nullptr) == LBM_CH_OK, "batch step");
+      EXPECT(a.saved() == 3.0 && b.saved() == 3.0, "batch");
+      dbl::fail_in = at;
+      EXPECT(lbm_ch_batch_step(batch, n, 0, nullptr) == LBM_CH_EHIP, "launch %d of %d", at, n);
+      for (Lattice* l : {&a, &b}) {
+        EXPECT((l->seen() < 0) == (at > 0), "launch %d of %d", at, n);
+        if (at == 0) continue;
+        EXPECT(lbm_ch_batch_step(batch, 1, 0, nullptr) == LBM_CH_ESTATE, "lost member");
+        EXPECT(lbm_ch_load_state(l->c, l->state.data(), l->state.size(), 3, nullptr) == LBM_CH_OK, "load");
+      }
+      EXPECT(lbm_ch_batch_step(batch, n, 0, nullptr) == LBM_CH_OK, "launch %d of %d", at, n);
+      EXPECT(a.saved() == 3 + n && b.saved() == 3 + n && a.seen() == 3 + n, "launch %d of %d", at, n);
+      lbm_ch_batch_destroy(batch);
+      free(ws);
+    }
+  for (int at = 0; at < 2; ++at) {
+    Lattice l(params(64, 48));
+    EXPECT(l.saved() == 0.0, "saved");
+    const std::vector<char> zero = l.state;
+    EXPECT(lbm_ch_step(l.c, 5, nullptr) == LBM_CH_OK, "step");
+    dbl::fail_in = at;
+    const int r = lbm_ch_load_state(l.c, zero.data(), zero.size(), 0, nullptr);
+    dbl::fail_in = -1;
+    if (r != LBM_CH_OK && l.seen() < 0)
+      EXPECT(lbm_ch_load_state(l.c, zero.data(), zero.size(), 0, nullptr) == LBM_CH_OK, "load");
+    consistent(l, "load");
+  }
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> checks = {{"failed_launch", failed_launch},
+                                                    {"failed_batch_and_load", failed_batch_and_load}};
+  const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
+  if (it == checks.end()) return 2;
+  it->second();
+  printf("%s: %d failed expectations\n", argv[1], fails);
+  return fails ? 1 : 0;
+}

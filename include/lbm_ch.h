@@ -74,6 +74,10 @@
  * the state is lost: calls that step or read it return LBM_CH_ESTATE until
  * lbm_ch_load_state; otherwise state and step counter are those of the last step that was
  * enqueued whole.  Calls on one context must not overlap in time from several host threads.
+ * Device work of one context on several streams is ordered by the caller, with two
+ * exceptions: lbm_ch_adjoint (below), and a read-out of the state (lbm_ch_moments of a
+ * prescribed flow, lbm_ch_diagnostics, lbm_ch_save_state), which one later single step may
+ * run beside.
  */
 #ifndef LBM_CH_H
 #define LBM_CH_H

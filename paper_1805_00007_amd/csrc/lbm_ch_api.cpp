@@ -386,11 +386,6 @@ static hipError_t phi_field(const lbm_ch_ctx* c, float* phi, hipStream_t stream)
                           c->p.ny, phi, stream);
 }
 
-// A float32 field of the workspace that holds no state.
-static float* scratch_field(const lbm_ch_ctx* c) {
-  return c->keep ? (float*)c->m[1 - c->cur] : c->phi;
-}
-
 extern "C" {
 
 size_t lbm_ch_workspace_bytes(const lbm_ch_params* p) {
@@ -818,10 +813,16 @@ int lbm_ch_moments(lbm_ch_ctx* c, float* phi, float* mu, float* ux, float* uy, f
   const int nx = c->p.nx, ny = c->p.ny;
   const size_t fb = (size_t)nx * ny * sizeof(float);
   const bool ns = c->p.velocity_mode == LBM_CH_VEL_NS;
-  float* ph = phi ? phi : scratch_field(c);
   hipError_t e = hipSuccess;
-  if (phi || mu || ns) e = phi_field(c, ph, stream);
-  if (e == hipSuccess && mu) e = launch_mu_field(walls, c->c, ph, nx, ny, mu, stream);
+  if (c->keep) {  // read-outs write no buffer that a step uses
+    if (phi) e = phi_field(c, phi, stream);
+    if (e == hipSuccess && mu)
+      e = launch_mu_field(walls, c->c, nullptr, c->m[c->cur], nx, ny, mu, stream);
+  } else {
+    float* ph = phi ? phi : c->phi;
+    if (phi || mu || ns) e = phi_field(c, ph, stream);
+    if (e == hipSuccess && mu) e = launch_mu_field(walls, c->c, ph, nullptr, nx, ny, mu, stream);
+  }
   if (e != hipSuccess) return hip_fail(e);
   if (ns) {
     if (ux || uy || p) {
@@ -853,10 +854,10 @@ int lbm_ch_diagnostics(lbm_ch_ctx* c, const float* phi_ref, double* out, hipStre
   if (!out || ((uintptr_t)out & 7u) != 0) return LBM_CH_EINVAL;
   if (phi_ref && !aligned4(phi_ref)) return LBM_CH_EINVAL;
   const bool walls = c->p.walls != 0;
-  float* phi = scratch_field(c);
-  hipError_t e = phi_field(c, phi, stream);
+  hipError_t e = c->keep ? hipSuccess : phi_field(c, c->phi, stream);
   if (e == hipSuccess)
-    e = launch_diag(walls, c->c, phi, phi_ref, c->p.nx, c->p.ny, c->part, out, stream);
+    e = launch_diag(walls, c->c, c->phi, c->keep ? c->m[c->cur] : nullptr, phi_ref, c->p.nx, c->p.ny,
+                    c->part, out, stream);
   return e == hipSuccess ? LBM_CH_OK : hip_fail(e);
 }
 

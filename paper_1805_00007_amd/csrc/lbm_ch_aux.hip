@@ -10,16 +10,16 @@ namespace {
 
 // ---------------------------------------------------------------------------------
 // Initial state: g = g^eq(phi0, mu[phi0], u(t0)); with NS f = f^eq(0, rho(phi0), u0).
-template <bool WALLS>
-__device__ __forceinline__ float field_at(const float* f, int nx, int ny, int x, int y) {
+template <bool WALLS, class T>
+__device__ __forceinline__ float field_at(const T* f, int nx, int ny, int x, int y) {
   x = x < 0 ? x + nx : (x >= nx ? x - nx : x);
   float sg;
   y = row_of<WALLS>(y, ny, sg);
-  return f[(uint32_t)y * nx + x];
+  return (float)f[(uint32_t)y * nx + x];
 }
 
-template <bool WALLS>
-__device__ __forceinline__ void stencil_at(const float* f, int nx, int ny, int x, int y,
+template <bool WALLS, class T>
+__device__ __forceinline__ void stencil_at(const T* f, int nx, int ny, int x, int y,
                                            float& gx, float& gy, float& lap) {
   float v[3][3];
 #pragma unroll
@@ -137,14 +137,15 @@ __global__ void __launch_bounds__(256) k_phi_of_sum(const double* __restrict__ m
   if (i < n) phi[i] = (float)m[i];
 }
 
-template <bool WALLS>
-__global__ void __launch_bounds__(256) k_mu_field(const Coef c, const float* __restrict__ phi,
+// T: float, or double where phi is read from the sum field of the state.
+template <bool WALLS, class T>
+__global__ void __launch_bounds__(256) k_mu_field(const Coef c, const T* __restrict__ phi,
                                                   int nx, int ny, float* __restrict__ mu) {
   const int x = blockIdx.x * 256 + threadIdx.x, y = blockIdx.y;
   if (x >= nx) return;
   float gx, gy, lap;
   stencil_at<WALLS>(phi, nx, ny, x, y, gx, gy, lap);
-  mu[(uint32_t)y * nx + x] = mu_bulk(c, phi[(uint32_t)y * nx + x]) - c.kappa * lap;
+  mu[(uint32_t)y * nx + x] = mu_bulk(c, (float)phi[(uint32_t)y * nx + x]) - c.kappa * lap;
 }
 
 __global__ void __launch_bounds__(256) k_velocity(int vmode, int nx, int ny, const float* ax,
@@ -227,9 +228,9 @@ __device__ __forceinline__ double block_reduce(double acc[NDIAG], double (*sh)[D
   return r;
 }
 
-template <bool WALLS>
+template <bool WALLS, class T>
 __global__ void __launch_bounds__(DIAG_THREADS) k_diag_partial(const Coef c,
-                                                               const float* __restrict__ phi,
+                                                               const T* __restrict__ phi,
                                                                const float* __restrict__ ref,
                                                                int nx, int ny,
                                                                double* __restrict__ part) {
@@ -238,7 +239,7 @@ __global__ void __launch_bounds__(DIAG_THREADS) k_diag_partial(const Coef c,
   const int64_t n = (int64_t)nx * ny;
   for (int64_t k = (int64_t)blockIdx.x * DIAG_THREADS + threadIdx.x; k < n;
        k += (int64_t)DIAG_BLOCKS * DIAG_THREADS) {
-    const float pf = phi[k];
+    const float pf = (float)phi[k];
     if (!isfinite(pf)) {
       acc[7] += 1.0;
       continue;
@@ -554,11 +555,13 @@ hipError_t launch_adjoint_step(const Coef& c, float mobility, int nx, int ny, in
   return hipGetLastError();
 }
 
-hipError_t launch_mu_field(bool walls, const Coef& c, const float* phi, int nx, int ny,
-                           float* mu, hipStream_t s) {
+hipError_t launch_mu_field(bool walls, const Coef& c, const float* phi, const double* m, int nx,
+                           int ny, float* mu, hipStream_t s) {
   const dim3 grid((nx + 255) / 256, ny);
-  if (walls) hipLaunchKernelGGL((k_mu_field<true>), grid, dim3(256), 0, s, c, phi, nx, ny, mu);
-  else hipLaunchKernelGGL((k_mu_field<false>), grid, dim3(256), 0, s, c, phi, nx, ny, mu);
+#define LBM_MU(W, T, F) hipLaunchKernelGGL((k_mu_field<W, T>), grid, dim3(256), 0, s, c, F, nx, ny, mu)
+  if (m) { if (walls) LBM_MU(true, double, m); else LBM_MU(false, double, m); }
+  else { if (walls) LBM_MU(true, float, phi); else LBM_MU(false, float, phi); }
+#undef LBM_MU
   return hipGetLastError();
 }
 
@@ -580,12 +583,14 @@ hipError_t launch_fill(float* dst, float value, int64_t n, hipStream_t s) {
 
 int diag_partial_blocks() { return DIAG_BLOCKS; }
 
-hipError_t launch_diag(bool walls, const Coef& c, const float* phi, const float* ref, int nx,
-                       int ny, double* partial, double* out, hipStream_t s) {
-  if (walls)
-    hipLaunchKernelGGL((k_diag_partial<true>), dim3(DIAG_BLOCKS), dim3(DIAG_THREADS), 0, s, c, phi, ref, nx, ny, partial);
-  else
-    hipLaunchKernelGGL((k_diag_partial<false>), dim3(DIAG_BLOCKS), dim3(DIAG_THREADS), 0, s, c, phi, ref, nx, ny, partial);
+hipError_t launch_diag(bool walls, const Coef& c, const float* phi, const double* m,
+                       const float* ref, int nx, int ny, double* partial, double* out,
+                       hipStream_t s) {
+#define LBM_DIAG(W, T, F) \
+  hipLaunchKernelGGL((k_diag_partial<W, T>), dim3(DIAG_BLOCKS), dim3(DIAG_THREADS), 0, s, c, F, ref, nx, ny, partial)
+  if (m) { if (walls) LBM_DIAG(true, double, m); else LBM_DIAG(false, double, m); }
+  else { if (walls) LBM_DIAG(true, float, phi); else LBM_DIAG(false, float, phi); }
+#undef LBM_DIAG
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(DIAG_THREADS), 0, s, partial, out);

@@ -149,8 +149,9 @@ hipError_t launch_phi_field(bool walls, int storage, const void* g, uint32_t pit
 hipError_t launch_sum_field(bool walls, int storage, const void* g, uint32_t pitch, int nx, int ny,
                             double* m, hipStream_t s);
 hipError_t launch_phi_of_sum(const double* m, int64_t nodes, float* phi, hipStream_t s);
-hipError_t launch_mu_field(bool walls, const Coef& c, const float* phi, int nx, int ny,
-                           float* mu, hipStream_t s);
+// mu of a phi field, or (m not null) of the phi that is the float32 value of m.
+hipError_t launch_mu_field(bool walls, const Coef& c, const float* phi, const double* m, int nx,
+                           int ny, float* mu, hipStream_t s);
 // One reverse step of the tau_g = 1 phi map (periodic); lam0 must not alias lam1.
 hipError_t launch_adjoint_step(const Coef& c, float mobility, int nx, int ny, int vmode,
                                 const float* ax, const float* ay, const float* bx,
@@ -168,9 +169,10 @@ hipError_t launch_fill(float* dst, float value, int64_t n, hipStream_t s);
 constexpr size_t ADJ_STATIC_MAX_NODES = size_t(1) << 20;
 hipError_t static_scratch_setup(int device);
 float* static_scratch(int device);
-// FP64 reductions of a phi field; partial needs diag_partial_blocks()*8 doubles.
+// FP64 reductions of a phi field (m as above); partial needs diag_partial_blocks()*8 doubles.
 int diag_partial_blocks();
-hipError_t launch_diag(bool walls, const Coef& c, const float* phi, const float* ref, int nx,
-                       int ny, double* partial, double* out, hipStream_t s);
+hipError_t launch_diag(bool walls, const Coef& c, const float* phi, const double* m,
+                       const float* ref, int nx, int ny, double* partial, double* out,
+                       hipStream_t s);
 
 }  // namespace lbmch

@@ -3,8 +3,8 @@
 // reduced to its first value.  A population buffer or sum field holds the number of steps
 // its state has taken, so that a state read from the wrong buffer, a step lost or made
 // twice, and sums that no longer belong to their populations show as wrong numbers.
-// Launches can be made to fail, and are counted by kind.  Captured launches run when their
-// graph is launched.
+// Launches can be made to fail or to wait (those on one side stream), and are counted by
+// kind.  Captured launches run when their graph is launched.
 #include "device_double.h"
 
 #include <stdlib.h>
@@ -24,7 +24,10 @@ static std::vector<std::function<void()>>* capturing = nullptr;
 std::function<float(const std::string&, int)> cost;  // us of a launch, for events
 static float clock_us = 0.0f;
 
-static hipError_t enqueue(const char* kind, int shape, std::function<void()> f) {
+hipStream_t side = nullptr;
+std::vector<std::function<void()>> waiting;
+
+static hipError_t enqueue(const char* kind, int shape, hipStream_t s, std::function<void()> f) {
   if (fail_in == 0) {
     fail_in = -1;
     return hipErrorLaunchFailure;
@@ -33,6 +36,7 @@ static hipError_t enqueue(const char* kind, int shape, std::function<void()> f) 
   count[kind] += 1;
   if (cost) clock_us += cost(kind, shape);
   if (capturing) capturing->push_back(f);
+  else if (side && s == side) waiting.push_back(f);
   else f();
   return hipSuccess;
 }
@@ -60,8 +64,8 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*) {
   a->type = hipMemoryTypeDevice;
   return hipSuccess;
 }
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
-  return enqueue("copy", 0, [=] { memmove(d, s, n); });
+hipError_t hipMemcpyAsync(void* d, const void* from, size_t n, hipMemcpyKind, hipStream_t s) {
+  return enqueue("copy", 0, s, [=] { memmove(d, from, n); });
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
@@ -81,8 +85,8 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*,
 }
 hipError_t hipGraphDestroy(hipGraph_t g) { delete (std::vector<std::function<void()>>*)g; return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t x) { delete (std::vector<std::function<void()>>*)x; return hipSuccess; }
-hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t) {
-  return enqueue("graph", 0, [=] { for (auto& f : *(std::vector<std::function<void()>>*)x) f(); });
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s) {
+  return enqueue("graph", 0, s, [=] { for (auto& f : *(std::vector<std::function<void()>>*)x) f(); });
 }
 hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)calloc(1, sizeof(float)); return hipSuccess; }
 hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
@@ -111,25 +115,25 @@ int rt_step_rows(int ty) { return ty >= 16 ? 16 : ty >= 8 ? 8 : ty >= 4 ? 4 : 2;
 hipError_t static_scratch_setup(int) { return hipSuccess; }
 float* static_scratch(int) { return nullptr; }
 
-static hipError_t population_step(const char* kind, int shape, StepArgs a) {
-  return enqueue(kind, shape, [=] {
+static hipError_t population_step(const char* kind, int shape, StepArgs a, hipStream_t s) {
+  return enqueue(kind, shape, s, [=] {
     if (a.phi_rec) *a.phi_rec = (float)get(a.src);
     dbl::steps.push_back({a.tf, 1});
     put(a.dst, get(a.src) + 1);
   });
 }
-hipError_t launch_phi_step(int tx, bool, int, int, int, const StepArgs& a, int, hipStream_t) {
-  return population_step("tile", tx * 1000 + a.ty, a);
+hipError_t launch_phi_step(int tx, bool, int, int, int, const StepArgs& a, int, hipStream_t s) {
+  return population_step("tile", tx * 1000 + a.ty, a, s);
 }
-hipError_t launch_phi_record(int tx, int, int, const StepArgs& a, int, hipStream_t) {
-  return population_step("record", tx * 1000 + a.ty, a);
+hipError_t launch_phi_record(int tx, int, int, const StepArgs& a, int, hipStream_t s) {
+  return population_step("record", tx * 1000 + a.ty, a, s);
 }
-hipError_t launch_pop_march(bool, int, int, int, const StepArgs& a, hipStream_t) {
-  return population_step("pop_march", a.mty, a);
+hipError_t launch_pop_march(bool, int, int, int, const StepArgs& a, hipStream_t s) {
+  return population_step("pop_march", a.mty, a, s);
 }
-hipError_t launch_phi_march(bool walls, int, int, int, bool to_g, const StepArgs& a, hipStream_t) {
+hipError_t launch_phi_march(bool walls, int, int, int, bool to_g, const StepArgs& a, hipStream_t s) {
   if (walls && a.phi_rec) return hipErrorInvalidValue;
-  return enqueue("march", a.mty, [=] {
+  return enqueue("march", a.mty, s, [=] {
     if (a.phi_rec) *a.phi_rec = (float)*a.msrc;
     dbl::steps.push_back({a.tf, 1});
     *a.mdst = *a.msrc + 1;
@@ -137,9 +141,9 @@ hipError_t launch_phi_march(bool walls, int, int, int, bool to_g, const StepArgs
   });
 }
 hipError_t launch_phi_block(int rows, int, int, int, bool to_g, const StepArgs& a,
-                            const BlockSteps& b, hipStream_t) {
+                            const BlockSteps& b, hipStream_t s) {
   if (b.steps < 1 || b.steps > BLOCK_STEPS) return hipErrorInvalidValue;
-  return enqueue("block", rows * 10 + b.steps, [=] {
+  return enqueue("block", rows * 10 + b.steps, s, [=] {
     for (int k = 0; k < b.steps; ++k) {
       if (a.phi_rec) a.phi_rec[(size_t)k * a.nx * a.ny] = (float)*a.msrc + k;
       dbl::steps.push_back({b.tf[k], 1});
@@ -148,8 +152,8 @@ hipError_t launch_phi_block(int rows, int, int, int, bool to_g, const StepArgs& 
     if (to_g) put(a.dst, *a.mdst);
   });
 }
-hipError_t launch_march_batch(int, bool, bool to_g, const BatchArgs& b, hipStream_t) {
-  return enqueue("march_batch", 0, [=] {
+hipError_t launch_march_batch(int, bool, bool to_g, const BatchArgs& b, hipStream_t s) {
+  return enqueue("march_batch", 0, s, [=] {
     for (int i = 0; i < b.n; ++i) {
       const StepArgs& a = b.args[i];
       const double* src = b.parity ? a.mdst : a.msrc;
@@ -159,8 +163,8 @@ hipError_t launch_march_batch(int, bool, bool to_g, const BatchArgs& b, hipStrea
     }
   });
 }
-hipError_t launch_phi_batch(int tx, int, bool, bool persistent, const BatchArgs& b, int, hipStream_t) {
-  return enqueue("tile_batch", tx * 10 + persistent, [=] {
+hipError_t launch_phi_batch(int tx, int, bool, bool persistent, const BatchArgs& b, int, hipStream_t s) {
+  return enqueue("tile_batch", tx * 10 + persistent, s, [=] {
     for (int i = 0; i < b.n; ++i) {
       const StepArgs& a = b.args[i];
       const void* src = b.parity ? a.dst : a.src;
@@ -173,20 +177,20 @@ hipError_t launch_rt_step(int, bool, int, int, const StepArgs&, const float*, fl
                           hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_init(bool, int, int, const Coef&, int, int, uint32_t, const float*, const float*,
                        const float*, const float*, const float*, const float*, const float*, float,
-                       void* g, float*, hipStream_t) {
-  return enqueue("init", 0, [=] { put(g, 0.0); });
+                       void* g, float*, hipStream_t s) {
+  return enqueue("init", 0, s, [=] { put(g, 0.0); });
 }
-hipError_t launch_phi_field(bool, int, const void* g, uint32_t, int, int, float* phi, hipStream_t) {
-  return enqueue("phi_field", 0, [=] { *phi = (float)get(g); });
+hipError_t launch_phi_field(bool, int, const void* g, uint32_t, int, int, float* phi, hipStream_t s) {
+  return enqueue("phi_field", 0, s, [=] { *phi = (float)get(g); });
 }
-hipError_t launch_sum_field(bool, int, const void* g, uint32_t, int, int, double* m, hipStream_t) {
-  return enqueue("sum_field", 0, [=] { *m = get(g); });
+hipError_t launch_sum_field(bool, int, const void* g, uint32_t, int, int, double* m, hipStream_t s) {
+  return enqueue("sum_field", 0, s, [=] { *m = get(g); });
 }
-hipError_t launch_phi_of_sum(const double* m, int64_t, float* phi, hipStream_t) {
-  return enqueue("phi_of_sum", 0, [=] { *phi = (float)*m; });
+hipError_t launch_phi_of_sum(const double* m, int64_t, float* phi, hipStream_t s) {
+  return enqueue("phi_of_sum", 0, s, [=] { *phi = (float)*m; });
 }
-hipError_t launch_mu_field(bool, const Coef&, const float* phi, int, int, float* mu, hipStream_t) {
-  return enqueue("mu", 0, [=] { *mu = *phi; });
+hipError_t launch_mu_field(bool, const Coef&, const float* phi, const double* m, int, int, float* mu, hipStream_t s) {
+  return enqueue("mu", 0, s, [=] { *mu = m ? (float)*m : *phi; });
 }
 hipError_t launch_adjoint_step(const Coef&, float, int, int, int, const float*, const float*,
                                const float*, const float*, const float*, const float*, float,
@@ -197,10 +201,10 @@ hipError_t launch_velocity_field(int, int, int, const float*, const float*, cons
                                  const float*, const float*, const float*, float, float*, float*,
                                  hipStream_t) { return hipErrorInvalidValue; }
 hipError_t launch_fill(float*, float, int64_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_diag(bool, const Coef&, const float* phi, const float*, int, int, double*,
-                       double* out, hipStream_t) {
-  return enqueue("diag", 0, [=] {
-    for (int i = 0; i < 8; ++i) out[i] = i == 7 ? 0.0 : *phi;
+hipError_t launch_diag(bool, const Coef&, const float* phi, const double* m, const float*, int, int, double*,
+                       double* out, hipStream_t s) {
+  return enqueue("diag", 0, s, [=] {
+    for (int i = 0; i < 8; ++i) out[i] = i == 7 ? 0.0 : m ? *m : *phi;
   });
 }
 

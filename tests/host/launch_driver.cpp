@@ -161,9 +161,42 @@ static void failed_batch_and_load() {
   }
 }
 
+// One step on one stream beside a read-out of the state before it on another, whatever the
+// order in which their launches meet: the read-out sees its state, and the step is whole.
+static void readout_beside_a_step() {
+  const hipStream_t other = (hipStream_t)&fails;
+  for (int walls : {0, 1})
+    for (double tau : {1.0, 0.8})
+      for (int what = 0; what < 3; ++what)
+        for (size_t before = 0; before < 3; ++before) {  // launches that run before the step
+          lbm_ch_params p = params(130, 60, tau);
+          p.walls = walls;
+          Lattice l(p);
+          EXPECT(lbm_ch_step(l.c, 3, nullptr) == LBM_CH_OK, "step");
+          std::vector<float> mu(130 * 60, -1.0f);
+          double d[8] = {-1.0};
+          dbl::side = other;
+          float* phi = what == 1 ? l.phi.data() : nullptr;
+          const int r = what == 2 ? lbm_ch_diagnostics(l.c, nullptr, d, other)
+                                  : lbm_ch_moments(l.c, phi, mu.data(), nullptr, nullptr, nullptr, other);
+          EXPECT(r == LBM_CH_OK, "read-out");
+          size_t k = 0;
+          for (; k < before && k < dbl::waiting.size(); ++k) dbl::waiting[k]();
+          EXPECT(lbm_ch_step(l.c, 1, nullptr) == LBM_CH_OK, "step");
+          for (; k < dbl::waiting.size(); ++k) dbl::waiting[k]();
+          dbl::waiting.clear();
+          dbl::side = nullptr;
+          const double got = what == 2 ? d[0] : mu[0];
+          EXPECT(got == 3.0, "walls %d tau %g read-out %d, %zu launches before: of step %g", walls, tau,
+                 what, before, got);
+          consistent(l, "after the read-out");
+        }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"failed_launch", failed_launch},
-                                                    {"failed_batch_and_load", failed_batch_and_load}};
+                                                    {"failed_batch_and_load", failed_batch_and_load},
+                                                    {"readout_beside_a_step", readout_beside_a_step}};
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
   it->second();

@@ -223,7 +223,8 @@ int lbm_ch_load_state(lbm_ch_ctx* ctx, const void* src, size_t bytes, int64_t st
  * 1 and 2 (LBM_CH_EINVAL elsewhere).  The default is chosen at init from the lattice size
  * and storage; it changes speed only, never results.  Lattices that keep their sum field
  * (lbm_ch_step) accept and report shapes, but step in launches of their own.  Some lattices
- * with a prescribed velocity at other tau_g also do so until a shape is set.
+ * with a prescribed velocity at other tau_g also do so while the default shape is set
+ * (recording and batched steps take the tiles there).
  *   On those: with float32 storage below 2048^2 nodes, tx = 0 with ty = 4 up to 65536
  *   nodes, else 16; with 16-bit storage at every size, ty = 4 up to 65536 nodes, 8 below
  *   2048^2, else 16.
@@ -261,9 +262,11 @@ int lbm_ch_set_graphs(lbm_ch_ctx* ctx, int32_t enable);
 
 /* Autotuner: time trial_steps >= 1 steps (after one untimed step) for each tile shape
  * tx in {64, 128, 256, 512} (skipping widths with more than half the lanes idle) and ty in
- * {1, 2, 4, 8, 16, 32} (one of them where the shape is without effect), keep the fastest,
- * and restore the state and step counter from
- * `backup`, a caller device buffer of exactly lbm_ch_state_bytes(ctx) bytes.
+ * {1, 2, 4, 8, 16, 32}, and for the launches of their own that some lattices have
+ * (lbm_ch_set_tiles), keep the fastest (of the latter: with the default shape set), and
+ * restore the state and step counter from
+ * `backup`, a caller device buffer of exactly lbm_ch_state_bytes(ctx) bytes.  Lattices that
+ * keep their sum field are timed once and keep the shape they have.
  * Synchronises `stream`.  *best_us (may be NULL) receives the chosen shape's time per
  * step in microseconds. */
 int lbm_ch_autotune(lbm_ch_ctx* ctx, void* backup, size_t backup_bytes, int32_t trial_steps,

@@ -112,7 +112,7 @@ struct lbm_ch_ctx {
   std::vector<double> tf;
   int tx, ty, nstrips, nblocks, xcd_remap;
   bool keep;  // m[cur] is kept beside g[cur] (keeps_sum)
-  bool pop;   // population steps run as marches (pop_march_ok; off once a tile shape is set)
+  bool pop;   // population steps run as marches (pop_march_ok; not while another tile shape than the default is set)
   bool lost;  // a launch failed after others of its call had overwritten the state
   int graphs;                     // lbm_ch_set_graphs: replay captured launch sequences
   hipStream_t cap;                // capture stream, created at the first capture
@@ -923,7 +923,9 @@ int lbm_ch_set_tiles(lbm_ch_ctx* c, int32_t tx, int32_t ty) {
     return LBM_CH_EINVAL;
   }
   apply_tiles(c, tx, ty);
-  c->pop = false;
+  int dx, dy;
+  default_tiles(c->p, dx, dy);
+  c->pop = pop_march_ok(c->p) && c->tx == dx && c->ty == std::min(dy, c->p.ny);
   return LBM_CH_OK;
 }
 
@@ -951,47 +953,62 @@ int lbm_ch_autotune(lbm_ch_ctx* c, void* backup, size_t backup_bytes, int32_t tr
     return LBM_CH_EINVAL;
   const int64_t step0 = c->step;
   const int tx0 = c->tx, ty0 = c->ty;
+  const bool pop0 = c->pop;
   int r = lbm_ch_save_state(c, backup, backup_bytes, stream);
   if (r != LBM_CH_OK) return r;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
-  float best = -1.0f;
+  // time of trial_steps steps as the context is set now (ms); false on an error
+  auto trial = [&](float& ms) {
+    r = run_steps(c, 1, nullptr, stream);  // untimed: first launch of this kernel shape
+    if (r == LBM_CH_OK) {
+      e = hipEventRecord(e0, stream);
+      if (e == hipSuccess) r = run_steps(c, trial_steps, nullptr, stream);
+      if (e == hipSuccess && r == LBM_CH_OK) e = hipEventRecord(e1, stream);
+      if (e == hipSuccess && r == LBM_CH_OK) e = hipEventSynchronize(e1);
+    }
+    if (e == hipSuccess && r == LBM_CH_OK) e = hipEventElapsedTime(&ms, e0, e1);
+    return e == hipSuccess && r == LBM_CH_OK;
+  };
+  float best = -1.0f, ms = 0.0f;
   int btx = tx0, bty = ty0;
+  bool bpop = pop0;
   const int nx = c->p.nx, ny = c->p.ny;
-  const bool pass = pass_eligible(c->p);
-  for (int xx : {0, 64, 128, 256, 512}) {
-    if (e != hipSuccess) break;
-    if ((c->keep || c->pop) && best >= 0.0f) break;  // launches of their own: one trial times them
-    if (xx == 0 && !pass) continue;
+  if (e == hipSuccess && c->keep) {  // no shape has an effect: one time, the shape stays
+    if (trial(ms)) best = ms;
+  }
+  c->pop = false;
+  for (int xx : {64, 128, 256, 512}) {
+    if (c->keep || e != hipSuccess || r != LBM_CH_OK) break;
     if (xx > 64 && xx / 2 >= nx) continue;  // more than half the lanes idle
     for (int yy : {1, 2, 4, 8, 16, 32}) {
-      if (xx == 0 && yy != 4 && yy != 8 && yy != 16) continue;
       if (yy > ny && yy > 2) continue;
       apply_tiles(c, xx, yy);
-      r = run_steps(c, 1, nullptr, stream);  // untimed: first launch of this kernel shape
-      if (r == LBM_CH_OK) {
-        e = hipEventRecord(e0, stream);
-        if (e == hipSuccess) r = run_steps(c, trial_steps, nullptr, stream);
-        if (e == hipSuccess && r == LBM_CH_OK) e = hipEventRecord(e1, stream);
-        if (e == hipSuccess && r == LBM_CH_OK) e = hipEventSynchronize(e1);
-      }
-      float ms = 0.0f;
-      if (e == hipSuccess && r == LBM_CH_OK) e = hipEventElapsedTime(&ms, e0, e1);
-      if (e != hipSuccess || r != LBM_CH_OK) break;
+      if (!trial(ms)) break;
       if (best < 0.0f || ms < best) {
         best = ms;
         btx = xx;
         bty = yy;
+        bpop = false;
       }
     }
-    if (r != LBM_CH_OK) break;
+  }
+  // the march against the fastest tile; with it the default shape, which set_tiles takes back
+  if (e == hipSuccess && r == LBM_CH_OK && pop_march_ok(c->p)) {
+    c->pop = true;
+    if (trial(ms) && ms <= best) {
+      best = ms;
+      default_tiles(c->p, btx, bty);
+      bpop = true;
+    }
   }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   // restore the state and the step counter whatever happened above
   const bool ok = e == hipSuccess && r == LBM_CH_OK;
   apply_tiles(c, ok ? btx : tx0, ok ? bty : ty0);
+  c->pop = ok ? bpop : pop0;
   const int r2 = lbm_ch_load_state(c, backup, backup_bytes, step0, stream);
   if (e != hipSuccess) return hip_fail(e);
   if (r != LBM_CH_OK) return r;

@@ -193,10 +193,73 @@ static void readout_beside_a_step() {
         }
 }
 
+static std::pair<int, int> tiles(const lbm_ch_ctx* c) {
+  int32_t tx = 0, ty = 0;
+  EXPECT(lbm_ch_get_tiles(c, &tx, &ty) == LBM_CH_OK, "get_tiles");
+  return {tx, ty};
+}
+static std::pair<int, int> default_tiles(const lbm_ch_params& p) {
+  int32_t tx = 0, ty = 0;
+  EXPECT(lbm_ch_default_tiles(&p, &tx, &ty) == LBM_CH_OK, "default_tiles");
+  return {tx, ty};
+}
+// kind of launch that one step is made of
+static std::string step_kind(Lattice& l) {
+  dbl::count.clear();
+  EXPECT(lbm_ch_step(l.c, 1, nullptr) == LBM_CH_OK, "step");
+  return dbl::count.size() == 1 ? dbl::count.begin()->first : "several";
+}
+
+// The autotuner sets what it has timed to be the fastest: the march or a tile where both
+// serve, and nothing where no shape has an effect.  Setting the shape it reports on another
+// context gives that context the same step, and the default shape the step of a new one.
+static void autotune() {
+  const std::pair<int, int> fast{128, 8};
+  for (double tau : {1.0, 0.8})
+    for (int walls : {0, 1})
+      for (int march_wins : {0, 1}) {
+        lbm_ch_params p = params(300, 200, tau);
+        p.walls = walls;
+        Lattice l(p);
+        const auto def = default_tiles(p);
+        EXPECT(def != fast, "the default is not the tile that the test makes the fastest");
+        if (tau == 1.0) EXPECT(lbm_ch_set_tiles(l.c, 256, 4) == LBM_CH_OK, "set_tiles");
+        EXPECT(lbm_ch_step(l.c, 3, nullptr) == LBM_CH_OK, "step");
+        // later launches are quicker, so that the last of equal ones would win
+        float drift = 0.0f;
+        dbl::cost = [&](const std::string& kind, int shape) {
+          drift -= 1e-4f;
+          if (kind == "pop_march") return (march_wins ? 4.0f : 9.0f) + drift;
+          return (kind == "tile" && shape == fast.first * 1000 + fast.second ? 6.0f : 12.0f) + drift;
+        };
+        float us = 0.0f;
+        dbl::count.clear();
+        EXPECT(lbm_ch_autotune(l.c, l.state.data(), l.state.size(), 4, nullptr, &us) == LBM_CH_OK, "autotune");
+        dbl::cost = nullptr;
+        EXPECT(lbm_ch_step_count(l.c) == 3 && l.seen() == 3.0, "restored");
+        const auto set = tiles(l.c);
+        if (tau == 1.0) {
+          EXPECT(set == std::make_pair(256, 4), "%d x %d", set.first, set.second);
+          EXPECT(dbl::count["march"] + dbl::count["block"] <= 1 + 4, "one trial");
+          continue;
+        }
+        EXPECT(set == (march_wins ? def : fast), "%d x %d", set.first, set.second);
+        EXPECT(us > (march_wins ? 3.9f : 5.9f) && us < (march_wins ? 4.1f : 6.1f), "%g us", us);
+        const std::string want = march_wins ? "pop_march" : "tile";
+        EXPECT(step_kind(l) == want, "%s", step_kind(l).c_str());
+        Lattice other(p);
+        EXPECT(lbm_ch_set_tiles(other.c, set.first, set.second) == LBM_CH_OK, "set_tiles");
+        EXPECT(step_kind(other) == want, "%s", step_kind(other).c_str());
+        EXPECT(lbm_ch_set_tiles(l.c, def.first, def.second) == LBM_CH_OK, "set_tiles");
+        EXPECT(step_kind(l) == "pop_march", "%s", step_kind(l).c_str());
+      }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"failed_launch", failed_launch},
                                                     {"failed_batch_and_load", failed_batch_and_load},
-                                                    {"readout_beside_a_step", readout_beside_a_step}};
+                                                    {"readout_beside_a_step", readout_beside_a_step},
+                                                    {"autotune", autotune}};
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
   it->second();

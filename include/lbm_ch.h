@@ -382,8 +382,8 @@ size_t lbm_ch_batch_state_bytes(const lbm_ch_batch* b);
 
 /* Autotuner: time trial_steps >= 1 batch steps (after one untimed step) for both
  * schedules, every tile policy tx in {0, 64, 128, 256} and ty in {4, 8, 16, 32}, keep the
- * fastest, and
- * restore every lattice's state and step counter from `backup` (device memory of
+ * fastest (a batch without tiles, every lattice at tau_g = 1, is timed once and keeps its
+ * settings), and restore every lattice's state and step counter from `backup` (device memory of
  * exactly lbm_ch_batch_state_bytes bytes, 256-byte aligned).  Synchronises `stream`.
  * *best_us (may be NULL): the chosen shape's time per batch step in microseconds. */
 int lbm_ch_batch_autotune(lbm_ch_batch* b, void* backup, size_t backup_bytes,

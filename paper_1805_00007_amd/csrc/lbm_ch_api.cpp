@@ -1137,22 +1137,15 @@ int lbm_ch_last_hip_error(void) { return g_last_hip; }
 // Batched stepping of many lattices.
 namespace {
 
+// Lattices that share a launch: those at tau_g = 1 march (a unit of work is a wave: a strip of
+// a chunk of rows), the others take tiles of one width (a unit is a tile).
 struct BatchGroup {
   int tx, vmode;
   bool model2;
-  bool t1;           // tau_g = 1 tile
+  bool t1;           // marches; tx and grid unused
   int first, count;  // range in the instance order
   int start_off;     // offset of this group's start[] in the device start array
-  int total, grid;
-};
-
-// Neighbouring groups that differ in tile width only: one launch of a march.
-struct MarchGroup {
-  int vmode;
-  bool model2;
-  int first, count;  // range in the instance order
-  int start_off;     // offset of this group's first waves in the device start array
-  int total;         // waves
+  int total, grid;   // units of work; workgroups
 };
 
 struct BatchExec {
@@ -1173,7 +1166,6 @@ struct lbm_ch_batch {
   std::vector<int> hstart;
   std::vector<int> built_cur;  // ctx->cur of each instance when the tables were built
   std::vector<BatchGroup> groups;
-  std::vector<MarchGroup> marches;  // the tau_g = 1 lattices, for calls of several steps
   int tx_policy;  // 0: per-instance width, else one width for all
   int ty;
   int persistent; // 1: a resident-size grid strides over the tiles; 0: a tile per workgroup
@@ -1188,8 +1180,8 @@ struct lbm_ch_batch {
 static bool batch_live(const lbm_ch_batch* b) { return b && b->magic == BATCH_MAGIC; }
 
 static size_t batch_table_bytes(int32_t n) {
-  // arguments; starts of the tile groups and of the marches (count + 1 entries per group)
-  return align_up((size_t)n * sizeof(StepArgs)) + align_up((size_t)(4 * n) * sizeof(int));
+  // arguments; starts of the groups (count + 1 entries each)
+  return align_up((size_t)n * sizeof(StepArgs)) + align_up((size_t)(2 * n + 1) * sizeof(int));
 }
 
 // Width of instance tiles: the policy's width, or (policy 0) the widest of 256, 128, 64
@@ -1226,7 +1218,8 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
   }
   auto key = [&](int i) {
     const lbm_ch_ctx* c = b->ctx[i];
-    return (c->vmode * 4 + (c->p.model == 2 ? 2 : 0) + (tau_one(c) ? 1 : 0)) * 1024 + txs[i];
+    const int variant = c->vmode * 4 + (c->p.model == 2 ? 2 : 0) + (tau_one(c) ? 1 : 0);
+    return variant * 1024 + (tau_one(c) ? 0 : txs[i]);
   };
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return key(x) < key(y); });
   b->hargs.assign(n, StepArgs{});
@@ -1237,25 +1230,22 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
     const int i = order[k];
     lbm_ch_ctx* c = b->ctx[i];
     if (b->groups.empty() || key(order[b->groups.back().first]) != key(i)) {
-      if (!b->groups.empty()) b->hstart.push_back(b->groups.back().total);
       BatchGroup g{};
       g.tx = txs[i];
       g.vmode = c->vmode;
       g.model2 = c->p.model == 2;
       g.t1 = tau_one(c);
       g.first = k;
-      g.start_off = (int)b->hstart.size();
       b->groups.push_back(g);
     }
     BatchGroup& g = b->groups.back();
-    const int ty = b->ty < c->p.ny ? b->ty : c->p.ny;
     StepArgs& a = b->hargs[k];
     a.src = c->g[c->cur];
     a.dst = c->g[1 - c->cur];
     a.pitch = c->L.pitch;
     a.nx = c->p.nx;
     a.ny = c->p.ny;
-    a.ty = ty;
+    a.ty = b->ty < c->p.ny ? b->ty : c->p.ny;
     a.nstrips = (c->p.nx + g.tx - 1) / g.tx;
     a.xcd_remap = 0;
     a.c = c->c;
@@ -1267,12 +1257,25 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
     a.mdst = c->m[1 - c->cur];
     a.mstrips = march_strips(c->p.nx);
     b->built_cur[i] = c->cur;
-    b->hstart.push_back(g.total);
-    g.total += a.nstrips * ((c->p.ny + ty - 1) / ty);
     g.count += 1;
   }
-  b->hstart.push_back(b->groups.back().total);
   for (BatchGroup& g : b->groups) {
+    if (g.t1) {
+      std::vector<MarchShape> shapes;
+      for (int k = g.first; k < g.first + g.count; ++k)
+        shapes.push_back(MarchShape{b->hargs[k].mstrips, b->hargs[k].ny});
+      const int ty = march_rows(shapes.data(), g.count);
+      for (int k = g.first; k < g.first + g.count; ++k) b->hargs[k].mty = ty;
+    }
+    g.start_off = (int)b->hstart.size();
+    for (int k = g.first; k < g.first + g.count; ++k) {
+      const StepArgs& a = b->hargs[k];
+      b->hstart.push_back(g.total);
+      g.total += g.t1 ? a.mstrips * ((a.ny + a.mty - 1) / a.mty)
+                      : a.nstrips * ((a.ny + a.ty - 1) / a.ty);
+    }
+    b->hstart.push_back(g.total);
+    if (g.t1) continue;
     const int want = (g.total + 7) / 8 * 8;
     if (b->persistent) {
       const int per_cu = phi_batch_blocks_per_cu(g.tx, g.vmode, g.model2);
@@ -1280,28 +1283,6 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
       g.grid = want < resident ? want : (resident > 8 ? resident : 8);
     } else {
       g.grid = want;
-    }
-  }
-  b->marches.clear();
-  for (const BatchGroup& g : b->groups) {
-    if (!g.t1) continue;
-    if (b->marches.empty() || b->marches.back().vmode != g.vmode ||
-        b->marches.back().model2 != g.model2 ||
-        b->marches.back().first + b->marches.back().count != g.first)
-      b->marches.push_back(MarchGroup{g.vmode, g.model2, g.first, 0, 0, 0});
-    b->marches.back().count += g.count;
-  }
-  for (MarchGroup& m : b->marches) {
-    std::vector<MarchShape> shapes;
-    for (int k = m.first; k < m.first + m.count; ++k)
-      shapes.push_back(MarchShape{b->hargs[k].mstrips, b->hargs[k].ny});
-    const int ty = march_rows(shapes.data(), m.count);
-    m.start_off = (int)b->hstart.size();
-    for (int k = m.first; k < m.first + m.count; ++k) {
-      StepArgs& a = b->hargs[k];
-      a.mty = ty;
-      b->hstart.push_back(m.total);
-      m.total += a.mstrips * ((a.ny + ty - 1) / ty);
     }
   }
   e = hipMemcpyAsync(b->dargs, b->hargs.data(), n * sizeof(StepArgs), hipMemcpyHostToDevice,
@@ -1334,28 +1315,18 @@ static hipError_t batch_enqueue(lbm_ch_batch* b, int64_t nsteps, int phase, hipS
                                 int64_t* launched) {
   *launched = 0;
   for (int64_t k = 0; k < nsteps; ++k) {
-    for (const MarchGroup& m : b->marches) {
-      BatchArgs a{};
-      a.args = b->dargs + m.first;
-      a.start = b->dstart + m.start_off;
-      a.n = m.count;
-      a.total = m.total;
-      // instance entries hold the buffers as of phase 0: step k goes from the buffers of
-      // phase + k to the others
-      a.parity = (int)((phase + k) & 1);
-      const hipError_t e = launch_march_batch(m.vmode, m.model2, k == nsteps - 1, a, s);
-      if (e != hipSuccess) return e;
-      *launched += 1;
-    }
     for (const BatchGroup& g : b->groups) {
-      if (g.t1) continue;
       BatchArgs a{};
       a.args = b->dargs + g.first;
       a.start = b->dstart + g.start_off;
       a.n = g.count;
       a.total = g.total;
+      // instance entries hold the buffers as of phase 0: step k goes from the buffers of
+      // phase + k to the others
       a.parity = (int)((phase + k) & 1);
-      hipError_t e = launch_phi_batch(g.tx, g.vmode, g.model2, b->persistent != 0, a, g.grid, s);
+      const hipError_t e =
+          g.t1 ? launch_march_batch(g.vmode, g.model2, k == nsteps - 1, a, s)
+               : launch_phi_batch(g.tx, g.vmode, g.model2, b->persistent != 0, a, g.grid, s);
       if (e != hipSuccess) return e;
       *launched += 1;
     }
@@ -1522,10 +1493,19 @@ int lbm_ch_batch_autotune(lbm_ch_batch* b, void* backup, size_t backup_bytes,
   int r = LBM_CH_OK;
   float best = -1.0f;
   int btx = tx0, bty = ty0, bpe = pe0;
+  // lattices that march have neither tiles nor a schedule: nothing to choose
+  bool tiled = false;
+  for (const lbm_ch_ctx* c : b->ctx) tiled = tiled || !tau_one(c);
   for (int pe : {0, 1})
   for (int xx : {0, 64, 128, 256}) {
     for (int yy : {4, 8, 16, 32}) {
       if (e != hipSuccess || r != LBM_CH_OK) break;
+      if (!tiled) {
+        if (best >= 0.0f) break;
+        pe = pe0;
+        xx = tx0;
+        yy = ty0;
+      }
       b->persistent = pe;
       b->tx_policy = xx;
       b->ty = yy;

@@ -255,11 +255,62 @@ static void autotune() {
       }
 }
 
+// The batch autotuner sets the fastest schedule and tile of the lattices that have them, and
+// nothing for a batch whose lattices all march; lattices of every kind step together.
+static void batch_autotune() {
+  for (int mixed : {0, 1}) {
+    std::vector<std::unique_ptr<Lattice>> ls;
+    std::vector<lbm_ch_ctx*> cs;
+    for (int i = 0; i < 7; ++i) {
+      lbm_ch_params p = params(40 + 70 * i, 50 + i, mixed && i % 2 ? 0.9 : 1.0);
+      p.model = 1 + (i / 2) % 2;
+      ls.push_back(std::make_unique<Lattice>(p));
+      cs.push_back(ls.back()->c);
+    }
+    const size_t nb = lbm_ch_batch_workspace_bytes(7);
+    void* ws = aligned_alloc(256, nb);
+    lbm_ch_batch* b = nullptr;
+    EXPECT(lbm_ch_batch_create(&b, cs.data(), 7, ws, nb) == LBM_CH_OK, "create");
+    EXPECT(lbm_ch_batch_set_tiles(b, 128, 8) == LBM_CH_OK, "set_tiles");
+    EXPECT(lbm_ch_batch_set_schedule(b, 1) == LBM_CH_OK, "set_schedule");
+    EXPECT(lbm_ch_batch_step(b, 3, 0, nullptr) == LBM_CH_OK, "step");
+    float drift = 0.0f;
+    dbl::cost = [&](const std::string& kind, int shape) {
+      drift -= 1e-4f;
+      return (kind == "tile_batch" && shape == 2560 ? 6.0f : 12.0f) + drift;
+    };
+    const size_t nst = lbm_ch_batch_state_bytes(b);
+    void* backup = aligned_alloc(256, nst);
+    float us = 0.0f;
+    dbl::count.clear();
+    EXPECT(lbm_ch_batch_autotune(b, backup, nst, 4, nullptr, &us) == LBM_CH_OK, "autotune");
+    dbl::cost = nullptr;
+    int32_t tx = 0, ty = 0;
+    EXPECT(lbm_ch_batch_get_tiles(b, &tx, &ty) == LBM_CH_OK, "get_tiles");
+    const int persistent = lbm_ch_batch_get_schedule(b);
+    if (mixed) {
+      EXPECT(tx == 256 && persistent == 0, "%d x %d, schedule %d", tx, ty, persistent);
+    } else {
+      EXPECT(tx == 128 && ty == 8 && persistent == 1, "%d x %d, schedule %d", tx, ty, persistent);
+      EXPECT(dbl::count["march_batch"] == 2 * (1 + 4), "%d launches", dbl::count["march_batch"]);
+      EXPECT(dbl::count["occupancy"] == 0, "a launch that has no tiles was sized for them");
+    }
+    for (int n : {1, 2, 5}) EXPECT(lbm_ch_batch_step(b, n, n == 2, nullptr) == LBM_CH_OK, "step");
+    for (auto& l : ls)
+      EXPECT(lbm_ch_step_count(l->c) == 11 && l->seen() == 11.0 && l->saved() == 11.0, "nx %d: %g, %g",
+             l->p.nx, l->seen(), l->saved());
+    lbm_ch_batch_destroy(b);
+    free(backup);
+    free(ws);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"failed_launch", failed_launch},
                                                     {"failed_batch_and_load", failed_batch_and_load},
                                                     {"readout_beside_a_step", readout_beside_a_step},
-                                                    {"autotune", autotune}};
+                                                    {"autotune", autotune},
+                                                    {"batch_autotune", batch_autotune}};
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
   it->second();

@@ -1,0 +1,147 @@
+"""Every launch that serves a prescribed flow against another one that serves the same call:
+tiles of every width and the register march at tau_g != 1, recording steps, the schedules
+and tiles of a batch, and the populations that the launches at tau_g = 1 store beside the
+sums that later calls read.  All bitwise."""
+import numpy as np
+import pytest
+
+import workloads
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _lattice(nx, ny, seed=0):
+    rng = np.random.default_rng(nx * 1000 + ny + seed)
+    phi0 = np.clip(0.3 + 0.2 * rng.normal(size=(ny, nx)), -1, 1)
+    tables = dict(ax=rng.uniform(-.04, .04, nx), ay=rng.uniform(-1, 1, ny),
+                  bx=rng.uniform(-.04, .04, nx), by=rng.uniform(-1, 1, ny))
+    field = (rng.uniform(-.04, .04, (ny, nx)), rng.uniform(-.04, .04, (ny, nx)))
+    return phi0, (dict(velocity=tables), dict(field=field))
+
+
+def _solver(nx, ny, phi0, vel, **phys):
+    import paper_1805_00007_amd as lbm
+    return lbm.Solver(nx, ny, phi0, **vel, **dict(workloads.PRESCRIBED, **phys))
+
+
+def _state(s):
+    """The saved state without the padding of its rows."""
+    buf, _ = s.save_state()
+    nx, ny, pitch = s.nx, s.ny, (s.nx + 31) // 32 * 32
+    if s.params.storage == 0:
+        n = ny * 36 * pitch
+        parts = [buf[:n].view(ny, 9, pitch, 4)[:, :, :nx]]
+    else:
+        n = ny * 20 * pitch
+        rows = buf[:n].view(ny, 20 * pitch)
+        parts = [rows[:, :4 * pitch].reshape(ny, pitch, 4)[:, :nx],
+                 rows[:, 4 * pitch:].reshape(ny, 8, pitch, 2)[:, :, :nx]]
+    return torch.cat([p.reshape(-1) for p in parts] + [buf[n:]])
+
+
+# 181 x 197 and 1100 x 37 take the march by default, 131 x 45 tiles; 1100 = 2 x 512 + 76
+@pytest.mark.parametrize("nx,ny", [(131, 45), (181, 197), (1100, 37)])
+@pytest.mark.parametrize("storage,model", [(0, 1), (0, 2), (0, 3), (1, 2), (2, 1)])
+def test_tile_shapes_at_other_tau(nx, ny, storage, model):
+    phi0, vels = _lattice(nx, ny)
+    for walls, vel, tau in ((0, vels[0], 0.8), (1, vels[0], 1.3), (0, vels[1], 1.3), (1, vels[1], 0.8)):
+        ref = None
+        for tiles in (None, (64, 1), (64, 5), (128, 16), (256, 3), (256, 32), (512, 8), (512, 1)):
+            s = _solver(nx, ny, phi0, vel, storage=storage, model=model, walls=walls, tau_g=tau)
+            if tiles:
+                s.set_tiles(*tiles)
+            got = _state(s.step(6))
+            s.close()
+            ref = got if ref is None else ref
+            assert torch.equal(got, ref), (walls, list(vel), tiles)
+
+
+@pytest.mark.parametrize("nx,ny", [(131, 45), (181, 197), (1100, 37)])
+@pytest.mark.parametrize("storage,model,walls", [(0, 1, 0), (0, 2, 0), (0, 3, 0), (0, 2, 1), (1, 2, 0)])
+def test_record_at_other_tau(nx, ny, storage, model, walls):
+    """Recorded steps leave the state of plain ones and the phi before each: the fused
+    recording tiles of periodic float32 lattices with models 1 and 2, and the others."""
+    phi0, vels = _lattice(nx, ny)
+    for vel in vels:
+        phys = dict(storage=storage, model=model, walls=walls, tau_g=0.8)
+        one = _solver(nx, ny, phi0, vel, **phys)
+        phis = []
+        for _ in range(7):
+            phis.append(one.phi())
+            one.step(1)
+        ref = _state(one)
+        one.close()
+        for tiles in (None, (64, 4), (128, 5), (256, 2), (512, 8)):
+            s = _solver(nx, ny, phi0, vel, **phys)
+            if tiles:
+                s.set_tiles(*tiles)
+            traj = torch.empty((7, ny, nx), dtype=torch.float32, device="cuda")
+            s.record(3, traj).record(4, traj[3:])
+            assert torch.equal(traj, torch.stack(phis)), (list(vel), tiles)
+            assert torch.equal(_state(s), ref), (list(vel), tiles)
+            s.close()
+
+
+@pytest.mark.parametrize("tiles,graph,persistent", [
+    ((0, 16), False, 0), ((0, 16), True, 1), ((64, 4), True, 0), ((64, 4), True, 1),
+    ((256, 32), False, 1), ((128, 1), True, 0), ((128, 5), False, 1)])
+def test_batch_at_other_tau(tiles, graph, persistent):
+    """Tiles and schedules of a batch at tau_g != 1 against single steps of each lattice
+    (tiles below 30000 nodes, the march above)."""
+    import paper_1805_00007_amd as lbm
+    sides = [(20, 9), (64, 64), (131, 45), (181, 197), (257, 130), (600, 51), (1100, 37)]
+    pairs = []
+    for i, (nx, ny) in enumerate(sides * 2):
+        phi0, vels = _lattice(nx, ny, i)
+        pairs.append([_solver(nx, ny, phi0, vels[i % 2], model=1 if i % 3 == 0 else 2,
+                              tau_g=1.0 if i == 5 else 0.8) for _ in range(2)])
+    b = lbm.Batch([p[0] for p in pairs]).set_tiles(*tiles).set_schedule(persistent)
+    for n in (3, 2):
+        b.step(n, graph=graph)
+    for got, one in pairs:
+        for _ in range(5):
+            one.step(1)
+        assert torch.equal(_state(got), _state(one)), (got.nx, got.ny)
+    b.close()
+    for p in pairs:
+        for s in p:
+            s.close()
+
+
+def _stored_populations_hold_the_state(s, n):
+    """After n steps: phi and a later step from the sums that the launches kept, and again
+    from the sums of the populations that they stored (a loaded state is summed anew)."""
+    s.step(n)
+    phi = s.phi()
+    saved = s.save_state()
+    after = s.step(1).phi()
+    s.load_state(*saved)
+    assert torch.equal(s.phi(), phi), (s.nx, s.ny, n)
+    assert torch.equal(s.step(1).phi(), after), (s.nx, s.ny, n)
+
+
+# small: regions, 16 and 32 rows; the others march
+@pytest.mark.parametrize("nx,ny", [(40, 23), (130, 90), (300, 260), (59, 1400), (701, 640)])
+@pytest.mark.parametrize("storage", [0, 1, 2])
+@pytest.mark.parametrize("walls", [0, 1])
+def test_stored_populations_at_tau_one(nx, ny, storage, walls):
+    phi0, vels = _lattice(nx, ny)
+    for model, vel in ((1, vels[0]), (2, vels[0]), (2, vels[1])):
+        s = _solver(nx, ny, phi0, vel, storage=storage, model=model, walls=walls)
+        for n in (1, 2, 5):
+            _stored_populations_hold_the_state(s, n)
+        s.close()
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+def test_stored_populations_at_the_largest_size(storage):
+    """Population offsets near 2^31 bytes, written and read."""
+    p = 80
+    phi0, vels = _lattice(p, p)
+    reps = (7760 // p, 7680 // p)
+    field = tuple(torch.tensor(f, dtype=torch.float32, device="cuda").repeat(reps) for f in vels[1]["field"])
+    s = _solver(7680, 7760, torch.tensor(phi0, dtype=torch.float32, device="cuda").repeat(reps),
+                dict(field=field), storage=storage)
+    _stored_populations_hold_the_state(s, 3)
+    s.close()

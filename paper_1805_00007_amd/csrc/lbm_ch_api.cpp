@@ -379,6 +379,18 @@ static hipError_t refresh_sum(lbm_ch_ctx* c, hipStream_t stream) {
                           c->p.ny, c->m[c->cur], stream);
 }
 
+// Whether a kernel of this context can read the state at src: memory of its device, at
+// 4-byte alignment (any other source is copied).
+static bool readable_state(const lbm_ch_ctx* c, const void* src) {
+  hipPointerAttribute_t at{};
+  if (!aligned4(src)) return false;
+  if (hipPointerGetAttributes(&at, src) != hipSuccess) {
+    (void)hipGetLastError();  // memory that HIP does not know: not an error of this call
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == c->device;
+}
+
 // phi of the current state.
 static hipError_t phi_field(const lbm_ch_ctx* c, float* phi, hipStream_t stream) {
   if (c->keep) return launch_phi_of_sum(c->m[c->cur], (int64_t)c->p.nx * c->p.ny, phi, stream);
@@ -901,7 +913,18 @@ int lbm_ch_load_state(lbm_ch_ctx* c, const void* src, size_t bytes, int64_t step
   __atomic_store_n(c->nf_host, 0, __ATOMIC_RELEASE);  // a new state: forget earlier NaNs
   const size_t g = c->L.g_state, f = c->L.f_state;
   const size_t fo = c->f[0] ? f : 0, x = (size_t)2 * c->p.nx * c->p.ny * sizeof(float);
-  hipError_t e = hipMemcpyAsync(c->g[c->cur], src, g, hipMemcpyDeviceToDevice, stream);
+  hipError_t e;
+  // Where the sums are kept, one launch copies and sums, instead of a copy and a second pass
+  // over the state.
+  if (c->keep && readable_state(c, src)) {
+    e = launch_load_sum(c->p.walls != 0, c->p.storage, src, c->L.pitch, c->p.nx, c->p.ny,
+                        c->g[c->cur], c->m[c->cur], stream);
+    if (e != hipSuccess) return hip_fail(e);
+    c->lost = false;
+    c->step = step;
+    return LBM_CH_OK;
+  }
+  e = hipMemcpyAsync(c->g[c->cur], src, g, hipMemcpyDeviceToDevice, stream);
   if (e != hipSuccess) return hip_fail(e);
   c->lost = true;  // until the whole state is enqueued
   if (c->f[0])

@@ -131,6 +131,45 @@ __global__ void __launch_bounds__(256) k_phi_field(const void* __restrict__ g, u
   phi[(uint32_t)y * nx + x] = (T)sum9d(p);
 }
 
+// A population state taken from src into dst, with its sum field: the state is read once from
+// memory (the neighbours' populations from the caches) and written once, so a load costs
+// little more than the copy alone.  One thread a column, padding included, whatever row its
+// neighbours in the wave are in, so that narrow lattices fill their waves; one band of rows
+// per XCD, so that the rows above and below a block's are in its L2 (2048^2 without: 49.8 us).
+// Us, copy alone / copy and a pass over it / this: 64^2 3.5 / 6.3 / 3.3, 512^2 3.4 / 9.3 / 4.1,
+// 1024^2 11.4 / 20 / 12.8, 2048^2 57 / 81 / 46.7 (80 B a node, 7.2 TB/s with the 256 MB cache), 4096^2
+// 228 / 357 / 230; half storage 2048^2 24.8 / 44 / 30.2.
+template <bool WALLS, int ST>
+__global__ void __launch_bounds__(256) k_load_sum(const void* __restrict__ src, uint32_t pitch,
+                                                  int nx, int ny, void* __restrict__ dst,
+                                                  double* __restrict__ m) {
+  const uint32_t t = ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * 256 + threadIdx.x;
+  const uint32_t y = t / pitch, x = t - y * pitch;
+  if (y >= (uint32_t)ny) return;
+  const rsrc_t s = make_rsrc(src, pop_bytes(ST, pitch, ny)), d = make_rsrc(dst, pop_bytes(ST, pitch, ny));
+  // non-temporal stores of whole waves' runs; of half waves' they cost (8 x 20000 8.4 / 12.2 us)
+  const bool nt = ST == ST_F32 && pitch >= 64;
+  uint32_t v[9];
+  float g[9];
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const uint32_t off = pop_off<ST>(i, pitch, y);
+    v[i] = ST == ST_F32 || i == 0 ? __builtin_amdgcn_raw_buffer_load_b32(s, x * 4u + off, 0, 0)
+                                  : __builtin_amdgcn_raw_buffer_load_b16(s, x * 2u + off, 0, 0);
+  }
+  if (x < (uint32_t)nx)
+    pull9_lanes<WALLS, ST>(s, pitch, ny, (int)y, x, x == 0 ? nx - 1 : x - 1,
+                           x == (uint32_t)nx - 1 ? 0 : x + 1, g);
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    const uint32_t off = pop_off<ST>(i, pitch, y);
+    if (nt) __builtin_amdgcn_raw_buffer_store_b32(v[i], d, x * 4u + off, 0, CP_NT);
+    else if (ST == ST_F32 || i == 0) __builtin_amdgcn_raw_buffer_store_b32(v[i], d, x * 4u + off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v[i], d, x * 2u + off, 0, 0);
+  }
+  if (x < (uint32_t)nx) m[y * (uint32_t)nx + x] = sum9d(g);
+}
+
 __global__ void __launch_bounds__(256) k_phi_of_sum(const double* __restrict__ m, int64_t n,
                                                     float* __restrict__ phi) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -534,6 +573,22 @@ hipError_t launch_phi_field(bool walls, int storage, const void* g, uint32_t pit
 hipError_t launch_sum_field(bool walls, int storage, const void* g, uint32_t pitch, int nx, int ny,
                             double* m, hipStream_t s) {
   return sum_field(walls, storage, g, pitch, nx, ny, m, s);
+}
+
+hipError_t launch_load_sum(bool walls, int storage, const void* src, uint32_t pitch, int nx, int ny,
+                           void* g, double* m, hipStream_t s) {
+  const dim3 grid(((pitch * (uint32_t)ny + 255) / 256 + 7) / 8 * 8);
+#define LBM_LOAD(ST)                                                                               \
+  if (walls) hipLaunchKernelGGL((k_load_sum<true, ST>), grid, dim3(256), 0, s, src, pitch, nx, ny, g, m); \
+  else hipLaunchKernelGGL((k_load_sum<false, ST>), grid, dim3(256), 0, s, src, pitch, nx, ny, g, m)
+  switch (storage) {
+    case ST_F32: LBM_LOAD(ST_F32); break;
+    case ST_F16: LBM_LOAD(ST_F16); break;
+    case ST_BF16: LBM_LOAD(ST_BF16); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef LBM_LOAD
+  return hipGetLastError();
 }
 
 hipError_t launch_phi_of_sum(const double* m, int64_t nodes, float* phi, hipStream_t s) {

@@ -148,6 +148,9 @@ hipError_t launch_phi_field(bool walls, int storage, const void* g, uint32_t pit
 // The sum field m of a population state, and phi from it.
 hipError_t launch_sum_field(bool walls, int storage, const void* g, uint32_t pitch, int nx, int ny,
                             double* m, hipStream_t s);
+// The population state at src (4-byte aligned device memory) copied to g, and its sum field.
+hipError_t launch_load_sum(bool walls, int storage, const void* src, uint32_t pitch, int nx, int ny,
+                           void* g, double* m, hipStream_t s);
 hipError_t launch_phi_of_sum(const double* m, int64_t nodes, float* phi, hipStream_t s);
 // mu of a phi field, or (m not null) of the phi that is the float32 value of m.
 hipError_t launch_mu_field(bool walls, const Coef& c, const float* phi, const double* m, int nx,

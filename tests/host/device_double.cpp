@@ -24,6 +24,7 @@ static std::vector<std::function<void()>>* capturing = nullptr;
 std::function<float(const std::string&, int)> cost;  // us of a launch, for events
 static float clock_us = 0.0f;
 
+int source_device = 0;
 hipStream_t side = nullptr;
 std::vector<std::function<void()>> waiting;
 
@@ -62,7 +63,9 @@ hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void*) {
   memset(a, 0, sizeof *a);
   a->type = hipMemoryTypeDevice;
-  return hipSuccess;
+  a->device = dbl::source_device;
+  if (dbl::source_device < 0) a->type = hipMemoryTypeHost;
+  return dbl::source_device < -1 ? hipErrorInvalidValue : hipSuccess;
 }
 hipError_t hipMemcpyAsync(void* d, const void* from, size_t n, hipMemcpyKind, hipStream_t s) {
   return enqueue("copy", 0, s, [=] { memmove(d, from, n); });
@@ -185,6 +188,13 @@ hipError_t launch_phi_field(bool, int, const void* g, uint32_t, int, int, float*
 }
 hipError_t launch_sum_field(bool, int, const void* g, uint32_t, int, int, double* m, hipStream_t s) {
   return enqueue("sum_field", 0, s, [=] { *m = get(g); });
+}
+hipError_t launch_load_sum(bool, int, const void* src, uint32_t, int, int, void* g, double* m,
+                           hipStream_t s) {
+  return enqueue("load_sum", 0, s, [=] {
+    put(g, get(src));
+    *m = get(src);
+  });
 }
 hipError_t launch_phi_of_sum(const double* m, int64_t, float* phi, hipStream_t s) {
   return enqueue("phi_of_sum", 0, s, [=] { *phi = (float)*m; });

@@ -15,6 +15,7 @@ struct Step {
 };
 extern int fail_in;                       // launches until one fails (-1: none does)
 extern std::map<std::string, int> count;  // launches of each kind
+extern int source_device;                 // device of memory that is asked for (-1: host, -2: unknown)
 extern hipStream_t side;                  // launches on this stream (not null) wait in
 extern std::vector<std::function<void()>> waiting;  // `waiting` for the test to run them
 extern std::vector<Step> steps;           // time factors in the order of the steps

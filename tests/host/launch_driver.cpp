@@ -305,12 +305,36 @@ static void batch_autotune() {
   }
 }
 
+// A state is loaded by one kernel from this device's memory at 4-byte alignment where the sums
+// are kept, and by a copy (and, with sums, a pass over it) from everywhere else.
+static void load_routes() {
+  for (double tau : {1.0, 0.8})
+    for (int dev : {0, 1, -1, -2})
+      for (int off : {0, 1, 2, 4}) {
+        Lattice l(params(64, 48, tau));
+        EXPECT(lbm_ch_step(l.c, 3, nullptr) == LBM_CH_OK && l.saved() == 3.0, "saved");
+        std::vector<char> buf(l.state.size() + 8);
+        memcpy(buf.data() + off, l.state.data(), l.state.size());
+        EXPECT(lbm_ch_step(l.c, 2, nullptr) == LBM_CH_OK, "step");
+        dbl::source_device = dev;
+        dbl::count.clear();
+        EXPECT(lbm_ch_load_state(l.c, buf.data() + off, l.state.size(), 3, nullptr) == LBM_CH_OK, "load");
+        dbl::source_device = 0;
+        const bool kernel = tau == 1.0 && dev == 0 && off % 4 == 0;
+        EXPECT(dbl::count["load_sum"] == kernel && dbl::count["copy"] == !kernel &&
+                   dbl::count["sum_field"] == (tau == 1.0 && !kernel), "device %d offset %d", dev, off);
+        EXPECT(l.seen() == 3.0, "loaded");
+        consistent(l, "loaded");
+      }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"failed_launch", failed_launch},
                                                     {"failed_batch_and_load", failed_batch_and_load},
                                                     {"readout_beside_a_step", readout_beside_a_step},
                                                     {"autotune", autotune},
-                                                    {"batch_autotune", batch_autotune}};
+                                                    {"batch_autotune", batch_autotune},
+                                                    {"load_routes", load_routes}};
   const auto it = argc > 1 ? checks.find(argv[1]) : checks.end();
   if (it == checks.end()) return 2;
   it->second();

@@ -145,3 +145,34 @@ def test_stored_populations_at_the_largest_size(storage):
                 dict(field=field), storage=storage)
     _stored_populations_hold_the_state(s, 3)
     s.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(4, 5), (5, 4), (31, 9), (32, 8), (33, 40), (250, 7), (257, 129), (8, 600)])
+@pytest.mark.parametrize("storage", [0, 1, 2])
+def test_loaded_state_is_the_saved_one(nx, ny, storage):
+    """A state loaded by the kernel that copies and sums, and from an odd address (a copy and
+    a pass over it): every byte of the populations, padding included, and bitwise the phi
+    and the steps of the state that was saved."""
+    phi0, vels = _lattice(nx, ny)
+    for walls in (0, 1):
+        s = _solver(nx, ny, phi0, vels[0], storage=storage, walls=walls)
+        buf, n = s.step(3).save_state()
+        pad = torch.randint(0, 256, buf.shape, dtype=torch.uint8, device="cuda")
+        body = torch.zeros_like(buf, dtype=torch.bool)
+        pitch = (nx + 31) // 32 * 32
+        if storage == 0:
+            body.view(ny, 9, pitch, 4)[:, :, :nx] = True
+        else:
+            body.view(ny, 20 * pitch)[:, :4 * nx] = True
+            body.view(ny, 20 * pitch)[:, 4 * pitch:].view(ny, 8, pitch, 2)[:, :, :nx] = True
+        buf = torch.where(body, buf, pad)
+        phi = s.phi()
+        after = s.step(4).phi()
+        odd = torch.empty(buf.numel() + 1, dtype=torch.uint8, device="cuda")[1:]
+        odd.copy_(buf)
+        for src in (buf, odd):
+            s.load_state(src, n)
+            assert torch.equal(s.save_state()[0], buf), walls
+            assert torch.equal(s.phi(), phi), walls
+            assert torch.equal(s.step(4).phi(), after), walls
+        s.close()

@@ -30,7 +30,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["failed_launch", "failed_batch_and_load", "readout_beside_a_step",
-                                   "autotune", "batch_autotune"])
+                                   "autotune", "batch_autotune", "load_routes"])
 def test_launches(driver, check):
     r = subprocess.run([driver, check], capture_output=True, text=True, timeout=300)
     print(r.stdout, r.stderr[-4000:])

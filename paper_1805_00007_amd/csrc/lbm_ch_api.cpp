@@ -318,6 +318,27 @@ static int march_rows(int nx, int ny) {
   return march_rows(&m, 1);
 }
 
+// The march that writes the populations too (the last launch of a call) is bound by memory
+// once populations and sums are more than the 256 MB cache behind L2, and then wants more and
+// shorter waves.  Us of a call of one step, population step before / march_rows / this:
+// float32 2560^2 104 / 115 / 106 with 8 rows; 4500^2 283 / 330 / 292; 7000^2 666 / 798 / 678; half
+// storage 4500^2 236 / 231 / 214.  Float32 with non-temporal stores (launch_phi_march) and 10
+// rows: 2048^2 40 (65 / 44 / 41), 2560^2 58, 4096^2 146 (216 / 273 / 252), while the two sum
+// fields fit that cache; beyond it 4500^2 293, and 1800^2 33.5 (34 / 32.5), 1280^2 20 (18 / 18).
+struct WriteMarch {
+  int rows, nt;
+};
+static WriteMarch write_march(const lbm_ch_params& p, bool rec) {
+  const int64_t nodes = (int64_t)p.nx * p.ny, cache = 256 << 20;
+  const bool f32 = p.storage == LBM_CH_STORE_F32;
+  if (f32 && nodes >= (4 << 20) && 16 * nodes <= cache) {
+    const int beside = (p.velocity_mode == LBM_CH_VEL_FIELD ? 8 : 0) + (rec ? 4 : 0);
+    return WriteMarch{10, (16 + beside) * nodes > cache ? 2 : 1};
+  }
+  if (nodes * (16 + (f32 ? 36 : 20)) > cache) return WriteMarch{8, 0};
+  return WriteMarch{march_rows(p.nx, p.ny), 0};
+}
+
 // Whether a context keeps the sum field m of its state beside the populations and steps in
 // the order-parameter form (lbm_ch_march.hip).  m[cur] then belongs to g[cur] at every
 // return.
@@ -562,10 +583,7 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
   // launches: as few as the plan allows, but two where one would read and write m[to]
   int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
   if (launches == 1 && to == c->cur) launches = 2;
-  if (plan.rows == 0) {
-    a.mty = march_rows(c->p.nx, c->p.ny);
-    a.mstrips = march_strips(c->p.nx);
-  }
+  const WriteMarch wm = write_march(c->p, phi_out != nullptr);
   a.dst = c->g[to];
   // the sums go from buffer to buffer through m[1 - to] and the population buffer that is
   // not the target, whose populations no launch reads, and end in m[to]
@@ -593,8 +611,11 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
         e = launch_phi_of_sum(a.msrc, (int64_t)nodes, a.phi_rec, stream);
         a.phi_rec = nullptr;
       }
+      const int nt = last ? wm.nt : 0;
+      a.mty = last ? wm.rows : march_rows(c->p.nx, c->p.ny);
+      a.mstrips = march_strips(c->p.nx, nt ? MARCH_OUT_NT : MARCH_OUT);
       if (e == hipSuccess)
-        e = launch_phi_march(c->p.walls != 0, c->vmode, c->p.model, c->p.storage, last, a, stream);
+        e = launch_phi_march(c->p.walls != 0, c->vmode, c->p.model, c->p.storage, last, nt, a, stream);
     } else {
       BlockSteps b{};
       b.steps = (int)k;

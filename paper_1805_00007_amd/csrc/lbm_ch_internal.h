@@ -98,11 +98,13 @@ hipError_t launch_phi_record(int tx, int vmode, int model, const StepArgs& a, in
 // prescribed velocity, models 1 and 2, any storage (march_ok).  From
 // a.msrc to a.mdst; to_g: the populations of the new state too, to a.dst.  a.phi_rec (may be
 // null, and is with walls) receives phi of the source state.  a.mty rows per wave, a.mstrips =
-// march_strips(nx).
+// march_strips(nx).  nt (to_g, float32 storage): strips of MARCH_OUT_NT columns and
+// non-temporal stores of the populations (1), and stored velocities and phi_rec too (2).
 constexpr int MARCH_OUT = 58;  // columns of a strip
-constexpr int march_strips(int nx) { return (nx + MARCH_OUT - 1) / MARCH_OUT; }
+constexpr int MARCH_OUT_NT = 48;
+constexpr int march_strips(int nx, int out = MARCH_OUT) { return (nx + out - 1) / out; }
 bool march_ok(int vmode, int model, bool t1);
-hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g,
+hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g, int nt,
                             const StepArgs& a, hipStream_t s);
 // Population step of any tau_g as a march in registers (lbm_ch_pop.hip): prescribed
 // velocity, every model and storage (model 3: float32).  a.mty rows per wave, a.mstrips =

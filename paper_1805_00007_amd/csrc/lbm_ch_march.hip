@@ -51,12 +51,21 @@ __device__ __forceinline__ void stb64(rsrc_t r, double v, uint32_t voff, uint32_
 // parts of lines that the neighbouring strip completes in L2.  A row holds no branch: phi
 // that is NaN or Inf is reported after the march (a test in every row cost 2-3 % at 2048^2,
 // 10 % of a batch).
-template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
+//
+// NT = 1 (writing float32 populations of lattices beyond the caches): strips of 48 columns,
+// whose rows start and end at multiples of 64 bytes, and non-temporal stores.  Streamed past
+// the caches in whole requests the populations leave the 256 MB cache to the sums: a call of
+// one step at 2560^2 took 115 us, now 58; 4096^2 273 -> 146 (HBM 604 MB, 4.1 TB/s).  58 columns
+// non-temporal 105 and 271 (parts of requests), 48 without 113 and 265.  NT = 2: stored
+// velocities and recorded phi pass the caches too, where with them the sums would not fit
+// (4096^2 stored velocity 277 -> 245, recorded 273 -> 179; where they fit it costs: 2500 x 2700
+// 85 -> 114 and 66 -> 78).
+template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC, int NT = 0>
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
   constexpr int M = 3;
-  constexpr int OUT = MARCH_OUT;
-  static_assert(OUT == 64 - 2 * M, "a strip and its margins are one wave");
+  constexpr int OUT = NT ? MARCH_OUT_NT : MARCH_OUT;
+  static_assert(OUT <= 64 - 2 * M, "a strip and its margins are one wave");
   const Coef& c = a.c;
   const int nx = a.nx, ny = a.ny;
   const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
@@ -109,8 +118,11 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     }
     I.m = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)row * 2u * rb);
     if (VFIELD) {
-      I.a = ldb(ru, (uint32_t)x * 4u, (uint32_t)row * rb);
-      I.b = ldb(rv, (uint32_t)x * 4u, (uint32_t)row * rb);
+      auto ld = [&](rsrc_t r) {
+        return NT == 2 ? ldb_nt(r, (uint32_t)x * 4u, (uint32_t)row * rb) : ldb(r, (uint32_t)x * 4u, (uint32_t)row * rb);
+      };
+      I.a = ld(ru);
+      I.b = ld(rv);
     } else {
       I.a = ld_uniform(a.ay, row);
       I.b = ld_uniform(a.by, row);
@@ -175,7 +187,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     uint32_t h[9];
     if (TO_G && (stage == 3 || K == K0 - 1)) {
       const bool in = stage < 3 || i + 1 < rows;
-      finish_store<ST, false>(rgd, pitch, in ? cst : OOB, (uint32_t)(in ? y0 + i + 1 : y0), m[j2], g);
+      finish_store<ST, NT != 0>(rgd, pitch, in ? cst : OOB, (uint32_t)(in ? y0 + i + 1 : y0), m[j2], g);
     } else {
       stored_values<ST>(m[j2], g, h);
     }
@@ -199,7 +211,8 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
     sw = (double)g[5];
     se = (double)g[6];
     if (stage < 3) return;
-    if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)(y0 + i) * rb);
+    if (REC && NT == 2) stb_nt(rrec, phi_out, cst * 4u, (uint32_t)(y0 + i) * rb);
+    else if (REC) stb(rrec, phi_out, cst * 4u, (uint32_t)(y0 + i) * rb);
     stb64(rdst, oc + (west(ow) + east(oe)), cst * 8u, (uint32_t)(y0 + i) * 2u * rb);
   };
 
@@ -225,14 +238,14 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
 
 constexpr int MARCH_WAVES = 4;  // waves per workgroup (independent of each other)
 
-template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC>
+template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC, int NT>
 __global__ void __launch_bounds__(64 * MARCH_WAVES) k_phi_march(const StepArgs a, const int total) {
   // workgroup w runs on XCD w % 8: give each XCD a band of neighbouring strips and chunks
   const int per = gridDim.x >> 3;
   const int w = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   const int L = w * MARCH_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (L >= total) return;
-  march_tile<WALLS, VMODE, MODEL2, ST, TO_G, REC>(a, L);
+  march_tile<WALLS, VMODE, MODEL2, ST, TO_G, REC, NT>(a, L);
 }
 
 // The marches of many lattices in one launch: wave L belongs to the instance whose range of
@@ -418,14 +431,14 @@ __global__ void __launch_bounds__(1024) k_phi_block(const StepArgs a, const Bloc
 // Workgroups for `total` waves, a multiple of 8 (one band per XCD).
 int march_grid(int total) { return ((total + MARCH_WAVES - 1) / MARCH_WAVES + 7) / 8 * 8; }
 
-template <int ST, bool TO_G>
+template <int ST, bool TO_G, int NT>
 hipError_t march_f(bool walls, int vmode, bool model2, const StepArgs& a, hipStream_t s) {
   const int total = a.mstrips * ((a.ny + a.mty - 1) / a.mty);
   const dim3 grid(march_grid(total)), block(64 * MARCH_WAVES);
   const bool rec = a.phi_rec != nullptr;
   if (walls && rec) return hipErrorInvalidValue;
 #define LBM_MARCH(W, V, M2, R) \
-  hipLaunchKernelGGL((k_phi_march<W, V, M2, ST, TO_G, R>), grid, block, 0, s, a, total)
+  hipLaunchKernelGGL((k_phi_march<W, V, M2, ST, TO_G, R, NT>), grid, block, 0, s, a, total)
 #define LBM_MARCH_FORM(V, M2)                         \
   if (walls) LBM_MARCH(true, V, M2, false);           \
   else if (rec) LBM_MARCH(false, V, M2, true);        \
@@ -467,8 +480,8 @@ hipError_t block_t(int vmode, bool model2, bool to_g, const StepArgs& a, const B
 
 template <int ST>
 hipError_t march_t(bool walls, int vmode, bool model2, bool to_g, const StepArgs& a, hipStream_t s) {
-  return to_g ? march_f<ST, true>(walls, vmode, model2, a, s)
-              : march_f<ST, false>(walls, vmode, model2, a, s);
+  return to_g ? march_f<ST, true, 0>(walls, vmode, model2, a, s)
+              : march_f<ST, false, 0>(walls, vmode, model2, a, s);
 }
 
 }  // namespace
@@ -477,10 +490,16 @@ bool march_ok(int vmode, int model, bool t1) {
   return t1 && (vmode == VEL_SEP || vmode == VEL_FIELD) && (model == 1 || model == 2);
 }
 
-hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g,
+hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g, int nt,
                             const StepArgs& a, hipStream_t s) {
-  if (!march_ok(vmode, model, true) || a.mty < 1 || a.mstrips != march_strips(a.nx))
+  if (!march_ok(vmode, model, true) || a.mty < 1 ||
+      a.mstrips != march_strips(a.nx, nt ? MARCH_OUT_NT : MARCH_OUT))
     return hipErrorInvalidValue;
+  if (nt) {
+    if (!to_g || storage != ST_F32) return hipErrorInvalidValue;
+    return nt == 2 ? march_f<ST_F32, true, 2>(walls, vmode, model == 2, a, s)
+                   : march_f<ST_F32, true, 1>(walls, vmode, model == 2, a, s);
+  }
   switch (storage) {
     case ST_F32: return march_t<ST_F32>(walls, vmode, model == 2, to_g, a, s);
     case ST_F16: return march_t<ST_F16>(walls, vmode, model == 2, to_g, a, s);

@@ -134,9 +134,12 @@ hipError_t launch_phi_record(int tx, int, int, const StepArgs& a, int, hipStream
 hipError_t launch_pop_march(bool, int, int, int, const StepArgs& a, hipStream_t s) {
   return population_step("pop_march", a.mty, a, s);
 }
-hipError_t launch_phi_march(bool walls, int, int, int, bool to_g, const StepArgs& a, hipStream_t s) {
-  if (walls && a.phi_rec) return hipErrorInvalidValue;
-  return enqueue("march", a.mty, s, [=] {
+hipError_t launch_phi_march(bool walls, int, int, int storage, bool to_g, int nt,
+                            const StepArgs& a, hipStream_t s) {
+  if ((walls && a.phi_rec) || (nt && (!to_g || storage != 0)) ||
+      a.mstrips != march_strips(a.nx, nt ? MARCH_OUT_NT : MARCH_OUT))
+    return hipErrorInvalidValue;
+  return enqueue(nt ? "march_nt" : "march", a.mty, s, [=] {
     if (a.phi_rec) *a.phi_rec = (float)*a.msrc;
     dbl::steps.push_back({a.tf, 1});
     *a.mdst = *a.msrc + 1;

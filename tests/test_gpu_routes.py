@@ -176,3 +176,27 @@ def test_loaded_state_is_the_saved_one(nx, ny, storage):
             assert torch.equal(s.phi(), phi), walls
             assert torch.equal(s.step(4).phi(), after), walls
         s.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(2048, 2048), (2111, 1999), (48 * 44, 2003), (4096, 4096), (4200, 4100)])
+@pytest.mark.parametrize("walls", [0, 1])
+def test_writing_march_of_large_lattices(nx, ny, walls):
+    """Float32 lattices whose last march of a call stores the populations past the caches, in
+    strips of 48 columns (up to 2^24 nodes), and one size beyond: the state stored, the phi
+    recorded, and the sums kept are those of launches in 58-column strips (the same steps as
+    the first of a longer call) and of the populations."""
+    phi0, vels = _lattice(nx, ny)
+    for model, vel in ((2, vels[0]), (1, vels[1])):
+        s = _solver(nx, ny, phi0, vel, model=model, walls=walls)
+        _stored_populations_hold_the_state(s, 1)
+        saved = s.save_state()
+        traj = torch.empty((3, ny, nx), dtype=torch.float32, device="cuda")
+        s.record(3, traj)  # 58-column strips for the first two
+        end = s.phi()
+        s.load_state(*saved)
+        for k in range(3):
+            one = torch.empty((1, ny, nx), dtype=torch.float32, device="cuda")
+            s.record(1, one)
+            assert torch.equal(one[0], traj[k]), (model, k)
+        assert torch.equal(s.phi(), end), model
+        s.close()

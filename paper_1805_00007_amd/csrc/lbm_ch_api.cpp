@@ -288,20 +288,22 @@ static void default_tiles(const lbm_ch_params& p, int& tx_out, int& ty_out) {
   ty_out = ty;
 }
 
-// Rows per wave of a march between population and order-parameter form (launch_phi_march:
-// strips of 58 columns, four waves to a workgroup, so one on each SIMD of a CU).  A wave
+// Rows per wave of a march (lbm_ch_march.hip, lbm_ch_pop.hip: strips of 58 or 60 columns,
+// four waves to a workgroup, so one on each SIMD of a CU).  A wave
 // pays its rows and about 2.3 rows' worth of entering rows; b workgroups to a CU share
 // its SIMDs, and a lone wave runs at 1 / 1.36 of a SIMD's rate.  The height with the
 // least (rows + 2.3) b therefore fills whole rounds of the 256 CUs.  Against a sweep of
 // heights 3 .. 74 the choice is within 5 % at every size from 128^2 to 5000 x 3900
-// (2048^2: within 3 % of the best; 6, 12, 24 and 32 rows cost 12-20 % more).
+// (2048^2: within 3 % of the best; 6, 12, 24 and 32 rows cost 12-20 % more).  Where the waves
+// of 2 rows still fit one round it is 2 (at least 4 rows / 2 rows, us a step: 384^2 6.2 / 5.7,
+// half storage 6.4 / 5.9; 128^2 between walls 6.3 / 5.2; 256^2 at tau_g = 0.8 6.8 / 5.5).
 struct MarchShape {  // lattices alike: strips of each, rows of each
   int strips, ny;
 };
 static int march_rows(const MarchShape* m, int n) {
-  int best = 4;
+  int best = 2;
   double cost = 1e30;
-  for (int ty = 4; ty <= 64; ++ty) {
+  for (int ty = 2; ty <= 64; ++ty) {
     long waves = 0;
     for (int i = 0; i < n; ++i) waves += (long)m[i].strips * ((m[i].ny + ty - 1) / ty);
     const long b = ((waves + 3) / 4 + 255) / 256;
@@ -325,18 +327,20 @@ static int march_rows(int nx, int ny) {
 // storage 4500^2 236 / 231 / 214.  Float32 with non-temporal stores (launch_phi_march) and 10
 // rows: 2048^2 40 (65 / 44 / 41), 2560^2 58, 4096^2 146 (216 / 273 / 252), while the two sum
 // fields fit that cache; beyond it 4500^2 293, and 1800^2 33.5 (34 / 32.5), 1280^2 20 (18 / 18).
+// 300000 to 600000 float32 nodes: non-temporal stores drain while the launch runs, 640^2 8.7 ->
+// 7.9, 768^2 10.3 -> 9.4 (512^2 7.1 / 7.2, 900^2 11.6 / 12.8).
 struct WriteMarch {
-  int rows, nt;
+  int rows, nt, out;
 };
 static WriteMarch write_march(const lbm_ch_params& p, bool rec) {
   const int64_t nodes = (int64_t)p.nx * p.ny, cache = 256 << 20;
   const bool f32 = p.storage == LBM_CH_STORE_F32;
   if (f32 && nodes >= (4 << 20) && 16 * nodes <= cache) {
     const int beside = (p.velocity_mode == LBM_CH_VEL_FIELD ? 8 : 0) + (rec ? 4 : 0);
-    return WriteMarch{10, (16 + beside) * nodes > cache ? 2 : 1};
+    return WriteMarch{10, (16 + beside) * nodes > cache ? 2 : 1, MARCH_OUT_ALIGNED};
   }
-  if (nodes * (16 + (f32 ? 36 : 20)) > cache) return WriteMarch{8, 0};
-  return WriteMarch{march_rows(p.nx, p.ny), 0};
+  if (nodes * (16 + (f32 ? 36 : 20)) > cache) return WriteMarch{8, 0, MARCH_OUT};
+  return WriteMarch{march_rows(p.nx, p.ny), f32 && nodes >= 300000 && nodes <= 600000, MARCH_OUT};
 }
 
 // Whether a context keeps the sum field m of its state beside the populations and steps in
@@ -348,8 +352,8 @@ static bool keeps_sum(const lbm_ch_params& p, int vmode) {
 
 // Whether the population step of a prescribed flow at another tau_g runs as a march in
 // registers (lbm_ch_pop.hip) instead of with tiles.  Us a step at tau_g = 0.8, tile / march,
-// float32 Model-II: 128^2 6.4 / 6.4, 256^2 6.9 / 6.6, 512^2 9.8 / 8.4, 768^2 17.1 / 11.8, 1500
-// x 1003 32.8 / 21.8, 1792^2 60 / 41; 2048^2 63 / 71, 4096^2 218 / 315: beyond the 256 MB
+// float32 Model-II: 256^2 7.0 / 5.5, 384^2 9.4 / 6.4, 512^2 9.6 / 8.2, 768^2 17.0 / 11.6, 1500
+// x 1003 32.8 / 21.8, 1792^2 60 / 41; 2048^2 68 / 71, 4096^2 218 / 315: beyond the 256 MB
 // cache behind L2 the march's strips, which store parts of lines, lose to the tiles.  Model
 // 3 with walls 128^2 7.2 / 7.3, 768^2 18.9 / 13.0.  Half storage 1792^2 54 / 33, 4096^2 227 /
 // 195.
@@ -611,11 +615,12 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
         e = launch_phi_of_sum(a.msrc, (int64_t)nodes, a.phi_rec, stream);
         a.phi_rec = nullptr;
       }
-      const int nt = last ? wm.nt : 0;
       a.mty = last ? wm.rows : march_rows(c->p.nx, c->p.ny);
-      a.mstrips = march_strips(c->p.nx, nt ? MARCH_OUT_NT : MARCH_OUT);
+      a.mout = last ? wm.out : MARCH_OUT;
+      a.mstrips = march_strips(c->p.nx, a.mout);
       if (e == hipSuccess)
-        e = launch_phi_march(c->p.walls != 0, c->vmode, c->p.model, c->p.storage, last, nt, a, stream);
+        e = launch_phi_march(c->p.walls != 0, c->vmode, c->p.model, c->p.storage, last,
+                             last ? wm.nt : 0, a, stream);
     } else {
       BlockSteps b{};
       b.steps = (int)k;
@@ -1299,6 +1304,7 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
     a.nonfinite = c->nf_dev;
     a.msrc = c->m[c->cur];
     a.mdst = c->m[1 - c->cur];
+    a.mout = MARCH_OUT;
     a.mstrips = march_strips(c->p.nx);
     b->built_cur[i] = c->cur;
     g.count += 1;

@@ -49,6 +49,7 @@ struct StepArgs {
   const double* msrc; // order-parameter form (lbm_ch_march.hip): sums at t_n
   double* mdst;       // and at t_{n+1} (nx*ny each)
   int mty, mstrips;   // its rows per wave and strips (march_strips)
+  int mout;           // and columns of a strip (at most MARCH_OUT)
   int* nonfinite;     // set to 1 when a phi summed in stage 1 is NaN or Inf (may be null)
 };
 
@@ -97,11 +98,11 @@ hipError_t launch_phi_record(int tx, int vmode, int model, const StepArgs& a, in
 // Marching step of a tau_g = 1 state in the order-parameter form (lbm_ch_march.hip):
 // prescribed velocity, models 1 and 2, any storage (march_ok).  From
 // a.msrc to a.mdst; to_g: the populations of the new state too, to a.dst.  a.phi_rec (may be
-// null, and is with walls) receives phi of the source state.  a.mty rows per wave, a.mstrips =
-// march_strips(nx).  nt (to_g, float32 storage): strips of MARCH_OUT_NT columns and
-// non-temporal stores of the populations (1), and stored velocities and phi_rec too (2).
-constexpr int MARCH_OUT = 58;  // columns of a strip
-constexpr int MARCH_OUT_NT = 48;
+// null, and is with walls) receives phi of the source state.  a.mty rows per wave, a.mout columns
+// per strip, a.mstrips = march_strips(nx, a.mout).  nt (to_g, float32 storage): non-temporal stores of the
+// populations (1), and of phi_rec, with stored velocities read past the caches too (2).
+constexpr int MARCH_OUT = 58;          // columns that a strip can yield
+constexpr int MARCH_OUT_ALIGNED = 48;  // strips whose rows start at multiples of 64 bytes
 constexpr int march_strips(int nx, int out = MARCH_OUT) { return (nx + out - 1) / out; }
 bool march_ok(int vmode, int model, bool t1);
 hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g, int nt,

@@ -64,8 +64,8 @@ template <bool WALLS, int VMODE, bool MODEL2, int ST, bool TO_G, bool REC, int N
 __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
   constexpr int M = 3;
-  constexpr int OUT = NT ? MARCH_OUT_NT : MARCH_OUT;
-  static_assert(OUT <= 64 - 2 * M, "a strip and its margins are one wave");
+  static_assert(MARCH_OUT == 64 - 2 * M, "a strip and its margins are one wave");
+  const int out = a.mout;
   const Coef& c = a.c;
   const int nx = a.nx, ny = a.ny;
   const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
@@ -81,15 +81,16 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   if (REC) rrec = make_rsrc(a.phi_rec, nodes * 4u);
 
   const int lane = threadIdx.x & 63;
-  const int x0 = (L % a.mstrips) * OUT;
-  const int y0 = (L / a.mstrips) * a.mty;
+  const int chunk = (int)((uint32_t)L / (uint32_t)a.mstrips);
+  const int x0 = (L - chunk * a.mstrips) * out;
+  const int y0 = chunk * a.mty;
   const int rows = min(a.mty, ny - y0);
   const int xl = x0 - M + lane;
-  const int x = ((xl % nx) + nx) % nx;
+  const int x = wrap_near(xl, nx);
   // columns this strip stores; the other lanes store at an offset beyond any buffer for
   // each element size (8, 4 and 2 bytes: 0xFFFFFE00, 0xFFFFFF00 and, against at most 1.2e9
   // bytes of 16-bit state, 0x7FFFFF80), which drops the store
-  const bool own = lane >= M && lane < M + OUT && xl < nx;
+  const bool own = lane >= M && lane < M + out && xl < nx;
   constexpr uint32_t OOB = 0x3FFFFFC0u;
   const uint32_t cst = own ? (uint32_t)x : OOB;
   constexpr int K0 = 2 * M;  // rows that enter before the first row is stored
@@ -106,7 +107,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   };
   In in[3];
   // rows enter in order from y0 - M; past the last needed row the load repeats it (in cache)
-  int lrow = WALLS ? y0 - M : ((y0 - M) % ny + ny) % ny;
+  int lrow = WALLS || y0 >= M ? y0 - M : y0 - M + ny;
   int left = rows + 2 * M;
   auto fetch = [&](In& I) {
     int row = lrow;
@@ -300,11 +301,12 @@ __global__ void __launch_bounds__(1024) k_phi_block(const StepArgs a, const Bloc
   const uint32_t rb = (uint32_t)nx * 4u;
   const int outc = 64 - 6 * T, outr = RR - 6 * T;
   const int strips = (nx + outc - 1) / outc;
-  const int x0 = (int)(blockIdx.x % strips) * outc, y0 = (int)(blockIdx.x / strips) * outr;
+  const int chunk = (int)(blockIdx.x / (uint32_t)strips);
+  const int x0 = ((int)blockIdx.x - chunk * strips) * outc, y0 = chunk * outr;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int xl = x0 - 3 * T + lane;
-  const int x = ((xl % nx) + nx) % nx;
+  const int x = wrap_near(xl, nx);
   const bool own = lane >= 3 * T && lane < 3 * T + outc && xl < nx;
   constexpr uint32_t OOB = 0x3FFFFFC0u;  // as in march_tile
   const uint32_t cst = own ? (uint32_t)x : OOB;
@@ -318,7 +320,7 @@ __global__ void __launch_bounds__(1024) k_phi_block(const StepArgs a, const Bloc
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int r = w * K + k, y = y0 - 3 * T + r;
-    yw[k] = ((y % ny) + ny) % ny;
+    yw[k] = wrap_near(y, ny);
     ownr[k] = r >= 3 * T && r < 3 * T + outr && y < ny;
     m[k] = ldb64(rsrc, (uint32_t)x * 8u, (uint32_t)yw[k] * 2u * rb);
     if (VFIELD) {
@@ -493,7 +495,7 @@ bool march_ok(int vmode, int model, bool t1) {
 hipError_t launch_phi_march(bool walls, int vmode, int model, int storage, bool to_g, int nt,
                             const StepArgs& a, hipStream_t s) {
   if (!march_ok(vmode, model, true) || a.mty < 1 ||
-      a.mstrips != march_strips(a.nx, nt ? MARCH_OUT_NT : MARCH_OUT))
+      a.mout < 1 || a.mout > MARCH_OUT || a.mstrips != march_strips(a.nx, a.mout))
     return hipErrorInvalidValue;
   if (nt) {
     if (!to_g || storage != ST_F32) return hipErrorInvalidValue;

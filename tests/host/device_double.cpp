@@ -137,7 +137,7 @@ hipError_t launch_pop_march(bool, int, int, int, const StepArgs& a, hipStream_t 
 hipError_t launch_phi_march(bool walls, int, int, int storage, bool to_g, int nt,
                             const StepArgs& a, hipStream_t s) {
   if ((walls && a.phi_rec) || (nt && (!to_g || storage != 0)) ||
-      a.mstrips != march_strips(a.nx, nt ? MARCH_OUT_NT : MARCH_OUT))
+      a.mstrips != march_strips(a.nx, a.mout))
     return hipErrorInvalidValue;
   return enqueue(nt ? "march_nt" : "march", a.mty, s, [=] {
     if (a.phi_rec) *a.phi_rec = (float)*a.msrc;

@@ -91,7 +91,12 @@ bool aligned4(const void* q) { return ((uintptr_t)q & 3u) == 0; }
 
 }  // namespace
 
+struct WriteMarch {  // shape of the march that writes the populations (write_march)
+  int rows, nt, out;
+};
+
 struct lbm_ch_ctx {
+  int cus;     // CUs of the device
   int device;  // HIP device current at lbm_ch_init
   // non-finite flag: pinned host memory mapped into the device, set by the step kernels
   // when a phi they sum is NaN or Inf, read by the next lbm_ch_step / lbm_ch_record
@@ -111,6 +116,8 @@ struct lbm_ch_ctx {
   const float *ax, *ay, *bx, *by, *ux, *uy;
   std::vector<double> tf;
   int tx, ty, nstrips, nblocks, xcd_remap;
+  int mty;              // rows per wave of the marches (march_rows)
+  WriteMarch write[2];  // the writing march; [1]: of recorded steps
   bool keep;  // m[cur] is kept beside g[cur] (keeps_sum)
   bool pop;   // population steps run as marches (pop_march_ok; not while another tile shape than the default is set)
   bool lost;  // a launch failed after others of its call had overwritten the state
@@ -169,9 +176,6 @@ static void apply_tiles(lbm_ch_ctx* c, int tx, int ty) {
   if (tx == 0) {  // shape of a lattice that steps in launches of its own
     c->tx = 0;
     c->ty = ty;
-    c->nstrips = (nx + 63) / 64;
-    c->nblocks = c->nstrips * ((ny + ty - 1) / ty);
-    c->xcd_remap = (c->nblocks % 8 == 0) ? 1 : 0;
     return;
   }
   if (ty > ny) ty = ny;
@@ -300,13 +304,13 @@ static void default_tiles(const lbm_ch_params& p, int& tx_out, int& ty_out) {
 struct MarchShape {  // lattices alike: strips of each, rows of each
   int strips, ny;
 };
-static int march_rows(const MarchShape* m, int n) {
+static int march_rows(const MarchShape* m, int n, int cus) {
   int best = 2;
   double cost = 1e30;
   for (int ty = 2; ty <= 64; ++ty) {
     long waves = 0;
     for (int i = 0; i < n; ++i) waves += (long)m[i].strips * ((m[i].ny + ty - 1) / ty);
-    const long b = ((waves + 3) / 4 + 255) / 256;
+    const long b = ((waves + 3) / 4 + cus - 1) / cus;
     const double t = (ty + 2.3) * (b == 1 ? 1.36 : (double)b);
     if (t < cost) {
       cost = t;
@@ -315,11 +319,6 @@ static int march_rows(const MarchShape* m, int n) {
   }
   return best;
 }
-static int march_rows(int nx, int ny) {
-  const MarchShape m{march_strips(nx), ny};
-  return march_rows(&m, 1);
-}
-
 // The march that writes the populations too (the last launch of a call) is bound by memory
 // once populations and sums are more than the 256 MB cache behind L2, and then wants more and
 // shorter waves.  Us of a call of one step, population step before / march_rows / this:
@@ -329,10 +328,8 @@ static int march_rows(int nx, int ny) {
 // fields fit that cache; beyond it 4500^2 293, and 1800^2 33.5 (34 / 32.5), 1280^2 20 (18 / 18).
 // 300000 to 600000 float32 nodes: non-temporal stores drain while the launch runs, 640^2 8.7 ->
 // 7.9, 768^2 10.3 -> 9.4 (512^2 7.1 / 7.2, 900^2 11.6 / 12.8).
-struct WriteMarch {
-  int rows, nt, out;
-};
-static WriteMarch write_march(const lbm_ch_params& p, bool rec) {
+// rows: of the other marches.
+static WriteMarch write_march(const lbm_ch_params& p, bool rec, int rows) {
   const int64_t nodes = (int64_t)p.nx * p.ny, cache = 256 << 20;
   const bool f32 = p.storage == LBM_CH_STORE_F32;
   if (f32 && nodes >= (4 << 20) && 16 * nodes <= cache) {
@@ -340,7 +337,7 @@ static WriteMarch write_march(const lbm_ch_params& p, bool rec) {
     return WriteMarch{10, (16 + beside) * nodes > cache ? 2 : 1, MARCH_OUT_ALIGNED};
   }
   if (nodes * (16 + (f32 ? 36 : 20)) > cache) return WriteMarch{8, 0, MARCH_OUT};
-  return WriteMarch{march_rows(p.nx, p.ny), f32 && nodes >= 300000 && nodes <= 600000, MARCH_OUT};
+  return WriteMarch{rows, f32 && nodes >= 300000 && nodes <= 600000, MARCH_OUT};
 }
 
 // Whether a context keeps the sum field m of its state beside the populations and steps in
@@ -366,23 +363,22 @@ static bool pop_march_ok(const lbm_ch_params& p) {
 }
 
 // How a lattice too small for marches takes its steps (launch_phi_block): region rows and
-// steps per launch, or rows = 0 for marches.  A workgroup fills a CU, so a shape serves while
-// its grid fits the 256 CUs at once; the more steps a launch takes, the smaller its output
-// and the larger its grid.  Us a step, float32, calls of 120 steps (march; 16 rows x 2
-// steps; 32 x 4; 32 x 3; 32 x 2), the shape taken first: 128^2 2.70 (16 x 2; march 4.71,
-// 32 x 4 2.90), 201 x 187 2.73 (16 x 2; 4.81, 3.04), 256^2 3.05 (32 x 4; 4.84, 16 x 2
-// 3.76), 300^2 3.55 (32 x 3; 4.82, 32 x 4 5.59), 384^2 3.70 (32 x 3; 4.96), 512^2 5.57
-// (march; 32 x 3 6.80).  Single steps: 16 rows x 1 (128^2 4.54, 300^2 5.21; march 5.42,
-// 5.89) while that fits.  So too calls of two, which are two launches of one step (one would
-// read and write the same sums): us a call, 16 rows / 32 rows / march: 300^2 10.7 / 13.9 /
-// 11.0, 384^2 13.9 / 14.4 / 11.4, with half storage 384^2 15.2 / 15.1 / 11.5.
+// steps per launch, or rows = 0 for marches.  A shape serves while its grid fits the CUs at
+// once (two workgroups of 16 rows fit a CU, but share its SIMDs: 512^2 7.6 us a single step,
+// march 7.4); the more steps a launch takes, the smaller its output and the larger its grid.
+// Us a step, float32, calls of 120 steps, the shape taken first: 128^2 2.53 (16 rows x 2 steps;
+// march 3.94, 32 x 4 2.79), 201 x 187 2.52 (16 x 2; 3.98, 2.85), 256^2 2.86 (32 x 4; 4.00, 16 x 2
+// 3.46), 300^2 3.33 (32 x 3; 4.10, 32 x 4 5.28), 384^2 3.46 (32 x 3; 4.46), 512^2 5.3 (march;
+// 32 x 3 6.5).  Single steps: 16 rows x 1 (128^2 5.0, 300^2 5.4; march 5.2, 5.6) while that fits.
+// So too calls of two, which are two launches of one step (one would read and write the same
+// sums): us a call, 16 rows / 32 rows / march: 300^2 10.2 / 12.8 / 10.3, 384^2 12.8 / 13.4 / 11.1.
 struct BlockPlan {
   int rows, steps;
 };
-static BlockPlan block_plan(int nx, int ny, int64_t nsteps) {
+static BlockPlan block_plan(int nx, int ny, int64_t nsteps, int cus) {
   auto fits = [&](int rows, int t) {
     const int w = 64 - 6 * t, h = rows - 6 * t;
-    return (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h) <= 256;
+    return (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h) <= cus;
   };
   if (nsteps <= 2) return fits(16, 1) ? BlockPlan{16, 1} : BlockPlan{0, 1};
   if (fits(16, 2)) return BlockPlan{16, 2};
@@ -460,6 +456,8 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   // the device's copy of the static scratch of lbm_ch_adjoint_static, looked up once per
   // device while that device is current
   if (de == hipSuccess) de = static_scratch_setup(device);
+  int cus = 0;
+  if (de == hipSuccess) de = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
   if (de != hipSuccess) return hip_fail(de);
   int* nf_host = nullptr;
   int* nf_dev = nullptr;
@@ -476,6 +474,7 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
     return LBM_CH_EINVAL;
   }
   c->device = device;
+  c->cus = cus > 0 ? cus : 1;
   c->nf_host = nf_host;
   c->nf_dev = nf_dev;
   c->p = *p;
@@ -554,6 +553,9 @@ int lbm_ch_init(lbm_ch_ctx** out, const lbm_ch_params* p, const lbm_ch_velocity*
   choose_tiles(c);
   c->keep = keeps_sum(*p, c->vmode);
   c->pop = pop_march_ok(*p);
+  const MarchShape shape{c->keep ? march_strips(p->nx) : pop_march_strips(p->nx), p->ny};
+  c->mty = march_rows(&shape, 1, c->cus);
+  for (int rec : {0, 1}) c->write[rec] = write_march(*p, rec != 0, c->mty);
   c->magic = CTX_MAGIC;
 
   hipError_t e = launch_fill(z, 0.0f, 2 * (int64_t)(p->nx + p->ny), stream);
@@ -583,11 +585,11 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
   const int to = c->cur ^ (int)(nsteps & 1);
   const size_t nodes = (size_t)c->p.nx * c->p.ny;
   // across walls a region would have to mirror its rows anew in every step: marches
-  const BlockPlan plan = c->p.walls ? BlockPlan{0, 1} : block_plan(c->p.nx, c->p.ny, nsteps);
+  const BlockPlan plan = c->p.walls ? BlockPlan{0, 1} : block_plan(c->p.nx, c->p.ny, nsteps, c->cus);
   // launches: as few as the plan allows, but two where one would read and write m[to]
   int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
   if (launches == 1 && to == c->cur) launches = 2;
-  const WriteMarch wm = write_march(c->p, phi_out != nullptr);
+  const WriteMarch wm = c->write[phi_out != nullptr];
   a.dst = c->g[to];
   // the sums go from buffer to buffer through m[1 - to] and the population buffer that is
   // not the target, whose populations no launch reads, and end in m[to]
@@ -615,7 +617,7 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
         e = launch_phi_of_sum(a.msrc, (int64_t)nodes, a.phi_rec, stream);
         a.phi_rec = nullptr;
       }
-      a.mty = last ? wm.rows : march_rows(c->p.nx, c->p.ny);
+      a.mty = last ? wm.rows : c->mty;
       a.mout = last ? wm.out : MARCH_OUT;
       a.mstrips = march_strips(c->p.nx, a.mout);
       if (e == hipSuccess)
@@ -670,9 +672,8 @@ static int run_steps(lbm_ch_ctx* c, int64_t nsteps, float* phi_out, hipStream_t 
   if (c->keep) return run_steps_march(c, a, nsteps, phi_out, stream);
   const bool pop_march = c->pop;
   if (pop_march) {
-    const MarchShape m{pop_march_strips(c->p.nx), c->p.ny};
-    a.mstrips = m.strips;
-    a.mty = march_rows(&m, 1);
+    a.mstrips = pop_march_strips(c->p.nx);
+    a.mty = c->mty;
   }
   StepArgs r = a;
   int rt_rows = 0, rt_blocks = 0;
@@ -1314,7 +1315,7 @@ static int batch_build(lbm_ch_batch* b, hipStream_t stream) {
       std::vector<MarchShape> shapes;
       for (int k = g.first; k < g.first + g.count; ++k)
         shapes.push_back(MarchShape{b->hargs[k].mstrips, b->hargs[k].ny});
-      const int ty = march_rows(shapes.data(), g.count);
+      const int ty = march_rows(shapes.data(), g.count, b->cus);
       for (int k = g.first; k < g.first + g.count; ++k) b->hargs[k].mty = ty;
     }
     g.start_off = (int)b->hstart.size();

@@ -45,7 +45,8 @@ struct StepArgs {
   float tf;
   float* xh;          // model 3: X of the previous step (2 planes of nx*ny), rewritten
   int xfirst;         // model 3: 1 on the first step (no earlier X: zero difference)
-  float* phi_rec;     // launch_phi_record only: phi of the source state (nx*ny), written
+  float* phi_rec;     // phi of the source state (nx*ny), written by launch_phi_record, marches and
+                      // blocks (may be null there); others ignore it
   const double* msrc; // order-parameter form (lbm_ch_march.hip): sums at t_n
   double* mdst;       // and at t_{n+1} (nx*ny each)
   int mty, mstrips;   // its rows per wave and strips (march_strips)
@@ -114,18 +115,19 @@ constexpr int POP_MARCH_OUT = 60;
 constexpr int pop_march_strips(int nx) { return (nx + POP_MARCH_OUT - 1) / POP_MARCH_OUT; }
 hipError_t launch_pop_march(bool walls, int vmode, int model, int storage, const StepArgs& a,
                             hipStream_t s);
-// Up to BLOCK_STEPS marching steps in one launch (small periodic lattices), on regions of 64 columns
-// x `rows` (16 or 32) rows; b.tf: the time factor of each.  phi of step k's source goes to
+// Up to BLOCK_STEPS marching steps in one launch (small periodic lattices), on regions of 64
+// columns x `rows` (16 or 32) rows; b.tf: the time factor of each.  phi of step k's source goes to
 // a.phi_rec + k nx ny.
-constexpr int BLOCK_STEPS = 5;
+constexpr int BLOCK_STEPS = 4;
 struct BlockSteps {
   int steps;
   float tf[BLOCK_STEPS];
 };
 hipError_t launch_phi_block(int rows, int vmode, int model, int storage, bool to_g,
                             const StepArgs& a, const BlockSteps& b, hipStream_t s);
-// The lattices of a batch at other tau_g.  grid: a multiple of 8 workgroups.  persistent: the grid strides over the tiles (size
-// it with phi_batch_blocks_per_cu); otherwise one tile per workgroup (grid >= tiles).
+// The lattices of a batch at other tau_g.  grid: a multiple of 8 workgroups.  persistent: the
+// grid strides over the tiles (size it with phi_batch_blocks_per_cu); otherwise one tile per
+// workgroup (grid >= tiles).
 int phi_batch_blocks_per_cu(int tx, int vmode, bool model2);
 hipError_t launch_phi_batch(int tx, int vmode, bool model2, bool persistent, const BatchArgs& b,
                             int grid, hipStream_t s);

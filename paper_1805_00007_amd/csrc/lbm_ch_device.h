@@ -71,9 +71,6 @@ __device__ __forceinline__ void stb(rsrc_t r, float v, uint32_t voff, uint32_t s
 // Measured on MI355X (2048^2): 2-5 % faster for float32 stores; the 2-byte stores of
 // the 16-bit storage modes become ~10 % slower with it, so they keep the default.
 constexpr int CP_NT = 2;
-__device__ __forceinline__ float ldb_nt(rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, CP_NT));
-}
 __device__ __forceinline__ void stb_nt(rsrc_t r, float v, uint32_t voff, uint32_t soff) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, CP_NT);
 }

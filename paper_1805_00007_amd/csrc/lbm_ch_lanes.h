@@ -31,6 +31,11 @@ __device__ __forceinline__ double east(double v) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// A non-temporal load (CP_NT).
+__device__ __forceinline__ float ldb_nt(rsrc_t r, uint32_t voff, uint32_t soff) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, CP_NT));
+}
+
 // Periodic index of i in -64 < i < n + 64: a comparison where that is enough, for the divisions
 // of a remainder before a wave's first load are a good part of a short launch.
 __device__ __forceinline__ int wrap_near(int i, int n) {

@@ -200,3 +200,25 @@ def test_writing_march_of_large_lattices(nx, ny, walls):
             assert torch.equal(one[0], traj[k]), (model, k)
         assert torch.equal(s.phi(), end), model
         s.close()
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+def test_load_and_steps_under_capture(storage):
+    """A captured load and an even number of steps replay from the loaded state, whatever ran
+    before."""
+    phi0, vels = _lattice(257, 129)
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        s = _solver(257, 129, phi0, vels[0], storage=storage)
+        buf, n = s.step(2).save_state()
+        want = s.step(4).phi()
+    st.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        s.load_state(buf, n).step(4)
+    for k in (2, 6, 4):
+        with torch.cuda.stream(st):
+            graph.replay()
+            assert torch.equal(s.phi(), want), k
+            s.step(k)
+    s.close()

@@ -324,20 +324,22 @@ static int march_rows(const MarchShape* m, int n, int cus) {
 // shorter waves.  Us of a call of one step, population step before / march_rows / this:
 // float32 2560^2 104 / 115 / 106 with 8 rows; 4500^2 283 / 330 / 292; 7000^2 666 / 798 / 678; half
 // storage 4500^2 236 / 231 / 214.  Float32 with non-temporal stores (launch_phi_march) and 10
-// rows: 2048^2 40 (65 / 44 / 41), 2560^2 58, 4096^2 146 (216 / 273 / 252), while the two sum
-// fields fit that cache; beyond it 4500^2 293, and 1800^2 33.5 (34 / 32.5), 1280^2 20 (18 / 18).
+// rows: 2300^2 48 (91 / 73 / 65), 2560^2 58, 4096^2 146 (216 / 273 / 252), while the two sum
+// fields fit that cache; beyond it 4500^2 293.  Where all fits the cache absorbs the stores:
+// 2048^2 40 (65 / 44 / 41), but 20 steps 526 against 520.
 // 300000 to 600000 float32 nodes: non-temporal stores drain while the launch runs, 640^2 8.7 ->
 // 7.9, 768^2 10.3 -> 9.4 (512^2 7.1 / 7.2, 900^2 11.6 / 12.8).
 // rows: of the other marches.
 static WriteMarch write_march(const lbm_ch_params& p, bool rec, int rows) {
   const int64_t nodes = (int64_t)p.nx * p.ny, cache = 256 << 20;
   const bool f32 = p.storage == LBM_CH_STORE_F32;
-  if (f32 && nodes >= (4 << 20) && 16 * nodes <= cache) {
+  if (nodes * (16 + (f32 ? 36 : 20)) <= cache)
+    return WriteMarch{rows, f32 && nodes >= 300000 && nodes <= 600000, MARCH_OUT};
+  if (f32 && 16 * nodes <= cache) {
     const int beside = (p.velocity_mode == LBM_CH_VEL_FIELD ? 8 : 0) + (rec ? 4 : 0);
     return WriteMarch{10, (16 + beside) * nodes > cache ? 2 : 1, MARCH_OUT_ALIGNED};
   }
-  if (nodes * (16 + (f32 ? 36 : 20)) > cache) return WriteMarch{8, 0, MARCH_OUT};
-  return WriteMarch{rows, f32 && nodes >= 300000 && nodes <= 600000, MARCH_OUT};
+  return WriteMarch{8, 0, MARCH_OUT};
 }
 
 // Whether a context keeps the sum field m of its state beside the populations and steps in

@@ -36,13 +36,6 @@ __device__ __forceinline__ float ldb_nt(rsrc_t r, uint32_t voff, uint32_t soff) 
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, CP_NT));
 }
 
-// Periodic index of i in -64 < i < n + 64: a comparison where that is enough, for the divisions
-// of a remainder before a wave's first load are a good part of a short launch.
-__device__ __forceinline__ int wrap_near(int i, int n) {
-  if (n >= 64) return i < 0 ? i + n : i >= n ? i - n : i;  // the same way for a whole wave
-  return ((i % n) + n) % n;
-}
-
 // A table read at a wave-uniform index through the scalar cache (never written while a
 // step runs).
 __device__ __forceinline__ float ld_uniform(const float* p, int i) {

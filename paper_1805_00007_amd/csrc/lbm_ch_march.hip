@@ -65,7 +65,7 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   constexpr bool VFIELD = VMODE == VEL_FIELD;
   constexpr int M = 3;
   static_assert(MARCH_OUT == 64 - 2 * M, "a strip and its margins are one wave");
-  const int out = a.mout;
+  const int out = TO_G ? a.mout : MARCH_OUT;
   const Coef& c = a.c;
   const int nx = a.nx, ny = a.ny;
   const uint32_t nodes = (uint32_t)nx * ny, pitch = a.pitch;
@@ -86,7 +86,10 @@ __device__ __forceinline__ void march_tile(const StepArgs& a, const int L) {
   const int y0 = chunk * a.mty;
   const int rows = min(a.mty, ny - y0);
   const int xl = x0 - M + lane;
-  const int x = wrap_near(xl, nx);
+  // by comparison (more than one on lattices narrower than a strip only): the two divisions of
+  // a remainder before the first load were a good part of a short launch
+  int x = xl < 0 ? xl + nx : xl;
+  while (x >= nx) x -= nx;
   // columns this strip stores; the other lanes store at an offset beyond any buffer for
   // each element size (8, 4 and 2 bytes: 0xFFFFFE00, 0xFFFFFF00 and, against at most 1.2e9
   // bytes of 16-bit state, 0x7FFFFF80), which drops the store
@@ -279,6 +282,12 @@ __global__ void __launch_bounds__(64 * MARCH_WAVES) k_march_batch(const BatchArg
   }
   const int first = ((const __attribute__((address_space(4))) int*)(uintptr_t)b.start)[inst];
   march_tile<false, VMODE, MODEL2, ST_F32, TO_G, false>(a, L - first);
+}
+
+// Periodic index of i in -64 < i < n + 64.
+__device__ __forceinline__ int wrap_near(int i, int n) {
+  if (n >= 64) return i < 0 ? i + n : i >= n ? i - n : i;  // the same way for a whole wave
+  return ((i % n) + n) % n;
 }
 
 // Several steps of one launch, for lattices too small to fill the chip with marches, where

@@ -11,9 +11,11 @@ the whole lattice.  At tau_g = 1 steps pass the sum of the populations (one FP64
 per node) from one to the next, and the last step of a call writes the nine float32
 populations too.  Prints one JSON line:
   value        MLUPS = nx*ny*steps / time of the timed steps (inputs resident in HBM)
-  roofline     algorithmic bytes (16 B per node update, 52 in the last step of a call) /
-               average kernel duration from HIP events, against the 8 TB/s HBM peak;
-               single_step: the same for calls of one step
+  roofline     the step is bound by vector instructions: cycles spent issuing them (from the
+               committed rocprofv3 counter summary) / average kernel duration from HIP events,
+               against 1024 SIMDs at 2.4 GHz; hbm: algorithmic bytes (16 B per node update, 52
+               in the last step of a call) against the 8 TB/s HBM peak; single_step: the
+               latter for calls of one step
   population_step  the step of any other tau_g, which reads and writes nine populations (72
                B per node update); traffic = measured HBM bytes per launch from the
                committed rocprofv3 counter summary (null when the kernel source changed)
@@ -54,6 +56,12 @@ RT_KERNEL_SRC = (os.path.join(ROOT, "paper_1805_00007_amd", "csrc", "lbm_ch_ns.h
                  os.path.join(ROOT, "paper_1805_00007_amd", "csrc", "lbm_ch_device.h"),
                  os.path.join(ROOT, "paper_1805_00007_amd", "csrc", "lbm_ch_stencil.h"))
 RT_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "rt_step_rt256x1024_traffic.txt")
+# and for the marching step at tau_g = 1, whose vector-ALU time bounds it
+MARCH_KERNEL_SRC = tuple(os.path.join(ROOT, "paper_1805_00007_amd", "csrc", f) for f in
+                         ("lbm_ch_march.hip", "lbm_ch_lanes.h", "lbm_ch_device.h",
+                          "lbm_ch_stencil.h"))
+MARCH_VALU_FILE = os.path.join(ROOT, "profiles", "march_vortex2048_valu.txt")
+VALU_PEAK_GCYCLES = 256 * 4 * 2.4  # SIMDs x GHz
 GOLDEN = os.path.join(ROOT, "tests", "golden", "vortex2048_oracle_1000.npz")
 ADJ_GOLDEN = os.path.join(ROOT, "tests", "golden", "adjoint256_oracle_2000.npz")
 
@@ -193,8 +201,8 @@ def population_step(lbm, torch, steps=50, warm=5):
 
 
 def storage_variant(lbm, torch, storage, steps):
-    """Same workload with 16-bit population storage (20 B of state per node): throughput over at least 500 steps, and phi at the stored
-    1000-step oracle samples."""
+    """Same workload with 16-bit population storage (20 B of state per node): throughput over at
+    least 500 steps, and phi at the stored 1000-step oracle samples."""
     import numpy as np
     import workloads
     steps = max(steps, 500)
@@ -210,13 +218,12 @@ def storage_variant(lbm, torch, storage, steps):
     ms = e0.elapsed_time(e1) / steps
     tiles = s.tiles
     s.close()
-    kernel = "k_phi_march (16-bit storage rounding, sum field between steps)"
     lu = run_bytes_per_lu(steps, 20.0)
     out = {"MLUPS": round(w.nx * w.ny / (ms * 1e-3) / 1e6, 1), "ms_per_step": round(ms, 5),
            "timed_steps": steps, "bytes_per_lu": round(lu, 2), "tiles": list(tiles),
            "effective_GBps": round(w.nx * w.ny * lu / (ms * 1e-3) / 1e9, 1),
-           "roofline": roofline(lu, w.nx * w.ny, ms * 1e3, kernel,
-                                "profiles/marches_kernel_trace.md")}
+           "roofline": march_roofline(lu, w.nx * w.ny, ms * 1e3,
+                                      {lbm.STORE_F16: "f16", lbm.STORE_BF16: "bf16"}[storage])}
     if os.path.exists(GOLDEN):
         g = np.load(GOLDEN)
         s = lbm.solver_for(workloads.metric2048(steps=1000), storage=storage)
@@ -391,10 +398,26 @@ def rt_leg(lbm, torch, steps=500, warm=50):
     return out
 
 
+def march_roofline(bytes_per_lu, nodes, us, case="f32", kernel="k_phi_march"):
+    """Roofline sub-object of the marching step: cycles its SIMDs spend issuing vector
+    instructions (committed counter summary of the unchanged kernel) over its duration,
+    against all SIMDs issuing in every cycle; the HBM figures beside it."""
+    hbm = roofline(bytes_per_lu, nodes, us, kernel, "profiles/marches_kernel_trace.md")
+    cycles = measured_traffic(MARCH_VALU_FILE, MARCH_KERNEL_SRC,
+                              "valu_issue_cycles_per_launch_" + case)
+    if cycles is None:
+        return hbm
+    achieved = cycles / (us * 1e-6) / 1e9
+    return {"bound": "valu", "achieved": round(achieved, 1), "peak": VALU_PEAK_GCYCLES,
+            "unit": "G issue cycles/s", "frac": round(achieved / VALU_PEAK_GCYCLES, 4),
+            "kernel": kernel,
+            "kernel_avg_us": round(us, 2), "profile": "profiles/march_vortex2048_valu.txt",
+            "hbm": {k: hbm[k] for k in ("bytes_per_lu", "achieved", "peak", "unit", "frac")}}
+
+
 def batch_leg(lbm, torch, steps=5000, plain_steps=200, check_steps=100):
-    """64 lattices of uneven sizes (sides 64-512, seeded): the batched kernel with the
-    autotuned schedule (persistent grid or one workgroup per tile) and tiles, `steps`
-    steps captured in one hipGraph and launched once,
+    """64 lattices of uneven sizes (sides 64-512, seeded): the batched marches, `steps` steps
+    captured in one hipGraph and launched once,
     against the plain form (one lbm_ch_step launch per lattice per step) on the same GPU;
     both give bitwise the same fields."""
     import numpy as np
@@ -404,8 +427,6 @@ def batch_leg(lbm, torch, steps=5000, plain_steps=200, check_steps=100):
     sol = [lbm.solver_for(w) for w in ws]
     ref = [lbm.solver_for(w) for w in ws]
     b = lbm.Batch(sol)
-    tiles, tuned_us = b.autotune(5)
-    persistent = b.persistent
     b.step(check_steps, graph=True)
     for s in ref:
         s.step(check_steps)
@@ -443,14 +464,12 @@ def batch_leg(lbm, torch, steps=5000, plain_steps=200, check_steps=100):
             "plain_MLUPS": round(nodes / t_plain / 1e6, 1),
             "plain_us_per_step": round(t_plain * 1e6, 2),
             "speedup_vs_plain": round(t_plain / t_batch, 2),
-            "autotuned_tiles": {"tx": tiles[0], "ty": tiles[1], "trial_us": round(tuned_us, 2),
-                                "schedule": "persistent" if persistent else "tile per workgroup"},
+            "schedule": "marches (tau_g = 1: neither tiles nor a schedule to tune)",
             "bitwise_equal_to_plain_after_%d" % check_steps: bool(same),
             "nonfinite": int(nonfinite),
             "bytes_per_lu": round(run_bytes_per_lu(steps) + 8, 2),
-            "roofline": roofline(run_bytes_per_lu(steps) + 8, nodes, t_batch * 1e6,
-                                 "k_march_batch (all 64 lattices)",
-                                 "profiles/marches_kernel_trace.md")}
+            "roofline": march_roofline(run_bytes_per_lu(steps) + 8, nodes, t_batch * 1e6, "batch",
+                                       "k_march_batch (all 64 lattices)")}
 
 
 def main():
@@ -545,8 +564,6 @@ def main():
     nodes = w.nx * w.ny
     mlups = nodes * args.steps / (t_ms * 1e-3) / 1e6
     lu = run_bytes_per_lu(args.steps)
-    algo = lu * nodes
-    achieved = algo / (k_ms * 1e-3) / 1e9
     single_lu = run_bytes_per_lu(1)
     single = single_lu * nodes / (iso_ms * 1e-3) / 1e9
     out = {
@@ -568,16 +585,13 @@ def main():
         "effective_GBps": round(mlups * lu / 1e3, 1),
         "hbm_frac_effective": round(mlups * lu / 1e3 / HBM_PEAK_GBS, 4),
         "wall_s_timed": round(wall, 4),
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "kernel": "k_phi_march (vector-ALU bound: sum field between steps)",
-                     "kernel_avg_us": round(k_ms * 1e3, 2),
-                     "algorithmic_bytes_per_launch": algo,
-                     "single_step": {"kernel": "k_phi_march, populations written",
-                                     "isolated_launch_us": round(iso_ms * 1e3, 2),
-                                     "achieved": round(single, 1),
-                                     "frac": round(single / HBM_PEAK_GBS, 4),
-                                     "algorithmic_bytes_per_launch": single_lu * nodes}},
+        "roofline": dict(march_roofline(lu, nodes, k_ms * 1e3),
+                         algorithmic_bytes_per_launch=lu * nodes,
+                         single_step={"bound": "hbm", "kernel": "k_phi_march, populations written",
+                                      "isolated_launch_us": round(iso_ms * 1e3, 2),
+                                      "achieved": round(single, 1),
+                                      "frac": round(single / HBM_PEAK_GBS, 4),
+                                      "algorithmic_bytes_per_launch": single_lu * nodes}),
     }
     if not args.no_accuracy:
         out["accuracy"] = accuracy(lbm, workloads.metric2048(steps=1000), torch)

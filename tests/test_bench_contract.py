@@ -28,3 +28,14 @@ def test_committed_traffic_summaries_match_the_kernel_sources():
                                    "hbm_bytes_per_launch_" + name)
         assert t is not None, "profiles/rt_step_rt256x1024_traffic.txt is stale"
         assert 1.0 <= t / (bytes_lu * 256 * 1024) < 1.1
+
+
+def test_committed_valu_summary_matches_the_kernel_sources():
+    """The vector-ALU time in bench.py's roofline of the marches comes from a committed counter
+    summary of the unchanged kernels, and is the greater part of a launch."""
+    sys.path.insert(0, ROOT)
+    import bench
+    for case, us in (("f32", 26.0), ("f16", 30.0), ("bf16", 29.0), ("batch", 42.5)):
+        r = bench.march_roofline(16.0, 2048 * 2048, us, case)
+        assert r["bound"] == "valu", "profiles/march_vortex2048_valu.txt is stale"
+        assert 0.6 < r["frac"] < 1.0, case

@@ -364,29 +364,36 @@ static bool pop_march_ok(const lbm_ch_params& p) {
   return nodes * (p.model == 3 ? 88 : 72) <= (256 << 20);
 }
 
-// How a lattice too small for marches takes its steps (launch_phi_block): region rows and
-// steps per launch, or rows = 0 for marches.  A shape serves while its grid fits the CUs at
-// once (two workgroups of 16 rows fit a CU, but share its SIMDs: 512^2 7.6 us a single step,
-// march 7.4); the more steps a launch takes, the smaller its output and the larger its grid.
-// Us a step, float32, calls of 120 steps, the shape taken first: 128^2 2.53 (16 rows x 2 steps;
-// march 3.94, 32 x 4 2.79), 201 x 187 2.52 (16 x 2; 3.98, 2.85), 256^2 2.86 (32 x 4; 4.00, 16 x 2
-// 3.46), 300^2 3.33 (32 x 3; 4.10, 32 x 4 5.28), 384^2 3.46 (32 x 3; 4.46), 512^2 5.3 (march;
-// 32 x 3 6.5).  Single steps: 16 rows x 1 (128^2 5.0, 300^2 5.4; march 5.2, 5.6) while that fits.
-// So too calls of two, which are two launches of one step (one would read and write the same
-// sums): us a call, 16 rows / 32 rows / march: 300^2 10.2 / 12.8 / 10.3, 384^2 12.8 / 13.4 / 11.1.
+// How a periodic lattice takes its steps: region rows and steps per launch where it is too
+// small for marches (launch_phi_block), or rows = 0 for marches.  A shape serves while its grid
+// fits the CUs at once; the more steps a launch takes, the smaller its output and the larger
+// its grid.  Us a step, float32, calls of 120 steps, the shape taken first: 128^2 2.53 (16 rows x
+// 2 steps; march 3.94, 32 x 4 2.79), 201 x 187 2.52 (16 x 2; 3.98, 2.85), 256^2 2.86 (32 x 4;
+// 4.00, 16 x 2 3.46), 300^2 3.33 (32 x 3; 4.10, 32 x 4 5.28), 384^2 3.46 (32 x 3; 4.46), 512^2 5.3
+// (march; 32 x 3 6.5).  Calls of one and two steps are launches of one step (one of two would
+// read and write the same sums), which march: 128^2 4.2 us (16 rows x 1 step 4.3), 300^2 4.75
+// (5.0).
+//   single: the last step of a call in tiles (launch_phi_single), where they are one round of
+// the CUs and a march's waves, of 4 rows or more, spend as much on their margins: tile / march
+// 512^2 6.2 / 7.0, half storage 5.9 / 7.0, 64 x 4096 6.5 / 8.0, 441 x 400 6.45 / 6.6; with 3 rows
+// 384^2 5.5 / 5.5, in two rounds 560^2 8.3 / 7.5.
 struct BlockPlan {
   int rows, steps;
+  bool single;
 };
-static BlockPlan block_plan(int nx, int ny, int64_t nsteps, int cus) {
-  auto fits = [&](int rows, int t) {
-    const int w = 64 - 6 * t, h = rows - 6 * t;
-    return (int64_t)((nx + w - 1) / w) * ((ny + h - 1) / h) <= cus;
+static BlockPlan block_plan(const lbm_ch_params& p, int64_t nsteps, int cus, int march_rows) {
+  auto fits = [&](int w, int h) {
+    return (int64_t)((p.nx + w - 1) / w) * ((p.ny + h - 1) / h) <= cus;
   };
-  if (nsteps <= 2) return fits(16, 1) ? BlockPlan{16, 1} : BlockPlan{0, 1};
-  if (fits(16, 2)) return BlockPlan{16, 2};
-  for (int t : {4, 3, 2})
-    if (fits(32, t)) return BlockPlan{32, t};
-  return BlockPlan{0, 1};
+  auto block_fits = [&](int rows, int t) { return fits(64 - 6 * t, rows - 6 * t); };
+  // across walls regions and tiles would have to mirror their rows anew: marches
+  if (p.walls) return BlockPlan{0, 1, false};
+  if (nsteps > 2) {
+    if (block_fits(16, 2)) return BlockPlan{16, 2, false};
+    for (int t : {4, 3, 2})
+      if (block_fits(32, t)) return BlockPlan{32, t, false};
+  }
+  return BlockPlan{0, 1, march_rows >= 4 && fits(64, 16)};
 }
 
 static void choose_tiles(lbm_ch_ctx* c) {
@@ -586,8 +593,7 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
                            hipStream_t stream) {
   const int to = c->cur ^ (int)(nsteps & 1);
   const size_t nodes = (size_t)c->p.nx * c->p.ny;
-  // across walls a region would have to mirror its rows anew in every step: marches
-  const BlockPlan plan = c->p.walls ? BlockPlan{0, 1} : block_plan(c->p.nx, c->p.ny, nsteps, c->cus);
+  const BlockPlan plan = block_plan(c->p, nsteps, c->cus, c->mty);
   // launches: as few as the plan allows, but two where one would read and write m[to]
   int64_t launches = (nsteps + plan.steps - 1) / plan.steps;
   if (launches == 1 && to == c->cur) launches = 2;
@@ -613,7 +619,10 @@ static int run_steps_march(lbm_ch_ctx* c, StepArgs a, int64_t nsteps, float* phi
     next ^= 1;
     a.phi_rec = phi_out ? phi_out + (size_t)done * nodes : nullptr;
     hipError_t e = hipSuccess;
-    if (plan.rows == 0) {
+    if (last && plan.single) {
+      a.tf = time_factor(c, n0 + done);
+      e = launch_phi_single(c->vmode, c->p.model, c->p.storage, a, stream);
+    } else if (plan.rows == 0) {
       a.tf = time_factor(c, n0 + done);
       if (c->p.walls && a.phi_rec) {
         e = launch_phi_of_sum(a.msrc, (int64_t)nodes, a.phi_rec, stream);

@@ -125,6 +125,9 @@ struct BlockSteps {
 };
 hipError_t launch_phi_block(int rows, int vmode, int model, int storage, bool to_g,
                             const StepArgs& a, const BlockSteps& b, hipStream_t s);
+// One step of a periodic lattice on tiles of 64 columns x 16 rows, from a.msrc to a.mdst and
+// a.dst (the last step of a call); a.phi_rec as above.
+hipError_t launch_phi_single(int vmode, int model, int storage, const StepArgs& a, hipStream_t s);
 // The lattices of a batch at other tau_g.  grid: a multiple of 8 workgroups.  persistent: the
 // grid strides over the tiles (size it with phi_batch_blocks_per_cu); otherwise one tile per
 // workgroup (grid >= tiles).

@@ -158,6 +158,14 @@ hipError_t launch_phi_block(int rows, int, int, int, bool to_g, const StepArgs& 
     if (to_g) put(a.dst, *a.mdst);
   });
 }
+hipError_t launch_phi_single(int, int, int, const StepArgs& a, hipStream_t s) {
+  return enqueue("single", 0, s, [=] {
+    if (a.phi_rec) *a.phi_rec = (float)*a.msrc;
+    dbl::steps.push_back({a.tf, 1});
+    *a.mdst = *a.msrc + 1;
+    put(a.dst, *a.mdst);
+  });
+}
 hipError_t launch_march_batch(int, bool, bool to_g, const BatchArgs& b, hipStream_t s) {
   return enqueue("march_batch", 0, s, [=] {
     for (int i = 0; i < b.n; ++i) {

@@ -222,3 +222,28 @@ def test_load_and_steps_under_capture(storage):
             assert torch.equal(s.phi(), want), k
             s.step(k)
     s.close()
+
+
+# at most 256 tiles of 64 x 16, and too large for marches of 3 rows
+@pytest.mark.parametrize("nx,ny", [(505, 509), (64, 4096), (65, 2035), (4090, 63), (449, 430), (100, 2000)])
+@pytest.mark.parametrize("storage", [0, 1, 2])
+def test_single_step_tiles(nx, ny, storage):
+    """The last step of a call in tiles: phi recorded, sums kept and populations stored are
+    bitwise those of marches (the same steps as the first of a longer call)."""
+    rng = np.random.default_rng(nx)
+    phi0, vels = _lattice(nx, ny)
+    vels[0]["velocity"]["tf"] = rng.uniform(0.5, 1, 9)
+    for model, vel in ((1, vels[0]), (2, vels[0]), (1, vels[1]), (2, vels[1])):
+        s = _solver(nx, ny, phi0, vel, storage=storage, model=model)
+        saved = s.save_state()
+        traj = torch.empty((5, ny, nx), dtype=torch.float32, device="cuda")
+        s.record(5, traj)  # marches but for the last
+        end, state = s.phi(), _state(s)
+        s.load_state(*saved)
+        one = torch.empty((5, ny, nx), dtype=torch.float32, device="cuda")
+        for k in range(5):
+            s.record(1, one[k:k + 1])
+        assert torch.equal(one, traj), (model, list(vel))
+        assert torch.equal(s.phi(), end) and torch.equal(_state(s), state), (model, list(vel))
+        _stored_populations_hold_the_state(s, 1)
+        s.close()

@@ -351,15 +351,14 @@ static bool keeps_sum(const lbm_ch_params& p, int vmode) {
 
 // Whether the population step of a prescribed flow at another tau_g runs as a march in
 // registers (lbm_ch_pop.hip) instead of with tiles.  Us a step at tau_g = 0.8, tile / march,
-// float32 Model-II: 256^2 7.0 / 5.5, 384^2 9.4 / 6.4, 512^2 9.6 / 8.2, 768^2 17.0 / 11.6, 1500
+// float32 Model-II: 16^2 6.1 / 5.2, 128^2 6.4 / 5.2, 170^2 7.6 / 5.3, 256^2 7.0 / 5.5, 384^2 9.4 / 6.4, 512^2 9.6 / 8.2, 768^2 17.0 / 11.6, 1500
 // x 1003 32.8 / 21.8, 1792^2 60 / 41; 2048^2 68 / 71, 4096^2 218 / 315: beyond the 256 MB
 // cache behind L2 the march's strips, which store parts of lines, lose to the tiles.  Model
-// 3 with walls 128^2 7.2 / 7.3, 768^2 18.9 / 13.0.  Half storage 1792^2 54 / 33, 4096^2 227 /
-// 195.
+// 3 48^2 6.5 / 5.6, with walls 768^2 18.9 / 13.0.  Half storage 48^2 6.7 / 5.2, 1792^2 54 / 33,
+// 4096^2 227 / 195.
 static bool pop_march_ok(const lbm_ch_params& p) {
   if (p.velocity_mode == LBM_CH_VEL_NS || p.tau_g == 1.0) return false;
   const int64_t nodes = (int64_t)p.nx * p.ny;
-  if (nodes < 30000) return false;
   if (p.storage != LBM_CH_STORE_F32) return nodes <= (20 << 20);
   return nodes * (p.model == 3 ? 88 : 72) <= (256 << 20);
 }

@@ -40,8 +40,8 @@ def _state(s):
     return torch.cat([p.reshape(-1) for p in parts] + [buf[n:]])
 
 
-# 181 x 197 and 1100 x 37 take the march by default, 131 x 45 tiles; 1100 = 2 x 512 + 76
-@pytest.mark.parametrize("nx,ny", [(131, 45), (181, 197), (1100, 37)])
+# by default all march; 1100 = 2 x 512 + 76
+@pytest.mark.parametrize("nx,ny", [(5, 4), (61, 7), (131, 45), (181, 197), (1100, 37)])
 @pytest.mark.parametrize("storage,model", [(0, 1), (0, 2), (0, 3), (1, 2), (2, 1)])
 def test_tile_shapes_at_other_tau(nx, ny, storage, model):
     phi0, vels = _lattice(nx, ny)
@@ -87,8 +87,8 @@ def test_record_at_other_tau(nx, ny, storage, model, walls):
     ((0, 16), False, 0), ((0, 16), True, 1), ((64, 4), True, 0), ((64, 4), True, 1),
     ((256, 32), False, 1), ((128, 1), True, 0), ((128, 5), False, 1)])
 def test_batch_at_other_tau(tiles, graph, persistent):
-    """Tiles and schedules of a batch at tau_g != 1 against single steps of each lattice
-    (tiles below 30000 nodes, the march above)."""
+    """Tiles and schedules of a batch at tau_g != 1 against single steps of each lattice, which
+    march."""
     import paper_1805_00007_amd as lbm
     sides = [(20, 9), (64, 64), (131, 45), (181, 197), (257, 130), (600, 51), (1100, 37)]
     pairs = []

@@ -370,8 +370,9 @@ static bool pop_march_ok(const lbm_ch_params& p) {
 // 2 steps; march 3.94, 32 x 4 2.79), 201 x 187 2.52 (16 x 2; 3.98, 2.85), 256^2 2.86 (32 x 4;
 // 4.00, 16 x 2 3.46), 300^2 3.33 (32 x 3; 4.10, 32 x 4 5.28), 384^2 3.46 (32 x 3; 4.46), 512^2 5.3
 // (march; 32 x 3 6.5).  Calls of one and two steps are launches of one step (one of two would
-// read and write the same sums), which march: 128^2 4.2 us (16 rows x 1 step 4.3), 300^2 4.75
-// (5.0).
+// read and write the same sums): 16 rows x 1 step while that fits; a march takes as long by
+// itself (128^2 5.0 us either way), but more when phi is read after it (7.2 / 7.7 us) or
+// recorded (4.8 / 5.2).
 //   single: the last step of a call in tiles (launch_phi_single), where they are one round of
 // the CUs and a march's waves, of 4 rows or more, spend as much on their margins: tile / march
 // 512^2 6.2 / 7.0, half storage 5.9 / 7.0, 64 x 4096 6.5 / 8.0, 441 x 400 6.45 / 6.6; with 3 rows
@@ -387,7 +388,9 @@ static BlockPlan block_plan(const lbm_ch_params& p, int64_t nsteps, int cus, int
   auto block_fits = [&](int rows, int t) { return fits(64 - 6 * t, rows - 6 * t); };
   // across walls regions and tiles would have to mirror their rows anew: marches
   if (p.walls) return BlockPlan{0, 1, false};
-  if (nsteps > 2) {
+  if (nsteps <= 2) {
+    if (block_fits(16, 1)) return BlockPlan{16, 1, false};
+  } else {
     if (block_fits(16, 2)) return BlockPlan{16, 2, false};
     for (int t : {4, 3, 2})
       if (block_fits(32, t)) return BlockPlan{32, t, false};
